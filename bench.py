@@ -101,7 +101,7 @@ def calibration_kernels():
 
 
 # Every source file that the device code is compiled from, in a fixed order.
-KERNEL_SOURCES = ("mma_kernels.hip", "mma_proto.h", "mma_xpacked.h")
+KERNEL_SOURCES = ("mma_kernels.hip", "mma_proto.h", "mma_xpacked.h", "mma_pool.h")
 
 
 def kernel_sources_sha256(root: str) -> str:

@@ -305,6 +305,36 @@ struct KvGeom {
   uint64_t layer_ptr[kMaxLayers];
 };
 
+// Table entries (pool slot | GPU block << 32) by the 32 bits at `shift`.
+// Counting passes of up to 11 bits: about 10 us for 4096 entries, where a
+// comparison sort takes some 200 (a 64k-token fetch in HBM takes 3 ms).
+inline void sort_table(std::vector<uint64_t>& v, uint32_t shift) {
+  const auto key = [shift](uint64_t e) { return static_cast<uint32_t>(e >> shift); };
+  if (v.size() < 64) {
+    std::sort(v.begin(), v.end(), [&](uint64_t a, uint64_t b) { return key(a) < key(b); });
+    return;
+  }
+  uint32_t top = 0;
+  for (uint64_t e : v) top |= key(e);
+  uint32_t bits = 1;
+  while (bits < 32 && top >> bits) ++bits;
+  const uint32_t passes = (bits + 10) / 11, width = (bits + passes - 1) / passes, mask = (1u << width) - 1;
+  std::vector<uint64_t> t(v.size());
+  std::vector<uint32_t> at(1u << width);
+  for (uint32_t p = 0; p < passes; ++p) {
+    std::fill(at.begin(), at.end(), 0u);
+    for (uint64_t e : v) ++at[(key(e) >> (p * width)) & mask];
+    uint32_t sum = 0;
+    for (uint32_t& c : at) {
+      const uint32_t n = c;
+      c = sum;
+      sum += n;
+    }
+    for (uint64_t e : v) t[at[(key(e) >> (p * width)) & mask]++] = e;
+    v.swap(t);
+  }
+}
+
 class Engine {
  public:
   Engine(int dir, const Config& cfg, Backend* be, Stats* st) : dir_(dir), cfg_(cfg), be_(be), st_(st) {}
@@ -329,7 +359,9 @@ class Engine {
     if ((rc = be_->alloc_records(sizeof(uint64_t) * kPoolTabEntries, &h, &d)) != MMA_OK) return rc;
     pool_tab_ = static_cast<uint64_t*>(h);
     pool_tab_dev_ = static_cast<uint64_t*>(d);
-    if ((rc = be_->alloc_device_state(sizeof(uint32_t) * kLightSlots, &d)) != MMA_OK) return rc;
+    if ((rc = be_->alloc_device_state(sizeof(uint64_t) * kPoolTabEntries, &d)) != MMA_OK) return rc;
+    pool_tab_copy_ = static_cast<uint64_t*>(d);
+    if ((rc = be_->alloc_device_state(sizeof(uint32_t) * kPoolCtrWords * kLightSlots, &d)) != MMA_OK) return rc;
     pool_ctr_ = static_cast<uint32_t*>(d);
     seg_used_.assign(kPoolTabEntries / kPoolTabSeg, 0);
     stage_bytes_ = stage_bytes;
@@ -427,6 +459,7 @@ class Engine {
       recs_ = nullptr;
       light_ = nullptr;
       pool_tab_ = nullptr;
+      pool_tab_copy_ = nullptr;
       pool_ctr_ = nullptr;
       return;
     }
@@ -439,11 +472,13 @@ class Engine {
     if (recs_) be_->free_records(recs_);
     if (light_) be_->free_records(light_);
     if (pool_tab_) be_->free_records(pool_tab_);
+    if (pool_tab_copy_) be_->free_device_state(pool_tab_copy_);
     if (pool_ctr_) be_->free_device_state(pool_ctr_);
     ds_ = nullptr;
     recs_ = nullptr;
     light_ = nullptr;
     pool_tab_ = nullptr;
+    pool_tab_copy_ = nullptr;
     pool_ctr_ = nullptr;
   }
 
@@ -733,12 +768,14 @@ class Engine {
     return grid;
   }
 
-  // An HBM pool launch: the table goes to the arena, the grid is sized to
-  // the spans (whole pieces for head-major blocks; at least one per wave, at
-  // most kPoolMaxWorkgroups workgroups),
-  // and the kernel is the transfer's only copy engine. Returns the grid.
+  // An HBM pool launch: the table goes to the arena and the kernel is the
+  // transfer's only copy engine. Returns a grid for the spans counted here (at
+  // least one per wave, at most kPoolMaxWorkgroups workgroups); the launch sizes
+  // its own (mma_pool.h).
   uint32_t prepare_pool(Transfer* x, const KvGeom* kv, KernelArgs& a) {
     const uint64_t nblk = x->pool_pairs.size();
+    // The kernel takes the pieces in the order of their destinations (mma_pool.h).
+    sort_table(x->pool_pairs, x->kind == Kind::kKvFetch ? 32 : 0);
     memcpy(pool_tab_ + static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg, x->pool_pairs.data(),
            nblk * sizeof(uint64_t));
     __atomic_thread_fence(__ATOMIC_RELEASE);
@@ -756,8 +793,12 @@ class Engine {
     x->waves = static_cast<uint32_t>(grid) * kWavesPerWG;
     fill_args(x, kv, 0, static_cast<uint32_t>(grid), 0, a);
     a.self_contained = 1;
-    a.pool_tab = pool_tab_dev_ + static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg;
-    a.pool_ctr = pool_ctr_ + x->light;
+    const uint64_t tab = static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg;
+    a.pool_tab = pool_tab_dev_ + tab;
+    a.pool_tab_host = pool_tab_ + tab;
+    a.pool_tab_copy = pool_tab_copy_ + tab;
+    a.pool_blocks = nblk;
+    a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;
     a.pool_units = units;
     a.pool_per_wg = per_wg;
@@ -1916,6 +1957,7 @@ class Engine {
   std::unique_ptr<CuEntry[]> light_ring_;  // scratch ring: light transfers' entries go to the kernel args
   uint64_t* pool_tab_ = nullptr;      // HBM pool launches' table arena (host address)
   uint64_t* pool_tab_dev_ = nullptr;  // the same, device address
+  uint64_t* pool_tab_copy_ = nullptr; // the arena's copy in device memory, for tables that do not fit the arguments
   uint32_t* pool_ctr_ = nullptr;      // per light slot: finished workgroups of its pool launch (device)
   std::vector<uint8_t> seg_used_;     // arena segments in use (mu_)
   DevState* ds_ = nullptr;

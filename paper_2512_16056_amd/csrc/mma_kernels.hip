@@ -32,6 +32,9 @@
 // mixed-contention workload.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstring>
+
 #include "mma_proto.h"
 #include "mma_xpacked.h"
 
@@ -640,89 +643,101 @@ __global__ __launch_bounds__(kBlock) void mma_whole_kernel(WholeArgs<N> a) {
 
 __global__ __launch_bounds__(kBlock) void mma_transfer_hnd_kernel(KernelArgs a) { transfer_body<kXeHnd>(a); }
 
-// One span of an HBM pool launch: n <= kPoolSpan bytes. A full, 16-byte
-// aligned span is read whole into registers before the first store, with
-// nontemporal loads and stores (every byte is moved once, so caching it would
-// only evict other data); a piece's shorter last span and misaligned spans
-// take plain loops.
-constexpr uint32_t kPoolVec = kPoolSpan / (kWave * 16);
-__device__ __forceinline__ void pool_span(const uint8_t* src, uint8_t* dst, uint32_t n, uint32_t lane) {
-  const uintptr_t mis = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u;
-  if (mis == 0 && n == kPoolSpan) {
-    const gu4* s = (const gu4*)(src) + lane;
-    gu4* d = (gu4*)(dst) + lane;
-    u32x4 v[kPoolVec];
-#pragma unroll
-    for (uint32_t i = 0; i < kPoolVec; ++i) v[i] = __builtin_nontemporal_load(s + i * kWave);
-#pragma unroll
-    for (uint32_t i = 0; i < kPoolVec; ++i) __builtin_nontemporal_store(v[i], d + i * kWave);
-    return;
-  }
-  if (mis == 0) {
-    const uint32_t n16 = n >> 4;
-    const gu4* s = (const gu4*)(src);
-    gu4* d = (gu4*)(dst);
-    for (uint32_t i = lane; i < n16; i += kWave) d[i] = s[i];
-    for (uint32_t i = (n16 << 4) + lane; i < n; i += kWave) dst[i] = src[i];
-    return;
-  }
-  for (uint32_t i = lane; i < n; i += kWave) dst[i] = src[i];
+// ---------------------------------------------------------------- HBM pool launches
+// A paged-KV transfer between a pool in this GPU's memory and the paged layer
+// tensors. Bound by HBM: every byte is read once and written once, in the order
+// of the destinations (mma_pool.h), with no ring and no host round trip.
+
+// Source and destination address of piece number q.
+struct PoolEnds {
+  uint64_t from, to;
+  uint32_t p;
+};
+__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
+  const PoolPiece pp = pool_piece(a.g, q);
+  const uint64_t e = a.tab ? a.tab[pp.entry] : a.w[a.layers + pp.entry];
+  const uint64_t pooled = a.pool + (e & 0xffffffffull) * a.slot_bytes + static_cast<uint64_t>(pp.p) * a.piece;
+  const uint64_t paged = a.w[pp.p >> 1] + (pp.p & 1u) * a.kstride + (e >> 32) * a.piece;
+  return PoolEnds{a.to_paged ? pooled : paged, a.to_paged ? paged : pooled, pp.p};
 }
 
-// A paged-KV transfer between a pool in this GPU's memory and the paged layer
-// tensors (piece layout): HBM-bound, so the launch is sized to the bytes, up
-// to kPoolMaxWorkgroups workgroups, with no ring and no host round trip. A
-// workgroup's spans are contiguous and its waves interleave over them, so a
-// wave meets one or two blocks and reads each one's table entry once. The
-// counter only orders the done tag after every workgroup has finished with its
-// table entries: the data itself becomes visible to later work through the
-// stream, when the kernel ends, as for any kernel (a device-wide release per
-// workgroup would write back the L2 of its XCD each time).
-// kHnd: GPU blocks in the head-major layout; a span is then a whole piece,
-// permuted row by row on its way (hnd_piece).
+// The workgroup that finishes last writes the done tag. The counters only order
+// the tag after every workgroup: the data itself becomes visible to later work
+// through the stream, when the kernel ends, as for any kernel (a device-wide
+// release per workgroup would write back the L2 of its XCD each time). A launch
+// of many workgroups counts them in up to kPoolCtrs groups first: two million
+// counts of an 8 GiB transfer do not queue up on one address.
+__device__ __forceinline__ void pool_finish(const PoolArgs& a) {
+  if (!a.done) return;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const uint32_t groups = max(1u, min(gridDim.x / 512u, 0u + kPoolCtrs));
+  if (groups > 1) {
+    const uint32_t i = blockIdx.x % groups, members = (gridDim.x - i + groups - 1) / groups;
+    uint32_t* c = a.ctr + (1 + i) * kPoolCtrStride;
+    if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
+    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const uint32_t members = groups > 1 ? groups : gridDim.x;
+  if (__hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
+  __hip_atomic_store(a.ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  st_sys(a.done, make_tag(a.seq, 0));
+}
+
+// Aligned pieces in the piece layout or (kHnd) head-major: one 16-byte unit per
+// lane. What hides the latency is the 32 waves a CU holds (the kernel takes few
+// registers), not loads in flight per wave, and small waves keep the writes in
+// order: 8 GiB fetch and offload 2.90 and 2.86 ms, 5.9 and 6.0 TB/s; with 32 KiB
+// read per wave before it writes 2.96 and 2.87, and 5.5 against 6.1 TB/s at 1 GiB.
+// Nontemporal: every byte is moved once, caching it would only evict other data.
 template <bool kHnd>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint64_t u0 = static_cast<uint64_t>(blockIdx.x) * a.per_wg;
-  const uint64_t u1 = min(a.units, u0 + a.per_wg);
-  const uint64_t per_blk = static_cast<uint64_t>(a.ppb) * a.spans;
-  uint64_t cur = ~0ull, pooled = 0, paged_off = 0;
-  for (uint64_t u = u0 + wave; u < u1; u += kWavesPerWG) {
-    const uint64_t i = u / per_blk;
-    const uint32_t r = static_cast<uint32_t>(u - i * per_blk);
-    const uint32_t p = r / a.spans;
-    const uint32_t sp = r - p * a.spans;
-    if (i != cur) {
-      cur = i;
-      const uint64_t e = ld_sys(&a.tab[i]);
-      pooled = a.pool + (e & 0xffffffffull) * a.slot_bytes;
-      paged_off = (e >> 32) * a.piece;
-    }
-    const uint64_t off = static_cast<uint64_t>(sp) * kPoolSpan;
-    const uint32_t n = static_cast<uint32_t>(min(static_cast<uint64_t>(kPoolSpan), a.piece - off));
-    uint8_t* host_side = reinterpret_cast<uint8_t*>(pooled + static_cast<uint64_t>(p) * a.piece + off);
-    uint8_t* gpu_side = reinterpret_cast<uint8_t*>(a.layer_ptr[p >> 1] + (p & 1u) * a.kstride + paged_off + off);
-    if constexpr (kHnd) {
-      const XGeom g{a.tokens, a.heads, a.row_bytes, a.elem, 0};
-      if (a.to_paged)
-        hnd_piece(host_side, gpu_side, true, g, lane);
-      else
-        hnd_piece(gpu_side, host_side, false, g, lane);
-    } else if (a.to_paged)
-      pool_span(host_side, gpu_side, n, lane);
-    else
-      pool_span(gpu_side, host_side, n, lane);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t prev = __hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == gridDim.x - 1) {
-      __hip_atomic_store(a.ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      st_sys(a.done, make_tag(a.seq, 0));
+  for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * kWavesPerWG + wave; w < a.g.waves;
+       w += static_cast<uint64_t>(gridDim.x) * kWavesPerWG) {
+    const PoolUnit x = pool_unit(a.g, static_cast<uint32_t>(w), lane);
+    if (x.ok) {
+      const PoolEnds e = pool_ends(a, x.q);
+      const gu4* src = (const gu4*)(e.from) + (kHnd ? hnd_src(a.hnd, x.u) : x.u);
+      __builtin_nontemporal_store(__builtin_nontemporal_load(src), (gu4*)(e.to) + x.u);
     }
   }
+  pool_finish(a);
+}
+
+// The other pieces, span by span (a.g counts a span as a row): x-packed ones
+// (kXE: element bytes) whole, through the wave's LDS tile; kXE = 0, pieces or
+// addresses that are no multiple of 16, in spans of kPoolSpan by wave_copy.
+template <uint32_t kXE>
+__global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const XGeom g{a.tokens, a.heads, a.row_bytes, a.elem, a.lds_wave};
+  for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * kWavesPerWG + wave; w < a.g.waves;
+       w += static_cast<uint64_t>(gridDim.x) * kWavesPerWG) {
+    const uint32_t q = div_by(a.g.rows, static_cast<uint32_t>(w));
+    PoolEnds e = pool_ends(a, q);
+    e.from = lane_u64(e.from, 0);
+    e.to = lane_u64(e.to, 0);
+    if constexpr (kXE != 0) {
+      xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
+                         e.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
+    } else {
+      const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * kPoolSpan;
+      wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
+                min(static_cast<uint64_t>(kPoolSpan), a.piece - off), lane);
+    }
+  }
+  pool_finish(a);
+}
+
+// A pool launch's block table from the arena in host memory to its copy in
+// device memory: 512 bytes per wave and read.
+__global__ __launch_bounds__(kBlock) void mma_kv_pool_table_kernel(PoolTabArgs a) {
+  const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (i < a.n) a.to[i] = ld_sys(a.from + i);
 }
 
 template <uint32_t E>
@@ -821,35 +836,75 @@ hipError_t launch_whole(const KernelArgs& args, uint32_t grid, hipStream_t strea
                          stream);
 }
 
-hipError_t launch_pool(const KernelArgs& args, uint32_t grid, hipStream_t stream) {
-  PoolArgs p;
+// One launch of the pool kernel its layout and alignment ask for. p holds
+// everything but the geometry.
+hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, hipStream_t stream) {
+  p.g = pool_geom(n, 2 * p.layers, p.piece, p.to_paged);
+  const void* k = nullptr;
+  uint32_t lds = 0;
+  if (layout == kKvLayoutHnd) {
+    p.hnd.X = p.to_paged ? p.heads : p.tokens;
+    p.hnd.Y = fast_div(p.to_paged ? p.tokens : p.heads);
+    p.hnd.C = fast_div(p.row_bytes / 16);
+    k = reinterpret_cast<const void*>(&mma_kv_pool_kernel<true>);
+  } else if (layout == kKvLayoutPiece && aligned) {
+    k = reinterpret_cast<const void*>(&mma_kv_pool_kernel<false>);
+  } else {
+    uint64_t spans = 1;
+    if (layout == kKvLayoutXPacked) {
+      lds = kWavesPerWG * p.lds_wave;
+      k = p.elem == 1   ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<1>)
+          : p.elem == 2 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<2>)
+          : p.elem == 4 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<4>)
+                        : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
+    } else {
+      spans = (p.piece + kPoolSpan - 1) / kPoolSpan;
+      k = reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<0>);
+    }
+    p.g.rows = fast_div(static_cast<uint32_t>(spans));
+    p.g.waves = spans * p.g.total;
+  }
+  // A launch has fewer than 2^32 threads; beyond that the waves go round again.
+  const uint64_t grid = std::min<uint64_t>((p.g.waves + kWavesPerWG - 1) / kWavesPerWG, 1u << 23);
+  void* params[] = {&p};
+  return hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
+}
+
+hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
+  static thread_local PoolArgs p;
   p.done = args.done;
   p.seq = args.seq;
   p.ctr = args.pool_ctr;
-  p.tab = args.pool_tab;
+  p.tab = nullptr;
   p.pool = args.pool_base;
-  p.units = args.pool_units;
-  p.per_wg = args.pool_per_wg;
-  p.ppb = 2 * args.kv_layers;
   p.piece = args.kv_piece_bytes;
-  p.slot_bytes = p.piece * p.ppb;
+  p.slot_bytes = p.piece * 2 * args.kv_layers;
   p.kstride = args.kv_kstride;
-  p.spans = args.pool_spans;
   p.to_paged = args.pool_to_paged;
   p.layers = args.kv_layers;
   p.tokens = args.kv_tokens;
   p.heads = args.kv_heads;
   p.row_bytes = args.kv_row_bytes;
   p.elem = args.kv_elem;
-  for (uint32_t l = 0; l < args.kv_layers; ++l) p.layer_ptr[l] = args.layer_ptr[l];
-  void* params[] = {&p};
-  const void* k = args.kv_layout == kKvLayoutHnd ? reinterpret_cast<const void*>(&mma_kv_pool_kernel<true>)
-                                                 : reinterpret_cast<const void*>(&mma_kv_pool_kernel<false>);
-  return hipLaunchKernel(k, dim3(grid), dim3(kBlock), params, 0, stream);
+  p.lds_wave = args.kv_lds_wave;
+  uint64_t mis = p.piece | p.pool;
+  for (uint32_t l = 0; l < p.layers; ++l) mis |= p.w[l] = args.layer_ptr[l];
+  if (p.layers + args.pool_blocks <= kPoolWords) {
+    memcpy(p.w + p.layers, args.pool_tab_host, args.pool_blocks * sizeof(uint64_t));
+  } else {
+    PoolTabArgs t{args.pool_tab, args.pool_tab_copy, args.pool_blocks};
+    void* params[] = {&t};
+    const hipError_t e =
+        hipLaunchKernel(reinterpret_cast<const void*>(&mma_kv_pool_table_kernel),
+                        dim3(static_cast<uint32_t>((t.n + kBlock - 1) / kBlock)), dim3(kBlock), params, 0, stream);
+    if (e != hipSuccess) return e;
+    p.tab = args.pool_tab_copy;
+  }
+  return launch_pool_kernel(p, static_cast<uint32_t>(args.pool_blocks), args.kv_layout, (mis & 15u) == 0, stream);
 }
 
 hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream) {
-  if (args.pool_tab) return launch_pool(args, grid, stream);
+  if (args.pool_tab) return launch_pool(args, stream);
   if (args.self_contained && args.kv_layers == 0) {  // linear: the lean kernel; KV: below, by layout
     if (args.n_pre <= 4) return launch_whole<4>(args, grid, stream);
     if (args.n_pre <= 16) return launch_whole<16>(args, grid, stream);

@@ -1,0 +1,122 @@
+// How an HBM pool launch (a paged-KV transfer whose pool is in this GPU's
+// memory) splits its pieces over waves. Plain arithmetic, shared by the launch,
+// the kernels and a CPU test that emulates every wave over it.
+//
+// Units of work are numbered in the order of their destinations, and the
+// hardware starts workgroups in that order, so that at any time the chip writes
+// a few compact regions: HBM takes that best. A fetch writes pieces all over the
+// layer tensors, an offload whole slots of the pool; so the table is sorted by
+// destination, a fetch goes piece-major (piece p of neighbouring blocks is
+// adjacent in the layer tensor) and an offload block-major.
+// Measured, kernel alone, read+write, 1 GiB and 8 GiB of payload:
+//                             32 KiB pieces               2 KiB pieces
+//   fetch / offload           6.17, 5.93 / 6.14, 6.00     5.98, 5.65 / 5.91, 5.87 TB/s
+//   the same, table unsorted  5.3 / 5.65                  5.2 / 5.2
+//   fetch block-major         5.4, 5.2                    4.9
+//   2, 4, 32 KiB per wave     6.06, 6.07, 5.51 (fetch, 1 GiB)
+//   each XCD its own eighth   5.92, 5.91 / 5.84, 5.78     5.44, 5.64 / 5.65, 5.72
+// and a plain copy of the same bytes 5.9 to 6.0.
+#ifndef MMA_POOL_H_
+#define MMA_POOL_H_
+
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define MMA_POOL_HD __host__ __device__
+#else
+#define MMA_POOL_HD
+#endif
+
+namespace mma {
+
+// Division by a number known at launch: the estimate by its reciprocal is exact
+// or one short.
+struct FastDiv {
+  uint32_t d, mul;
+};
+MMA_POOL_HD inline FastDiv fast_div(uint32_t d) {
+  return FastDiv{d, d > 1 ? static_cast<uint32_t>((1ull << 32) / d) : 0xffffffffu};
+}
+MMA_POOL_HD inline uint32_t div_by(const FastDiv& f, uint32_t n) {
+  const uint32_t q = static_cast<uint32_t>((static_cast<uint64_t>(n) * f.mul) >> 32);
+  return n - q * f.d >= f.d ? q + 1 : q;
+}
+
+// 16-byte units one wave moves with one load per lane.
+constexpr uint32_t kPoolRowUnits = 64;
+
+// The pieces of a launch: number q is piece q / div of table entry q % div
+// (by_piece: fetch, div = entries) or piece q % div of entry q / div (offload,
+// div = pieces per block). n * ppb fits 32 bits.
+struct PoolGeom {
+  uint32_t by_piece;
+  uint32_t total;    // pieces
+  FastDiv div;
+  // Rows of 64 units: a piece of 64 units or more takes rows.d of them, smaller
+  // pieces share one, per_row each (rows.d = 1).
+  uint32_t units;    // 16-byte units of a piece
+  FastDiv rows, piece_units;  // piece_units.d = units, where pieces share rows
+  uint32_t per_row;
+  uint64_t waves;
+};
+
+MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t piece, uint32_t by_piece) {
+  PoolGeom g;
+  g.by_piece = by_piece;
+  g.total = n * ppb;
+  g.div = fast_div(by_piece ? n : ppb);
+  g.units = static_cast<uint32_t>(piece >> 4);
+  const uint32_t u = g.units ? g.units : 1;
+  const uint32_t rows = (u + kPoolRowUnits - 1) / kPoolRowUnits;
+  g.rows = fast_div(rows);
+  g.piece_units = fast_div(u < kPoolRowUnits ? u : kPoolRowUnits);
+  g.per_row = u < kPoolRowUnits ? kPoolRowUnits / u : 1;
+  g.waves = g.per_row > 1 ? (static_cast<uint64_t>(g.total) + g.per_row - 1) / g.per_row
+                          : static_cast<uint64_t>(g.total) * rows;
+  return g;
+}
+
+// Table entry and piece of its block of piece number q.
+struct PoolPiece {
+  uint32_t entry, p;
+};
+MMA_POOL_HD inline PoolPiece pool_piece(const PoolGeom& g, uint32_t q) {
+  const uint32_t hi = div_by(g.div, q), lo = q - hi * g.div.d;
+  return PoolPiece{g.by_piece ? lo : hi, g.by_piece ? hi : lo};
+}
+
+// What a lane of wave w moves: unit u of piece number q, if ok.
+struct PoolUnit {
+  uint32_t q, u;
+  bool ok;
+};
+MMA_POOL_HD inline PoolUnit pool_unit(const PoolGeom& g, uint32_t w, uint32_t lane) {
+  PoolUnit x;
+  if (g.per_row > 1) {
+    const uint32_t j = div_by(g.piece_units, lane);
+    x.q = w * g.per_row + j;
+    x.u = lane - j * g.units;
+    x.ok = j < g.per_row && x.q < g.total;
+  } else {
+    x.q = div_by(g.rows, w);
+    x.u = (w - x.q * g.rows.d) * kPoolRowUnits + lane;
+    x.ok = x.u < g.units;
+  }
+  return x;
+}
+
+// Head-major blocks: a piece is X x Y rows of C units, stored [X][Y][C] at the
+// destination and [Y][X][C] at the source (fetch: X = heads, Y = tokens;
+// offload: the reverse). The source unit of destination unit u.
+struct HndMap {
+  uint32_t X;
+  FastDiv Y, C;
+};
+MMA_POOL_HD inline uint32_t hnd_src(const HndMap& m, uint32_t u) {
+  const uint32_t row = div_by(m.C, u), x = div_by(m.Y, row);
+  return ((row - x * m.Y.d) * m.X + x) * m.C.d + (u - row * m.C.d);
+}
+
+}  // namespace mma
+
+#endif  // MMA_POOL_H_

@@ -18,6 +18,8 @@
 
 #include <stdint.h>
 
+#include "mma_pool.h"
+
 namespace mma {
 
 constexpr uint32_t kRingSize = 4096;   // CU ring entries per record
@@ -32,14 +34,26 @@ constexpr uint32_t kMaxLdsPerWave = 36 * 1024;  // x-packed KV tiles: 4 waves x 
 constexpr uint32_t kWave = 64;
 constexpr uint32_t kWavesPerWG = 4;
 constexpr uint32_t kBlock = kWave * kWavesPerWG;
-// HBM pool launches (a paged-KV transfer whose pool is in device memory): a
-// piece is moved in spans of kPoolSpan bytes, one 16-byte unit per lane and
-// register, at most kPoolMaxWorkgroups workgroups per launch. The block table
-// goes to the kernel through an arena of kPoolTabEntries 8-byte entries in
-// device-visible host memory, handed out in segments of kPoolTabSeg entries.
+// HBM pool launches (a paged-KV transfer whose pool is in device memory, see
+// mma_pool.h). The block table goes through an arena of kPoolTabEntries 8-byte
+// entries, handed out in segments of kPoolTabSeg entries: kept in host memory
+// and, if it does not fit the launch's arguments beside the layer pointers
+// (kPoolWords in all), copied to device memory by a launch before it. Read from
+// host memory by the pool kernel itself, the entries cost one uncached PCIe read
+// per wave, about 80 ns each one after the other: 1.30 ms for 64 blocks of 2 MiB
+// that HBM moves in 45 us.
+// kPoolSpan: bytes a wave moves at a time where it cannot move 16-byte units, and
+// the unit in the engine's own count of a launch's work.
 constexpr uint32_t kPoolSpan = 8 * 1024;
 constexpr uint32_t kPoolMaxWorkgroups = 8192;
-constexpr uint32_t kPoolTabEntries = 1u << 19;
+constexpr uint32_t kPoolWords = 472;      // 3.9 KiB of arguments in all
+// Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
+// finished workgroups of group i, [0] the finished groups (one group: its
+// workgroups).
+constexpr uint32_t kPoolCtrs = 64;
+constexpr uint32_t kPoolCtrStride = 32;   // 128 bytes
+constexpr uint32_t kPoolCtrWords = (1 + kPoolCtrs) * kPoolCtrStride;
+constexpr uint32_t kPoolTabEntries = 1u << 21;
 constexpr uint32_t kPoolTabSeg = 512;
 
 // GPU block layouts of a paged-KV piece (one layer's K or V of one block). The
@@ -143,7 +157,10 @@ struct KernelArgs {
   // HBM pool launch (pool_tab non-null): the whole transfer is one launch of
   // mma_kv_pool_kernel, converted from these arguments (see PoolArgs).
   const uint64_t* pool_tab;  // per block: pool slot | GPU block << 32 (device-visible host memory)
-  uint32_t* pool_ctr;        // device counter of finished workgroups, 0 between launches
+  const uint64_t* pool_tab_host;  // the same, host address
+  uint64_t* pool_tab_copy;   // room for it in device memory
+  uint64_t pool_blocks;      // its entries
+  uint32_t* pool_ctr;        // device counters of finished workgroups, 0 between launches
   uint64_t pool_base;        // device address of the pool
   uint64_t pool_units;       // spans in the transfer
   uint64_t pool_per_wg;      // spans per workgroup
@@ -153,23 +170,28 @@ struct KernelArgs {
   uint64_t pre[kPrefill][3];  // words a, b, count|kind_p0 of the first ring entries
 };
 
-// Arguments of an HBM pool launch (GPU blocks in the piece or the head-major
-// layout). Span u is span s of piece p of block i,
-// u = (i * ppb + p) * spans + s (ppb = 2 * layers pieces per block, piece p =
-// layer p / 2, K for even p and V for odd); workgroup g takes spans
-// [g * per_wg, (g + 1) * per_wg). The workgroup that finishes last writes
-// done[0] = make_tag(seq, 0) and returns the counter to 0.
+// Arguments of an HBM pool launch. The workgroup that finishes last writes
+// done[0] = make_tag(seq, 0) and leaves the counters at 0 (done null: neither).
 struct PoolArgs {
   uint64_t* done;
   uint64_t seq;
   uint32_t* ctr;
-  const uint64_t* tab;
+  const uint64_t* tab;      // block table in device memory; null: w[layers ..]
   uint64_t pool;
-  uint64_t units, per_wg;
   uint64_t slot_bytes, piece, kstride;
-  uint32_t ppb, spans, to_paged, layers;
-  uint32_t tokens, heads, row_bytes, elem;  // head-major blocks: a piece is one unit (spans = 1)
-  uint64_t layer_ptr[kMaxLayers];
+  PoolGeom g;
+  uint32_t to_paged, layers;
+  HndMap hnd;               // head-major blocks
+  uint32_t tokens, heads, row_bytes, elem, lds_wave;  // x-packed blocks
+  uint64_t w[kPoolWords];   // layer pointers, then the block table if it fits
+};
+static_assert(sizeof(PoolArgs) <= 4096, "pool launch arguments");
+
+// Copies n table entries from device-visible host memory to device memory.
+struct PoolTabArgs {
+  const uint64_t* from;
+  uint64_t* to;
+  uint64_t n;
 };
 
 // Arguments of a self-contained launch (every entry of a linear transfer, no

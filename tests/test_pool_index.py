@@ -1,0 +1,82 @@
+"""How an HBM pool launch splits its pieces over waves, emulated on the CPU (no GPU).
+
+tests/cpp/pool_emu.cpp runs every lane of a launch over the kernel's own index maps
+(mma_pool.h) and checks bounds and that each destination byte is written exactly once;
+the result is compared here with the oracle, in the piece and head-major layouts and both
+directions.
+"""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import kv as okv
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    out = str(tmp_path_factory.mktemp("pool") / "libpoolemu.so")
+    cmd = [cxx, "-std=c++17", "-O1", "-g", "-shared", "-fPIC", "-Wall",
+           f"-I{os.path.join(ROOT, 'paper_2512_16056_amd', 'csrc')}",
+           os.path.join(ROOT, "tests", "cpp", "pool_emu.cpp"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    lib = ctypes.CDLL(out)
+    f = lib.emu_pool
+    f.restype = ctypes.c_int
+    f.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
+                  ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_int] + [ctypes.c_uint32] * 3)
+    f.div = lib.emu_div
+    f.div.restype = ctypes.c_uint64
+    f.div.argtypes = [ctypes.c_uint32] * 3
+    return f
+
+
+# tokens, heads, row bytes, layers, blocks: pieces of one unit, several to a row with lanes left over and
+# a short last row, just over half a row, exactly one row, a row and a unit, many rows with a short last
+# one; head rows that do and do not divide a wave's row
+SHAPES = [(1, 1, 16, 1, 5), (3, 1, 80, 2, 7), (16, 1, 64, 3, 9), (11, 3, 16, 1, 4), (13, 5, 16, 1, 3), (16, 5, 160, 2, 4),
+          (16, 4, 96, 3, 5), (16, 8, 64, 1, 3), (16, 8, 256, 2, 5), (16, 8, 272, 1, 3), (32, 8, 512, 1, 2),
+          (7, 3, 1040, 1, 3), (16, 2, 2048, 1, 2)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("layout", [okv.LAYOUT_PIECE, okv.LAYOUT_HND])
+def test_pool_index_maps_match_oracle(emu, shape, layout):
+    B, H, R, L, n = shape
+    piece, ppb, nb, slots = B * H * R, 2 * L, n + 3, n + 2
+    geom = (B, H, R, 1)
+    r = np.random.default_rng(B * 31 + H + R)
+    pool = r.integers(0, 256, (slots, ppb * piece), dtype=np.uint8)
+    cache = r.integers(0, 256, (L, 2, nb, piece), dtype=np.uint8)
+    hs = r.permutation(slots)[:n].astype(np.int32)
+    gb = np.sort(r.permutation(nb)[:n]).astype(np.int32)
+    tab = hs.astype(np.uint64) | (gb.astype(np.uint64) << np.uint64(32))
+
+    def run(p, c, to_paged):
+        rc = emu(p.ctypes.data, p.nbytes, c.ctypes.data, c.nbytes, tab.ctypes.data, n, ppb, piece, nb, to_paged,
+                 int(layout == okv.LAYOUT_HND), B, H, R)
+        assert rc == 0, rc
+
+    got = cache.copy()
+    run(pool.copy(), got, 1)
+    for l in range(L):
+        assert np.array_equal(got[l], okv.kv_fetch_layer(pool, cache[l], l, L, hs, gb, layout, geom)), l
+    got = pool.copy()
+    run(got, cache.copy(), 0)
+    assert np.array_equal(got, okv.kv_offload(pool, list(cache), gb, hs, layout, geom))
+
+
+def test_division_by_reciprocal(emu):
+    for d in [*range(1, 130), 255, 256, 257, 4095, 4096, 4097, 65521, 2 ** 28 - 1, 2 ** 28, 2 ** 31 + 1, 2 ** 32 - 1]:
+        for first in {0, max(d - 500, 0), 2 ** 28 // d * d - min(500, 2 ** 28 // d * d), 2 ** 32 - 1000}:
+            bad = emu.div(d, first, 1000)
+            assert bad == 0, (d, bad - 1)
