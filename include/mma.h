@@ -94,8 +94,8 @@ typedef struct mma_config {
                                SDMA engines reported by ROCr */
   uint32_t path_mask_d2h;   /* paths used device->host; same default */
   uint32_t cu_workgroups;   /* max workgroups (4 wave64 each) of the dummy-task kernel; default 16,
-                               at most 256 (x-packed KV transfers use up to 1.5 times this:
-                               their waves spend part of their time writing out an LDS tile);
+                               at most 256 (KV transfers in a transformed layout or in one
+                               launch use up to 1.5 times this: their waves have less in flight);
                                chunk_bytes / cu_sub_bytes must not exceed 2048 */
   uint32_t cu_sub_bytes;    /* bytes one wave moves per CU claim; default 64 KiB */
   uint32_t watchdog_ms;     /* wait-kernel gives up after this long without engine progress;
@@ -118,7 +118,8 @@ typedef struct mma_config {
                                trip (no start signal, no completion wait) -- below this size the
                                setup of several paths costs more than it gains (Section 3.2
                                fallback); default 24 MiB; 1 keeps every transfer on the multipath
-                               engine */
+                               engine. KV transfers up to this size, and larger ones whose blocks
+                               are at most chunk_bytes / 4, likewise take one launch */
   uint32_t cu_whole_bytes_d2h; /* the same for device->host; default 8 MiB (CU stores to host
                                memory reach the link less efficiently than CU loads, measured) */
   uint32_t control;         /* who drives a transfer once it is submitted (Section 6, Current

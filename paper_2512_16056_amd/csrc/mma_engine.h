@@ -139,7 +139,8 @@ struct Transfer {
   uint64_t pushed = 0, done_upto = 0;
   uint32_t waves = 0;          // waves of the dummy-task kernel
   bool pool_dev = false;       // KV pool in device memory: HBM gather/scatter, one entry per task
-  // HBM pool launch: the transfer is one launch of the pool kernel, which reads
+  // Pool launch: the KV transfer is one launch of a kernel of its own (HBM pool,
+  // or a host pool by link_eligible), which gets
   // the block table (pool slot | GPU block << 32 per block) from the engine's
   // table arena, segments [tab_seg, tab_seg + tab_nseg).
   bool pool_launch = false;
@@ -538,6 +539,29 @@ class Engine {
     return x->tasks.size() <= kPrefill;
   }
 
+  // A KV transfer with its pool in host memory that one launch over the link
+  // carries alone, unless that route is off (cu_whole_bytes[_d2h] = 1):
+  //  - within the whole-transfer limit, any but a few large pieces as they are on
+  //    the host, whose entries of whole pieces (whole_kv_per) are a little faster:
+  //    1, 2, 3 blocks of 2 MiB fetched in 43.3, 82.1, 120.1 us, by one launch 43.8,
+  //    83.0, 121.2; but head-major 49.5 / 44.0, x-packed 51.4 / 43.2, one block of
+  //    768 KiB 21.2 / 19.4, 8 blocks 318 / 313, 56 blocks of 147 KiB, which are
+  //    too many entries, 578 / 155;
+  //  - beyond it, blocks of at most a quarter of a chunk. The engine thread's
+  //    micro-tasks never span blocks, so with small ones the CU path's queue holds
+  //    too little and the copy engines get short commands. 512 MiB, ring / one
+  //    launch, fetch and offload in GB/s, by block:
+  //    256 KiB piece 46.3 / 57.4, 47.6 / 54.5; x-packed 34.1 / 53.5, 31.7 / 51.5
+  //    512 KiB piece 53.3 / 57.4, 53.4 / 54.5; x-packed 49.7 / 53.6, 45.6 / 51.6
+  //    1 MiB   piece 57.0 / 57.4, 56.6 / 54.6; x-packed 56.1 / 53.5, 54.3 / 51.6
+  // The launch has 1.5 times cu_workgroups at most, as the transformed layouts.
+  bool link_eligible(const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
+    if (!cu_enabled() || cfg_.static_split || cfg_.whole[dir_] <= 1) return false;
+    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / 4;
+    const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
+    return !few_large || payload_bytes > 12 * MiB;
+  }
+
   // Pieces per CU entry of a whole KV transfer: the engine thread's entry size,
   // grown until all of the transfer's entries fit the launch arguments (one
   // entry never spans two micro-tasks, i.e. two blocks); 0 if they cannot.
@@ -561,9 +585,12 @@ class Engine {
     bool light = whole_eligible(x, payload_bytes, kv);
     reap();
     std::unique_lock<std::mutex> lk(mu_);
-    // An HBM pool launch needs room for its table in the arena; without it the
-    // transfer takes the ring path like any other.
-    if (x->pool_launch) light = x->pool_launch = !g_fault_pool_no_table.load() && take_tab(x);
+    // A pool launch needs room for its table in the arena; without it the
+    // transfer goes on like any other.
+    if (x->pool_launch) {
+      x->pool_launch = !g_fault_pool_no_table.load() && take_tab(x);
+      light |= x->pool_launch;
+    }
     std::deque<uint32_t>& pool = light ? free_light_ : free_recs_;
     if (pool.empty() && !wait_for_pool(lk, pool, timeout_ms)) {
       give_tab(x);
@@ -768,14 +795,14 @@ class Engine {
     return grid;
   }
 
-  // An HBM pool launch: the table goes to the arena and the kernel is the
+  // A pool launch: the table goes to the arena and the kernel is the
   // transfer's only copy engine. Returns a grid for the spans counted here (at
   // least one per wave, at most kPoolMaxWorkgroups workgroups); the launch sizes
   // its own (mma_pool.h).
   uint32_t prepare_pool(Transfer* x, const KvGeom* kv, KernelArgs& a) {
     const uint64_t nblk = x->pool_pairs.size();
-    // The kernel takes the pieces in the order of their destinations (mma_pool.h).
-    sort_table(x->pool_pairs, x->kind == Kind::kKvFetch ? 32 : 0);
+    // In HBM the kernel takes the pieces in the order of their destinations (mma_pool.h).
+    if (x->pool_dev) sort_table(x->pool_pairs, x->kind == Kind::kKvFetch ? 32 : 0);
     memcpy(pool_tab_ + static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg, x->pool_pairs.data(),
            nblk * sizeof(uint64_t));
     __atomic_thread_fence(__ATOMIC_RELEASE);
@@ -798,6 +825,11 @@ class Engine {
     a.pool_tab_host = pool_tab_ + tab;
     a.pool_tab_copy = pool_tab_copy_ + tab;
     a.pool_blocks = nblk;
+    if (!x->pool_dev) {  // over the link: few workgroups, each with done tags of its own
+      a.pool_link = 1;
+      a.pool_wgs = static_cast<uint32_t>(std::min<uint64_t>(wg_cap(true), kPrefill));
+      x->pushed = a.pool_wgs;
+    }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;
     a.pool_units = units;
@@ -1226,7 +1258,7 @@ class Engine {
       st_->failed += 1;
     }
     if (counted) st_->transfers += 1;
-    if (x->pool_launch) st_->pool_launches += 1;
+    if (x->pool_launch && x->pool_dev) st_->pool_launches += 1;
     if (g_trace.load(std::memory_order_relaxed)) record_trace(x, bad);
     if (x->waiter) {
       std::lock_guard<std::mutex> g(x->waiter->mu);
@@ -2031,6 +2063,15 @@ inline std::unique_ptr<Transfer> make_list_transfer(int dir, const mma_copy_desc
   return x;
 }
 
+// What a pool launch of x needs: the pool's device-visible address and the table.
+inline void set_pool_table(Transfer* x, uint64_t pool, const int32_t* host_slots, const int32_t* gpu_blocks,
+                           uint64_t n) {
+  x->pool_base = pool;
+  x->pool_pairs.resize(n);
+  for (uint64_t i = 0; i < n; ++i)
+    x->pool_pairs[i] = static_cast<uint32_t>(host_slots[i]) | static_cast<uint64_t>(gpu_blocks[i]) << 32;
+}
+
 // Micro-tasks of a block-table KV transfer: host slot host_slots[i] <-> GPU
 // block gpu_blocks[i], ppb pieces of `piece` bytes per block. `host` is the
 // pool's address for the copy engines, pool_cu the CU path's.
@@ -2046,12 +2087,7 @@ inline std::unique_ptr<Transfer> make_kv_transfer(int dir, uint64_t piece, uint3
   x->piece = piece;
   x->pool_dev = pool_dev;
   x->sdma_ok = sdma_ok;
-  if (pool_dev) {
-    x->pool_base = host;
-    x->pool_pairs.resize(n);
-    for (uint64_t i = 0; i < n; ++i)
-      x->pool_pairs[i] = static_cast<uint32_t>(host_slots[i]) | static_cast<uint64_t>(gpu_blocks[i]) << 32;
-  }
+  if (pool_dev) set_pool_table(x.get(), host, host_slots, gpu_blocks, n);
   x->tasks.reserve(plan.size());
   const uint64_t slot_bytes = piece * ppb;
   for (const PlanItem& p : plan) {

@@ -643,22 +643,33 @@ __global__ __launch_bounds__(kBlock) void mma_whole_kernel(WholeArgs<N> a) {
 
 __global__ __launch_bounds__(kBlock) void mma_transfer_hnd_kernel(KernelArgs a) { transfer_body<kXeHnd>(a); }
 
-// ---------------------------------------------------------------- HBM pool launches
-// A paged-KV transfer between a pool in this GPU's memory and the paged layer
-// tensors. Bound by HBM: every byte is read once and written once, in the order
+// ---------------------------------------------------------------- pool launches
+// A paged-KV transfer between a pool and the paged layer tensors in one launch.
+// With the pool in this GPU's memory it is bound by HBM: every byte is read once and written once, in the order
 // of the destinations (mma_pool.h), with no ring and no host round trip.
 
-// Source and destination address of piece number q.
+// Source and destination address of piece number q. word(i): word i of the
+// arguments; kTab: the block table is in device memory instead.
 struct PoolEnds {
   uint64_t from, to;
   uint32_t p;
 };
-__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
+template <bool kTab, class Word>
+__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q, Word word) {
+  typedef __attribute__((address_space(1))) uint64_t gu64;
   const PoolPiece pp = pool_piece(a.g, q);
-  const uint64_t e = a.tab ? a.tab[pp.entry] : a.w[a.layers + pp.entry];
+  uint64_t e;
+  if constexpr (kTab)
+    e = ((const gu64*)(a.tab))[pp.entry];
+  else
+    e = word(a.layers + pp.entry);
   const uint64_t pooled = a.pool + (e & 0xffffffffull) * a.slot_bytes + static_cast<uint64_t>(pp.p) * a.piece;
-  const uint64_t paged = a.w[pp.p >> 1] + (pp.p & 1u) * a.kstride + (e >> 32) * a.piece;
+  const uint64_t paged = word(pp.p >> 1) + (pp.p & 1u) * a.kstride + (e >> 32) * a.piece;
   return PoolEnds{a.to_paged ? pooled : paged, a.to_paged ? paged : pooled, pp.p};
+}
+__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
+  const auto word = [&](uint32_t i) { return a.w[i]; };
+  return a.tab ? pool_ends<true>(a, q, word) : pool_ends<false>(a, q, word);
 }
 
 // The workgroup that finishes last writes the done tag. The counters only order
@@ -669,8 +680,13 @@ __device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
 // counts of an 8 GiB transfer do not queue up on one address.
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   if (!a.done) return;
+  if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   __syncthreads();
   if (threadIdx.x != 0) return;
+  if (a.tags) {  // few workgroups: tags of their own, no count (an atomic's round trip, about 1 us)
+    for (uint32_t t = blockIdx.x; t < a.tags; t += gridDim.x) st_sys(&a.done[t], make_tag(a.seq, t));
+    return;
+  }
   const uint32_t groups = max(1u, min(gridDim.x / 512u, 0u + kPoolCtrs));
   if (groups > 1) {
     const uint32_t i = blockIdx.x % groups, members = (gridDim.x - i + groups - 1) / groups;
@@ -684,6 +700,10 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   st_sys(a.done, make_tag(a.seq, 0));
 }
+
+// s_waitcnt vmcnt(0), the other counters left alone (gfx9 encoding).
+constexpr int kWaitVm0 = 0x0f70;
+constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link
 
 // Aligned pieces in the piece layout or (kHnd) head-major: one 16-byte unit per
 // lane. What hides the latency is the 32 waves a CU holds (the kernel takes few
@@ -700,7 +720,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
     const PoolUnit x = pool_unit(a.g, static_cast<uint32_t>(w), lane);
     if (x.ok) {
       const PoolEnds e = pool_ends(a, x.q);
-      const gu4* src = (const gu4*)(e.from) + (kHnd ? hnd_src(a.hnd, x.u) : x.u);
+      const gu4* src = (const gu4*)(e.from) + (kHnd ? hnd_other(a.hnd, x.u) : x.u);
       __builtin_nontemporal_store(__builtin_nontemporal_load(src), (gu4*)(e.to) + x.u);
     }
   }
@@ -725,10 +745,75 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
       xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
                          e.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
     } else {
-      const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * kPoolSpan;
+      const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * a.span;
       wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
-                min(static_cast<uint64_t>(kPoolSpan), a.piece - off), lane);
+                min(static_cast<uint64_t>(a.span), a.piece - off), lane);
     }
+  }
+  pool_finish(a);
+}
+
+// The same pieces with the pool in pinned host memory: bound by the PCIe link, so
+// few waves (the launch keeps to a limit of workgroups) with much in flight each.
+// A wave takes every nw-th span of kLinkRows rows: all addresses first (from the words in
+// LDS: the arguments are host memory), then all reads, then all writes. Rows count across pieces, so small
+// pieces fill a wave as large ones do. Reads past the last row repeat a unit of
+// piece 0. Over 64 MiB (36 layers of 2 KiB pieces / 32 layers of 32 KiB pieces):
+// fetch 1192 / 1190 us, 56.3 GB/s, where the link needs 1171; through the ring,
+// whose micro-tasks are no larger than a block, 4762 / 1211. Spans of 4 and 16 rows
+// took 1195 and 1245 us, all with 24 workgroups.
+// kShared: pieces below a row share one (each lane its own piece); else a row's
+// piece is the same for all lanes and its addresses are scalars.
+template <bool kHnd, bool kTab, bool kShared, class Word>
+__device__ __forceinline__ void link_span(const PoolArgs& a, uint32_t first, uint32_t lane, Word word) {
+  constexpr uint32_t K = kLinkRows;
+  const gu4* from[K];
+  gu4* to[K];
+#pragma unroll
+  for (uint32_t k = 0; k < K; ++k) {
+    const bool in = first + k < a.g.waves;
+    const PoolUnit x = pool_unit(a.g, in ? first + k : first, lane);
+    const bool ok = x.ok && in;
+    PoolEnds e;
+    if constexpr (kShared) {
+      e = pool_ends<kTab>(a, ok ? x.q : 0, word);
+    } else {
+      e = pool_ends<kTab>(a, __builtin_amdgcn_readfirstlane(x.q), word);
+      e.from = lane_u64(e.from, 0);
+      e.to = lane_u64(e.to, 0);
+    }
+    const uint32_t u = ok ? x.u : 0, v = kHnd ? hnd_other(a.hnd, u) : u;
+    from[k] = (const gu4*)(e.from) + (a.to_paged ? u : v);
+    to[k] = ok ? (gu4*)(e.to) + (a.to_paged ? v : u) : nullptr;
+  }
+  u32x4 v[K];
+#pragma unroll
+  for (uint32_t k = 0; k < K; ++k) v[k] = *from[k];
+  // All reads are in before the first write: left to itself the compiler, which
+  // loses count of them over the branches below, waits before every write, and
+  // so for the write before it too.
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (uint32_t k = 0; k < K; ++k)
+    if (to[k]) *to[k] = v[k];
+}
+
+template <bool kHnd, bool kTab>
+__global__ __launch_bounds__(kBlock) void mma_kv_link_kernel(PoolArgs a) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint64_t step = static_cast<uint64_t>(gridDim.x) * kWavesPerWG * kLinkRows;
+  __shared__ uint64_t s_w[kPoolWords];
+  for (uint32_t i = threadIdx.x; i < a.words; i += kBlock) s_w[i] = a.w[i];
+  __syncthreads();
+  const auto word = [&](uint32_t i) { return s_w[i]; };
+  for (uint64_t first = (static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x) * kLinkRows; first < a.g.waves;
+       first += step) {
+    if (a.g.per_row > 1)
+      link_span<kHnd, kTab, true>(a, static_cast<uint32_t>(first), lane, word);
+    else
+      link_span<kHnd, kTab, false>(a, static_cast<uint32_t>(first), lane, word);
   }
   pool_finish(a);
 }
@@ -836,19 +921,26 @@ hipError_t launch_whole(const KernelArgs& args, uint32_t grid, hipStream_t strea
                          stream);
 }
 
-// One launch of the pool kernel its layout and alignment ask for. p holds
-// everything but the geometry.
-hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, hipStream_t stream) {
-  p.g = pool_geom(n, 2 * p.layers, p.piece, p.to_paged);
+// One launch of the kernel that the pool's place, the layout and the alignment
+// ask for. p holds everything but the geometry; wgs: the most workgroups of a
+// launch over the link, 0 for a pool in HBM.
+hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, uint32_t wgs,
+                              hipStream_t stream) {
+  p.g = pool_geom(n, 2 * p.layers, p.piece, wgs ? 0 : p.to_paged);
   const void* k = nullptr;
-  uint32_t lds = 0;
+  uint32_t lds = 0, rows = 1;
   if (layout == kKvLayoutHnd) {
-    p.hnd.X = p.to_paged ? p.heads : p.tokens;
-    p.hnd.Y = fast_div(p.to_paged ? p.tokens : p.heads);
-    p.hnd.C = fast_div(p.row_bytes / 16);
-    k = reinterpret_cast<const void*>(&mma_kv_pool_kernel<true>);
+    const bool heads_first = !wgs && p.to_paged;
+    p.hnd = heads_first ? hnd_map(p.heads, p.tokens, p.row_bytes / 16) : hnd_map(p.tokens, p.heads, p.row_bytes / 16);
+    k = wgs ? (p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<true, true>)
+                     : reinterpret_cast<const void*>(&mma_kv_link_kernel<true, false>))
+            : reinterpret_cast<const void*>(&mma_kv_pool_kernel<true>);
+    rows = wgs ? kLinkRows : 1;
   } else if (layout == kKvLayoutPiece && aligned) {
-    k = reinterpret_cast<const void*>(&mma_kv_pool_kernel<false>);
+    k = wgs ? (p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<false, true>)
+                     : reinterpret_cast<const void*>(&mma_kv_link_kernel<false, false>))
+            : reinterpret_cast<const void*>(&mma_kv_pool_kernel<false>);
+    rows = wgs ? kLinkRows : 1;
   } else {
     uint64_t spans = 1;
     if (layout == kKvLayoutXPacked) {
@@ -858,14 +950,16 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
           : p.elem == 4 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<4>)
                         : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
     } else {
-      spans = (p.piece + kPoolSpan - 1) / kPoolSpan;
+      p.span = wgs ? 2 * kPoolSpan : kPoolSpan;
+      spans = (p.piece + p.span - 1) / p.span;
       k = reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<0>);
     }
     p.g.rows = fast_div(static_cast<uint32_t>(spans));
     p.g.waves = spans * p.g.total;
   }
   // A launch has fewer than 2^32 threads; beyond that the waves go round again.
-  const uint64_t grid = std::min<uint64_t>((p.g.waves + kWavesPerWG - 1) / kWavesPerWG, 1u << 23);
+  const uint64_t per_wg = static_cast<uint64_t>(kWavesPerWG) * rows;
+  const uint64_t grid = std::min<uint64_t>((p.g.waves + per_wg - 1) / per_wg, wgs ? wgs : 1u << 23);
   void* params[] = {&p};
   return hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
 }
@@ -887,9 +981,13 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
   p.row_bytes = args.kv_row_bytes;
   p.elem = args.kv_elem;
   p.lds_wave = args.kv_lds_wave;
+  p.release = args.release_each;
   uint64_t mis = p.piece | p.pool;
   for (uint32_t l = 0; l < p.layers; ++l) mis |= p.w[l] = args.layer_ptr[l];
+  p.words = p.layers;
+  p.tags = args.pool_link ? args.pool_wgs : 0;
   if (p.layers + args.pool_blocks <= kPoolWords) {
+    p.words += static_cast<uint32_t>(args.pool_blocks);
     memcpy(p.w + p.layers, args.pool_tab_host, args.pool_blocks * sizeof(uint64_t));
   } else {
     PoolTabArgs t{args.pool_tab, args.pool_tab_copy, args.pool_blocks};
@@ -900,7 +998,8 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
     if (e != hipSuccess) return e;
     p.tab = args.pool_tab_copy;
   }
-  return launch_pool_kernel(p, static_cast<uint32_t>(args.pool_blocks), args.kv_layout, (mis & 15u) == 0, stream);
+  return launch_pool_kernel(p, static_cast<uint32_t>(args.pool_blocks), args.kv_layout, (mis & 15u) == 0,
+                            args.pool_link ? args.pool_wgs : 0, stream);
 }
 
 hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream) {

@@ -1,5 +1,5 @@
-// How an HBM pool launch (a paged-KV transfer whose pool is in this GPU's
-// memory) splits its pieces over waves. Plain arithmetic, shared by the launch,
+// How a pool launch (a paged-KV transfer carried by one kernel, its pool in this
+// GPU's memory or on the host) splits its pieces over waves. Plain arithmetic, shared by the launch,
 // the kernels and a CPU test that emulates every wave over it.
 //
 // Units of work are numbered in the order of their destinations, and the
@@ -15,7 +15,8 @@
 //   fetch block-major         5.4, 5.2                    4.9
 //   2, 4, 32 KiB per wave     6.06, 6.07, 5.51 (fetch, 1 GiB)
 //   each XCD its own eighth   5.92, 5.91 / 5.84, 5.78     5.44, 5.64 / 5.65, 5.72
-// and a plain copy of the same bytes 5.9 to 6.0.
+// and a plain copy of the same bytes 5.9 to 6.0. A host pool is taken block-major
+// in table order, which reads or writes whole slots of it in a row.
 #ifndef MMA_POOL_H_
 #define MMA_POOL_H_
 
@@ -105,14 +106,18 @@ MMA_POOL_HD inline PoolUnit pool_unit(const PoolGeom& g, uint32_t w, uint32_t la
   return x;
 }
 
-// Head-major blocks: a piece is X x Y rows of C units, stored [X][Y][C] at the
-// destination and [Y][X][C] at the source (fetch: X = heads, Y = tokens;
-// offload: the reverse). The source unit of destination unit u.
+// Head-major blocks: a piece is X x Y rows of C units, stored [X][Y][C] on the
+// side whose order the lanes follow and [Y][X][C] on the other one. In HBM they
+// follow the destination (fetch: X = heads, Y = tokens; offload: the reverse),
+// over the link the host piece (X = tokens, Y = heads), so that PCIe requests
+// stay whole: a fetch that followed its destination read 160-byte rows at
+// 35-43 GB/s. The other side's unit for unit u.
 struct HndMap {
   uint32_t X;
   FastDiv Y, C;
 };
-MMA_POOL_HD inline uint32_t hnd_src(const HndMap& m, uint32_t u) {
+MMA_POOL_HD inline HndMap hnd_map(uint32_t X, uint32_t Y, uint32_t C) { return HndMap{X, fast_div(Y), fast_div(C)}; }
+MMA_POOL_HD inline uint32_t hnd_other(const HndMap& m, uint32_t u) {
   const uint32_t row = div_by(m.C, u), x = div_by(m.Y, row);
   return ((row - x * m.Y.d) * m.X + x) * m.C.d + (u - row * m.C.d);
 }

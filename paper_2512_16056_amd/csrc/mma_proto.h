@@ -42,11 +42,12 @@ constexpr uint32_t kBlock = kWave * kWavesPerWG;
 // host memory by the pool kernel itself, the entries cost one uncached PCIe read
 // per wave, about 80 ns each one after the other: 1.30 ms for 64 blocks of 2 MiB
 // that HBM moves in 45 us.
-// kPoolSpan: bytes a wave moves at a time where it cannot move 16-byte units, and
-// the unit in the engine's own count of a launch's work.
+// kPoolSpan: bytes a wave moves at a time in HBM where it cannot move 16-byte
+// units (twice that over the link), and the unit in the engine's own count of a
+// launch's work.
 constexpr uint32_t kPoolSpan = 8 * 1024;
 constexpr uint32_t kPoolMaxWorkgroups = 8192;
-constexpr uint32_t kPoolWords = 472;      // 3.9 KiB of arguments in all
+constexpr uint32_t kPoolWords = 468;      // 3.9 KiB of arguments in all
 // Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
 // finished workgroups of group i, [0] the finished groups (one group: its
 // workgroups).
@@ -160,6 +161,8 @@ struct KernelArgs {
   const uint64_t* pool_tab_host;  // the same, host address
   uint64_t* pool_tab_copy;   // room for it in device memory
   uint64_t pool_blocks;      // its entries
+  uint32_t pool_link;        // 1: the pool is host memory (mma_kv_link_kernel), pool_wgs its workgroups at most
+  uint32_t pool_wgs;
   uint32_t* pool_ctr;        // device counters of finished workgroups, 0 between launches
   uint64_t pool_base;        // device address of the pool
   uint64_t pool_units;       // spans in the transfer
@@ -180,9 +183,12 @@ struct PoolArgs {
   uint64_t pool;
   uint64_t slot_bytes, piece, kstride;
   PoolGeom g;
-  uint32_t to_paged, layers;
+  uint32_t to_paged, layers, release;  // release: 1: system-scope release before the done tag
   HndMap hnd;               // head-major blocks
   uint32_t tokens, heads, row_bytes, elem, lds_wave;  // x-packed blocks
+  uint32_t span;            // bytes of a span where 16-byte units cannot move
+  uint32_t words;           // of w in use
+  uint32_t tags;            // > 0: no counters, workgroup i writes done[i], done[i + grid], ... below tags
   uint64_t w[kPoolWords];   // layer pointers, then the block table if it fits
 };
 static_assert(sizeof(PoolArgs) <= 4096, "pool launch arguments");

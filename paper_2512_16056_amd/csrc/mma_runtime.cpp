@@ -979,9 +979,10 @@ static mma_status_t kv_common(const mma_kv_layout_t* lay, const void* host_pool,
   const bool sdma_ok = per_task <= rt->eng[dir]->stage_bytes() && !c.pool_dev;
   std::unique_ptr<Transfer> x = make_kv_transfer(dir, c.piece, c.ppb, reinterpret_cast<uint64_t>(host_pool),
                                                  c.pool_cu, c.pool_dev, sdma_ok, host_slots, gpu_blocks, n, rt->cfg);
-  // A pool in HBM: one launch of the pool kernel sized to the bytes, if the
-  // table finds room (acquire).
-  x->pool_launch = c.pool_dev;
+  // A pool in HBM, or a transfer over the link that one launch carries best: a
+  // pool launch, if the table finds room (acquire).
+  x->pool_launch = c.pool_dev || rt->eng[dir]->link_eligible(c.kv, n * c.slot_bytes, c.slot_bytes);
+  if (x->pool_launch && !c.pool_dev) set_pool_table(x.get(), c.pool_cu, host_slots, gpu_blocks, n);
   x->t_api = t_api;
   return submit(std::move(x), n * c.slot_bytes, stream, &c.kv);
 } catch (...) {

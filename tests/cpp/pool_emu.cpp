@@ -1,5 +1,5 @@
-// CPU emulation of an HBM pool launch over the kernel's own index maps
-// (paper_2512_16056_amd/csrc/mma_pool.h): every workgroup, wave, row and lane,
+// CPU emulation of a pool launch, in HBM (link = 0) or over the link, over the kernel's own index maps
+// (paper_2512_16056_amd/csrc/mma_pool.h): every wave, row and lane,
 // in the piece layout (hnd = 0) or the head-major one. Every access is checked
 // against its buffer, and every byte of the destination pieces must be written
 // exactly once. Built by tests/test_pool_index.py and compared there with the
@@ -14,10 +14,10 @@ using namespace mma;
 
 // pool: slots of ppb pieces; cache: [layers][2][nb][piece]; tab: slot | block << 32.
 extern "C" int emu_pool(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes, const uint64_t* tab,
-                        uint32_t n, uint32_t ppb, uint64_t piece, uint32_t nb, int to_paged, int hnd, uint32_t B,
-                        uint32_t H, uint32_t R) {
-  const PoolGeom g = pool_geom(n, ppb, piece, to_paged ? 1 : 0);
-  const HndMap m{to_paged ? H : B, fast_div(to_paged ? B : H), fast_div(R ? R / 16 : 1)};
+                        uint32_t n, uint32_t ppb, uint64_t piece, uint32_t nb, int to_paged, int hnd, int link,
+                        uint32_t B, uint32_t H, uint32_t R) {
+  const PoolGeom g = pool_geom(n, ppb, piece, to_paged && !link ? 1 : 0);
+  const HndMap m = to_paged && !link ? hnd_map(H, B, R / 16) : hnd_map(B, H, R / 16);
   std::vector<uint8_t> wrote(to_paged ? cache_bytes : pool_bytes, 0);
   const uint8_t* src = to_paged ? pool : cache;
   uint8_t* dst = to_paged ? cache : pool;
@@ -32,8 +32,11 @@ extern "C" int emu_pool(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint
       const uint64_t e = tab[pp.entry];
       const uint64_t in_pool = (e & 0xffffffffull) * ppb * piece + pp.p * piece;
       const uint64_t in_cache = pp.p * nb * piece + (e >> 32) * piece;
-      const uint64_t from = (to_paged ? in_pool : in_cache) + (hnd ? hnd_src(m, x.u) : x.u) * 16ull;
-      const uint64_t to = (to_paged ? in_cache : in_pool) + x.u * 16ull;
+      // the lanes follow the destination, over the link the pool
+      const uint64_t other = (hnd ? hnd_other(m, x.u) : x.u) * 16ull, own = x.u * 16ull;
+      const bool own_src = link && to_paged;
+      const uint64_t from = (to_paged ? in_pool : in_cache) + (own_src ? own : other);
+      const uint64_t to = (to_paged ? in_cache : in_pool) + (own_src ? other : own);
       if (from + 16 > src_bytes || to + 16 > dst_bytes) return 3;
       std::memcpy(dst + to, src + from, 16);
       for (uint32_t i = 0; i < 16; ++i)

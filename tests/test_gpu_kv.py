@@ -588,6 +588,67 @@ def test_kv_whole_transfers(gpu_layout):
             pool.free()
 
 
+LINK_SHAPES = {
+    # pieces of 256 bytes: four share a row; a short last row
+    "shared_rows": W.KVShape(layers=3, block_tokens=16, kv_heads=1, head_dim=16, elem_bytes=1, gpu_num_blocks=50,
+                             host_num_slots=48, n_blocks=37),
+    # 13 rows per piece, the last one half full; head rows of 160 bytes
+    "ragged_rows": W.KVShape(layers=2, block_tokens=16, kv_heads=5, head_dim=80, elem_bytes=2, gpu_num_blocks=20,
+                             host_num_slots=16, n_blocks=11),
+    # more blocks than the launch's arguments hold
+    "long_table": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=700,
+                            host_num_slots=650, n_blocks=600),
+    # above the whole-transfer limits, in small blocks
+    "many_small": W.KVShape(layers=4, block_tokens=16, kv_heads=2, head_dim=128, elem_bytes=2, gpu_num_blocks=520,
+                            host_num_slots=500, n_blocks=480),
+}
+
+
+@pytest.mark.parametrize("mis", [0, 3])
+@pytest.mark.parametrize("gpu_layout", [mma.MMA_KV_LAYOUT_PIECE, mma.MMA_KV_LAYOUT_HND, mma.MMA_KV_LAYOUT_XPACKED])
+@pytest.mark.parametrize("shape", list(LINK_SHAPES))
+def test_kv_link_launch(shape, gpu_layout, mis):
+    """KV transfers with a host pool that one launch carries over the link (default limits): no copy
+    engine takes part, and every byte matches the oracle in both directions. mis: a pool that is not
+    16-byte aligned (piece layout only)."""
+    if mis and gpu_layout != mma.MMA_KV_LAYOUT_PIECE:
+        pytest.skip("the transformed layouts need an aligned pool")
+    s = LINK_SHAPES[shape]
+    log(f"link launch {shape} layout={gpu_layout} mis={mis}")
+    ol = {mma.MMA_KV_LAYOUT_PIECE: okv.LAYOUT_PIECE, mma.MMA_KV_LAYOUT_HND: okv.LAYOUT_HND,
+          mma.MMA_KV_LAYOUT_XPACKED: okv.LAYOUT_XPACKED}[gpu_layout]
+    geom = _geom(s)
+    lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                        s.host_num_slots, gpu_layout)
+    hs, gb = W.kv_fetch_tables(s, cfg=3)
+    n = s.host_num_slots * s.slot_bytes
+    with session("both", cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+        raw = mma.PinnedBuffer(n + 16)
+        pool = raw.array[mis: mis + n]
+        pool[:] = np.random.default_rng(31).integers(0, 256, n, dtype=np.uint8)
+        layers = _layers(s, W.GPU_POISON)
+        before = _layer_views(s, layers)
+        mma.mma_kv_fetch(lay, pool, layers, hs, gb)
+        torch.cuda.synchronize()
+        pv = pool.reshape(s.host_num_slots, s.slot_bytes)
+        for l in range(s.layers):
+            want = okv.kv_fetch_layer(pv, before[l], l, s.layers, hs, gb, ol, geom)
+            assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), l
+        src = _layers(s, seed=700)
+        dest = np.roll(hs, 1).astype(np.int32)
+        want = okv.kv_offload(pv.copy(), _layer_views(s, src), gb, dest, ol, geom)
+        guard = raw.array[n + mis:].copy()
+        mma.mma_kv_offload(lay, pool, src, gb, dest)
+        torch.cuda.synchronize()
+        mma.mma_synchronize()
+        assert np.array_equal(pv, want) and np.array_equal(raw.array[n + mis:], guard)
+        st = mma.mma_get_stats()
+        assert sum(st["path_bytes"][:16]) == 0 and st["transfers"] == 2 and st["failed_transfers"] == 0
+        assert st["pool_launches"] == 0 and st["engine_wall_busy_ns"] == 0
+        del pool, pv
+        raw.free()
+
+
 def _fill_pool_c3(pool: np.ndarray, s: W.KVShape, hs: np.ndarray):
     v = pool.reshape(s.host_num_slots, s.slot_bytes)
     for i in range(s.n_blocks):

@@ -1,4 +1,4 @@
-"""How an HBM pool launch splits its pieces over waves, emulated on the CPU (no GPU).
+"""How a pool launch, in HBM or over the link, splits its pieces over waves, emulated on the CPU (no GPU).
 
 tests/cpp/pool_emu.cpp runs every lane of a launch over the kernel's own index maps
 (mma_pool.h) and checks bounds and that each destination byte is written exactly once;
@@ -33,7 +33,7 @@ def emu(tmp_path_factory):
     f = lib.emu_pool
     f.restype = ctypes.c_int
     f.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
-                  ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_int] + [ctypes.c_uint32] * 3)
+                  ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 3 + [ctypes.c_uint32] * 3)
     f.div = lib.emu_div
     f.div.restype = ctypes.c_uint64
     f.div.argtypes = [ctypes.c_uint32] * 3
@@ -48,9 +48,10 @@ SHAPES = [(1, 1, 16, 1, 5), (3, 1, 80, 2, 7), (16, 1, 64, 3, 9), (11, 3, 16, 1, 
           (7, 3, 1040, 1, 3), (16, 2, 2048, 1, 2)]
 
 
+@pytest.mark.parametrize("link", [0, 1])
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("layout", [okv.LAYOUT_PIECE, okv.LAYOUT_HND])
-def test_pool_index_maps_match_oracle(emu, shape, layout):
+def test_pool_index_maps_match_oracle(emu, shape, layout, link):
     B, H, R, L, n = shape
     piece, ppb, nb, slots = B * H * R, 2 * L, n + 3, n + 2
     geom = (B, H, R, 1)
@@ -63,7 +64,7 @@ def test_pool_index_maps_match_oracle(emu, shape, layout):
 
     def run(p, c, to_paged):
         rc = emu(p.ctypes.data, p.nbytes, c.ctypes.data, c.nbytes, tab.ctypes.data, n, ppb, piece, nb, to_paged,
-                 int(layout == okv.LAYOUT_HND), B, H, R)
+                 int(layout == okv.LAYOUT_HND), link, B, H, R)
         assert rc == 0, rc
 
     got = cache.copy()
