@@ -547,17 +547,17 @@ class Engine {
   //    83.0, 121.2; but head-major 49.5 / 44.0, x-packed 51.4 / 43.2, one block of
   //    768 KiB 21.2 / 19.4, 8 blocks 318 / 313, 56 blocks of 147 KiB, which are
   //    too many entries, 578 / 155;
-  //  - beyond it, blocks of at most a quarter of a chunk. The engine thread's
-  //    micro-tasks never span blocks, so with small ones the CU path's queue holds
-  //    too little and the copy engines get short commands. 512 MiB, ring / one
-  //    launch, fetch and offload in GB/s, by block:
-  //    256 KiB piece 46.3 / 57.4, 47.6 / 54.5; x-packed 34.1 / 53.5, 31.7 / 51.5
-  //    512 KiB piece 53.3 / 57.4, 53.4 / 54.5; x-packed 49.7 / 53.6, 45.6 / 51.6
-  //    1 MiB   piece 57.0 / 57.4, 56.6 / 54.6; x-packed 56.1 / 53.5, 54.3 / 51.6
+  //  - beyond it, blocks of at most half (offload: a quarter) of a chunk. The
+  //    engine thread's micro-tasks never span blocks, so with small ones the CU
+  //    path's queue holds too little and the copy engines get short commands.
+  //    512 MiB, ring / one launch, fetch and offload in GB/s, by block:
+  //    256 KiB piece 46.3 / 57.4, 47.6 / 55.6; x-packed 34.1 / 57.4, 31.7 / 55.5
+  //    512 KiB piece 53.3 / 57.4, 53.4 / 55.6; x-packed 49.7 / 57.4, 45.6 / 55.5
+  //    1 MiB   piece 57.0 / 57.4, 56.6 / 55.6; x-packed 56.1 / 57.4, 54.3 / 55.5
   // The launch has 1.5 times cu_workgroups at most, as the transformed layouts.
   bool link_eligible(const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
     if (!cu_enabled() || cfg_.static_split || cfg_.whole[dir_] <= 1) return false;
-    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / 4;
+    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / (dir_ == MMA_H2D ? 2 : 4);
     const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
     return !few_large || payload_bytes > 12 * MiB;
   }
@@ -825,10 +825,19 @@ class Engine {
     a.pool_tab_host = pool_tab_ + tab;
     a.pool_tab_copy = pool_tab_copy_ + tab;
     a.pool_blocks = nblk;
-    if (!x->pool_dev) {  // over the link: few workgroups, each with done tags of its own
+    if (!x->pool_dev) {  // over the link: few workgroups
       a.pool_link = 1;
       a.pool_wgs = static_cast<uint32_t>(std::min<uint64_t>(wg_cap(true), kPrefill));
-      x->pushed = a.pool_wgs;
+      // A large transfer's waves claim their spans. Below, fixed shares and done
+      // tags per workgroup save the counts' round trips. Fixed / claimed: fetch,
+      // 8 MiB 158 / 159 us, 16 MiB 312 / 302, 64 MiB 1237 / 1184; offload, 64 MiB
+      // 1231 / 1237, 512 MiB 9815 / 9678; x-packed, whose waves' speeds differ
+      // most, fetch 7 MiB 145 / 138, offload 8 MiB 188 / 196, 16 MiB 361 / 346,
+      // 512 MiB 10531 / 9672.
+      const bool xp = kv->layout == kKvLayoutXPacked;
+      const uint64_t from = dir_ == MMA_H2D ? (xp ? 6 : 16) * MiB : (xp ? 16 : 128) * MiB;
+      a.pool_claim = x->bytes >= from ? 1 : 0;
+      if (!a.pool_claim) x->pushed = a.pool_wgs;
     }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;

@@ -679,7 +679,7 @@ __device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
 // of many workgroups counts them in up to kPoolCtrs groups first: two million
 // counts of an 8 GiB transfer do not queue up on one address.
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
-  if (!a.done) return;
+  if (!a.done && !a.claim) return;
   if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -697,8 +697,30 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   const uint32_t members = groups > 1 ? groups : gridDim.x;
   if (__hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
   __hip_atomic_store(a.ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (a.claim) __hip_atomic_store(a.claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  st_sys(a.done, make_tag(a.seq, 0));
+  if (a.done) st_sys(a.done, make_tag(a.seq, 0));
+}
+
+// The spans of one wave of a launch with fewer waves than spans: its own first,
+// then every nw-th, or, with a claim counter, the next one nobody has taken. Over
+// the link the waves' shares of it differ, and with fixed shares the slow ones
+// leave it idle at the end: x-packed fetches 53.5 GB/s, with claims 57.
+struct SpanWalk {
+  uint64_t at, nw;
+  uint32_t got;
+};
+__device__ __forceinline__ SpanWalk span_walk(uint32_t wave) {
+  return SpanWalk{static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x,
+                  static_cast<uint64_t>(gridDim.x) * kWavesPerWG, 0};
+}
+// Before the span's own reads, so that the claim's round trip overlaps theirs.
+__device__ __forceinline__ void span_claim(const PoolArgs& a, SpanWalk& s, uint32_t lane) {
+  if (a.claim && lane == 0)
+    s.got = __hip_atomic_fetch_add(a.claim, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void span_next(const PoolArgs& a, SpanWalk& s) {
+  s.at = a.claim ? s.nw + __builtin_amdgcn_readfirstlane(s.got) : s.at + s.nw;
 }
 
 // s_waitcnt vmcnt(0), the other counters left alone (gfx9 encoding).
@@ -728,26 +750,29 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
 }
 
 // The other pieces, span by span (a.g counts a span as a row): x-packed ones
-// (kXE: element bytes) whole, through the wave's LDS tile; kXE = 0, pieces or
+// (kXE: element bytes) whole, through the wave's LDS tile, a.group at a time; kXE = 0, pieces or
 // addresses that are no multiple of 16, in spans of kPoolSpan by wave_copy.
 template <uint32_t kXE>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const XGeom g{a.tokens, a.heads, a.row_bytes, a.elem, a.lds_wave};
-  for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * kWavesPerWG + wave; w < a.g.waves;
-       w += static_cast<uint64_t>(gridDim.x) * kWavesPerWG) {
-    const uint32_t q = div_by(a.g.rows, static_cast<uint32_t>(w));
-    PoolEnds e = pool_ends(a, q);
-    e.from = lane_u64(e.from, 0);
-    e.to = lane_u64(e.to, 0);
-    if constexpr (kXE != 0) {
-      xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
-                         e.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
-    } else {
-      const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * a.span;
-      wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
-                min(static_cast<uint64_t>(a.span), a.piece - off), lane);
+  for (SpanWalk s = span_walk(wave); s.at * a.group < a.g.waves; span_next(a, s)) {
+    span_claim(a, s, lane);
+    const uint64_t end = min(a.g.waves, (s.at + 1) * a.group);
+    for (uint64_t w = s.at * a.group; w < end; ++w) {
+      const uint32_t q = div_by(a.g.rows, static_cast<uint32_t>(w));
+      PoolEnds e = pool_ends(a, q);
+      e.from = lane_u64(e.from, 0);
+      e.to = lane_u64(e.to, 0);
+      if constexpr (kXE != 0) {
+        xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
+                           e.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
+      } else {
+        const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * a.span;
+        wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
+                  min(static_cast<uint64_t>(a.span), a.piece - off), lane);
+      }
     }
   }
   pool_finish(a);
@@ -755,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
 
 // The same pieces with the pool in pinned host memory: bound by the PCIe link, so
 // few waves (the launch keeps to a limit of workgroups) with much in flight each.
-// A wave takes every nw-th span of kLinkRows rows: all addresses first (from the words in
+// A wave takes span after span of kLinkRows rows (SpanWalk): all addresses first (from the words in
 // LDS: the arguments are host memory), then all reads, then all writes. Rows count across pieces, so small
 // pieces fill a wave as large ones do. Reads past the last row repeat a unit of
 // piece 0. Over 64 MiB (36 layers of 2 KiB pieces / 32 layers of 32 KiB pieces):
@@ -803,13 +828,13 @@ template <bool kHnd, bool kTab>
 __global__ __launch_bounds__(kBlock) void mma_kv_link_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint64_t step = static_cast<uint64_t>(gridDim.x) * kWavesPerWG * kLinkRows;
   __shared__ uint64_t s_w[kPoolWords];
   for (uint32_t i = threadIdx.x; i < a.words; i += kBlock) s_w[i] = a.w[i];
   __syncthreads();
   const auto word = [&](uint32_t i) { return s_w[i]; };
-  for (uint64_t first = (static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x) * kLinkRows; first < a.g.waves;
-       first += step) {
+  for (SpanWalk s = span_walk(wave); s.at * kLinkRows < a.g.waves; span_next(a, s)) {
+    const uint64_t first = s.at * kLinkRows;
+    span_claim(a, s, lane);
     if (a.g.per_row > 1)
       link_span<kHnd, kTab, true>(a, static_cast<uint32_t>(first), lane, word);
     else
@@ -956,6 +981,10 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
     }
     p.g.rows = fast_div(static_cast<uint32_t>(spans));
     p.g.waves = spans * p.g.total;
+    // A claim's round trip pays for 8 KiB at least (2 KiB pieces one by one:
+    // 44 GB/s, 48 without claims).
+    p.group = p.claim ? static_cast<uint32_t>(std::max<uint64_t>(1, kPoolSpan / p.piece)) : 1;
+    rows = p.group;
   }
   // A launch has fewer than 2^32 threads; beyond that the waves go round again.
   const uint64_t per_wg = static_cast<uint64_t>(kWavesPerWG) * rows;
@@ -985,7 +1014,8 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
   uint64_t mis = p.piece | p.pool;
   for (uint32_t l = 0; l < p.layers; ++l) mis |= p.w[l] = args.layer_ptr[l];
   p.words = p.layers;
-  p.tags = args.pool_link ? args.pool_wgs : 0;
+  p.tags = args.pool_link && !args.pool_claim ? args.pool_wgs : 0;
+  p.claim = args.pool_claim ? args.pool_ctr + kPoolCtrStride : nullptr;
   if (p.layers + args.pool_blocks <= kPoolWords) {
     p.words += static_cast<uint32_t>(args.pool_blocks);
     memcpy(p.w + p.layers, args.pool_tab_host, args.pool_blocks * sizeof(uint64_t));

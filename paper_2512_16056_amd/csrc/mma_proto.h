@@ -47,10 +47,10 @@ constexpr uint32_t kBlock = kWave * kWavesPerWG;
 // launch's work.
 constexpr uint32_t kPoolSpan = 8 * 1024;
 constexpr uint32_t kPoolMaxWorkgroups = 8192;
-constexpr uint32_t kPoolWords = 468;      // 3.9 KiB of arguments in all
+constexpr uint32_t kPoolWords = 466;      // 3.9 KiB of arguments in all
 // Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
 // finished workgroups of group i, [0] the finished groups (one group: its
-// workgroups).
+// workgroups; [1] then is free for the claims of a launch over the link).
 constexpr uint32_t kPoolCtrs = 64;
 constexpr uint32_t kPoolCtrStride = 32;   // 128 bytes
 constexpr uint32_t kPoolCtrWords = (1 + kPoolCtrs) * kPoolCtrStride;
@@ -163,6 +163,7 @@ struct KernelArgs {
   uint64_t pool_blocks;      // its entries
   uint32_t pool_link;        // 1: the pool is host memory (mma_kv_link_kernel), pool_wgs its workgroups at most
   uint32_t pool_wgs;
+  uint32_t pool_claim;       // 1: its waves claim their spans (else fixed shares and a done tag per workgroup)
   uint32_t* pool_ctr;        // device counters of finished workgroups, 0 between launches
   uint64_t pool_base;        // device address of the pool
   uint64_t pool_units;       // spans in the transfer
@@ -179,6 +180,7 @@ struct PoolArgs {
   uint64_t* done;
   uint64_t seq;
   uint32_t* ctr;
+  uint32_t* claim;          // counter of claimed spans, 0 between launches; null: fixed shares
   const uint64_t* tab;      // block table in device memory; null: w[layers ..]
   uint64_t pool;
   uint64_t slot_bytes, piece, kstride;
@@ -187,6 +189,7 @@ struct PoolArgs {
   HndMap hnd;               // head-major blocks
   uint32_t tokens, heads, row_bytes, elem, lds_wave;  // x-packed blocks
   uint32_t span;            // bytes of a span where 16-byte units cannot move
+  uint32_t group;           // spans that go together
   uint32_t words;           // of w in use
   uint32_t tags;            // > 0: no counters, workgroup i writes done[i], done[i + grid], ... below tags
   uint64_t w[kPoolWords];   // layer pointers, then the block table if it fits
