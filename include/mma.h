@@ -379,14 +379,15 @@ mma_status_t mma_kv_offload(const mma_kv_layout_t* layout, void* host_pool, cons
  * forbid hipMalloc. The same operation, arguments, validation and errors as
  * mma_kv_fetch (every GPU block layout; a pinned host pool or a pool in this
  * GPU's memory), and the same bytes in the GPU cache. It makes no hipMalloc,
- * hipHostMalloc or hipFree call and uses no buffer of the engine: the block
- * table and a claim counter live in `scratch`, a fixed array of the library's
- * device code (256 B + 8 B per block, 512 KiB + 256 B in all per GPU, held
- * until the process ends), whose address mma_init looks up. The table reaches
- * it through the arguments of ceil(n_blocks / 448) small kernel launches on
- * `stream`, then one launch carries every piece on the CU path alone (no copy
- * engine, no engine thread); the transfer is complete when that launch
- * completes on the stream, and it does not appear in mma_get_stats.
+ * hipHostMalloc or hipFree call and uses no buffer of the engine. One launch on
+ * `stream` carries every piece on the CU path alone (no copy engine, no engine
+ * thread); the transfer is complete when that launch completes on the stream,
+ * and it does not appear in mma_get_stats. Layer pointers and block table travel
+ * in its arguments up to 466 of them in all; a longer table goes to `scratch`, a
+ * fixed array of the library's device code (256 B of counters + 8 B per block,
+ * 512 KiB + 256 B in all per GPU, held until the process ends) whose address
+ * mma_init looks up, through the arguments of ceil(n_blocks / 448) small launches
+ * before.
  * n_blocks at most 65536: larger calls return MMA_ERR_INVALID_ARG and enqueue
  * nothing. Every call on one GPU shares its scratch array, which keeps the
  * last call's table: calls that may overlap on one GPU (other streams, other

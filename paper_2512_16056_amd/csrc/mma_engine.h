@@ -309,31 +309,44 @@ struct KvGeom {
 // Table entries (pool slot | GPU block << 32) by the 32 bits at `shift`.
 // Counting passes of up to 11 bits: about 10 us for 4096 entries, where a
 // comparison sort takes some 200 (a 64k-token fetch in HBM takes 3 ms).
-inline void sort_table(std::vector<uint64_t>& v, uint32_t shift) {
+// tmp: room for n entries.
+inline void sort_table(uint64_t* v, size_t n, uint32_t shift, uint64_t* tmp) {
   const auto key = [shift](uint64_t e) { return static_cast<uint32_t>(e >> shift); };
-  if (v.size() < 64) {
-    std::sort(v.begin(), v.end(), [&](uint64_t a, uint64_t b) { return key(a) < key(b); });
+  if (n < 64) {
+    std::sort(v, v + n, [&](uint64_t a, uint64_t b) { return key(a) < key(b); });
     return;
   }
   uint32_t top = 0;
-  for (uint64_t e : v) top |= key(e);
+  for (size_t i = 0; i < n; ++i) top |= key(v[i]);
   uint32_t bits = 1;
   while (bits < 32 && top >> bits) ++bits;
   const uint32_t passes = (bits + 10) / 11, width = (bits + passes - 1) / passes, mask = (1u << width) - 1;
-  std::vector<uint64_t> t(v.size());
-  std::vector<uint32_t> at(1u << width);
+  uint32_t at[1u << 11];
+  uint64_t *from = v, *to = tmp;
   for (uint32_t p = 0; p < passes; ++p) {
-    std::fill(at.begin(), at.end(), 0u);
-    for (uint64_t e : v) ++at[(key(e) >> (p * width)) & mask];
+    std::fill(at, at + mask + 1, 0u);
+    for (size_t i = 0; i < n; ++i) ++at[(key(from[i]) >> (p * width)) & mask];
     uint32_t sum = 0;
-    for (uint32_t& c : at) {
-      const uint32_t n = c;
-      c = sum;
-      sum += n;
+    for (uint32_t c = 0; c <= mask; ++c) {
+      const uint32_t k = at[c];
+      at[c] = sum;
+      sum += k;
     }
-    for (uint64_t e : v) t[at[(key(e) >> (p * width)) & mask]++] = e;
-    v.swap(t);
+    for (size_t i = 0; i < n; ++i) to[at[(key(from[i]) >> (p * width)) & mask]++] = from[i];
+    std::swap(from, to);
   }
+  if (from != v) std::copy(from, from + n, v);
+}
+
+// Whether the waves of a launch over the link claim their spans. Below these sizes
+// fixed shares and done tags per workgroup save the counts' round trips. Fixed /
+// claimed: fetch, 8 MiB 158 / 159 us, 16 MiB 312 / 302, 64 MiB 1237 / 1184;
+// offload, 64 MiB 1231 / 1237, 512 MiB 9815 / 9678; x-packed, whose waves' speeds
+// differ most, fetch 7 MiB 145 / 138, offload 8 MiB 188 / 196, 16 MiB 361 / 346,
+// 512 MiB 10531 / 9672.
+inline bool link_claims(int dir, uint32_t layout, uint64_t bytes) {
+  const bool xp = layout == kKvLayoutXPacked;
+  return bytes >= (dir == MMA_H2D ? (xp ? 6 : 16) * MiB : (xp ? 16 : 128) * MiB);
 }
 
 class Engine {
@@ -802,7 +815,10 @@ class Engine {
   uint32_t prepare_pool(Transfer* x, const KvGeom* kv, KernelArgs& a) {
     const uint64_t nblk = x->pool_pairs.size();
     // In HBM the kernel takes the pieces in the order of their destinations (mma_pool.h).
-    if (x->pool_dev) sort_table(x->pool_pairs, x->kind == Kind::kKvFetch ? 32 : 0);
+    if (x->pool_dev) {
+      std::vector<uint64_t> tmp(nblk);
+      sort_table(x->pool_pairs.data(), nblk, x->kind == Kind::kKvFetch ? 32 : 0, tmp.data());
+    }
     memcpy(pool_tab_ + static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg, x->pool_pairs.data(),
            nblk * sizeof(uint64_t));
     __atomic_thread_fence(__ATOMIC_RELEASE);
@@ -828,15 +844,7 @@ class Engine {
     if (!x->pool_dev) {  // over the link: few workgroups
       a.pool_link = 1;
       a.pool_wgs = static_cast<uint32_t>(std::min<uint64_t>(wg_cap(true), kPrefill));
-      // A large transfer's waves claim their spans. Below, fixed shares and done
-      // tags per workgroup save the counts' round trips. Fixed / claimed: fetch,
-      // 8 MiB 158 / 159 us, 16 MiB 312 / 302, 64 MiB 1237 / 1184; offload, 64 MiB
-      // 1231 / 1237, 512 MiB 9815 / 9678; x-packed, whose waves' speeds differ
-      // most, fetch 7 MiB 145 / 138, offload 8 MiB 188 / 196, 16 MiB 361 / 346,
-      // 512 MiB 10531 / 9672.
-      const bool xp = kv->layout == kKvLayoutXPacked;
-      const uint64_t from = dir_ == MMA_H2D ? (xp ? 6 : 16) * MiB : (xp ? 16 : 128) * MiB;
-      a.pool_claim = x->bytes >= from ? 1 : 0;
+      a.pool_claim = link_claims(dir_, kv->layout, x->bytes) ? 1 : 0;
       if (!a.pool_claim) x->pushed = a.pool_wgs;
     }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;

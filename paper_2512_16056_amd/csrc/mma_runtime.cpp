@@ -22,7 +22,7 @@ hipError_t launch_digest(const void* ptr, uint64_t bytes, uint64_t* out, hipStre
 hipError_t noalloc_setup(int dev);
 uint64_t* noalloc_scratch(int dev);
 hipError_t launch_noalloc_table(const NoallocTabArgs& t, hipStream_t stream);
-hipError_t launch_noalloc(const NoallocArgs& a, uint32_t grid, hipStream_t stream);
+hipError_t launch_noalloc(PoolArgs& p, uint32_t n, uint32_t layout, uint32_t wgs, hipStream_t stream);
 
 namespace {
 
@@ -996,6 +996,9 @@ std::mutex g_noalloc_mu;
 constexpr uint32_t kNoallocBitmapBits = 1u << 24;
 uint64_t g_noalloc_seen[kNoallocBitmapBits / 64];
 int32_t g_noalloc_sorted[kNoallocMaxBlocks];
+// The table of the call being launched, and room to sort it.
+std::mutex g_noalloc_tab_mu;
+uint64_t g_noalloc_tab[kNoallocMaxBlocks], g_noalloc_tmp[kNoallocMaxBlocks];
 
 bool noalloc_tables_valid(const int32_t* src, uint32_t src_count, const int32_t* dst, uint32_t dst_count,
                           uint64_t n) {
@@ -1053,49 +1056,51 @@ mma_status_t mma_kv_fetch_noalloc(const mma_kv_layout_t* layout, const void* hos
   if ((s = kv_check(layout, host_pool, const_cast<const void* const*>(gpu_layers), host_slots, gpu_blocks, n_blocks,
                     MMA_H2D, noalloc_tables_valid, &c)))
     return s;
-  NoallocArgs a;
-  memset(&a, 0, sizeof a);
-  a.scratch = scratch;
+  static thread_local PoolArgs a;
+  memset(&a, 0, offsetof(PoolArgs, w));
+  a.ctr = reinterpret_cast<uint32_t*>(scratch);
   a.pool = c.pool_cu;
   a.slot_bytes = c.slot_bytes;
   a.piece = c.piece;
   a.kstride = c.kv.kstride;
-  a.ppb = c.ppb;
-  a.units = n_blocks * c.ppb;
-  a.per_claim = static_cast<uint32_t>(std::max<uint64_t>(1, rt->cfg.sub / c.piece));
-  a.layout = c.kv.layout;
+  a.to_paged = 1;
+  a.layers = c.kv.layers;
   a.tokens = c.kv.tokens;
   a.heads = c.kv.heads;
   a.row_bytes = c.kv.row_bytes;
   a.elem = c.kv.elem;
   a.lds_wave = c.kv.lds_wave;
-  memcpy(a.layer_ptr, c.kv.layer_ptr, sizeof(uint64_t) * c.kv.layers);
+  memcpy(a.w, c.kv.layer_ptr, sizeof(uint64_t) * c.kv.layers);
+  a.words = a.layers;
   const hipStream_t hs = static_cast<hipStream_t>(stream);
-  // The table goes into the scratch array through kernel arguments, chunk by
-  // chunk, on the caller's stream: no copy call and no staging buffer.
-  NoallocTabArgs t;
-  memset(&t, 0, offsetof(NoallocTabArgs, e));
-  t.scratch = scratch;
-  for (uint64_t first = 0; first < n_blocks; first += kNoallocTabChunk) {
-    const uint32_t count = static_cast<uint32_t>(std::min<uint64_t>(kNoallocTabChunk, n_blocks - first));
-    t.first = static_cast<uint32_t>(first);
-    t.count = count;
-    t.reset = first == 0 ? 1u : 0u;
-    for (uint32_t j = 0; j < count; ++j)
-      t.e[j] = static_cast<uint64_t>(static_cast<uint32_t>(host_slots[first + j])) |
-               (static_cast<uint64_t>(static_cast<uint32_t>(gpu_blocks[first + j])) << 32);
-    const hipError_t err = launch_noalloc_table(t, hs);
-    if (err != hipSuccess) return fail(MMA_ERR_HIP, "no-alloc table launch failed: %s", hipGetErrorString(err));
+  std::lock_guard<std::mutex> g(g_noalloc_tab_mu);
+  for (uint64_t i = 0; i < n_blocks; ++i)
+    g_noalloc_tab[i] = static_cast<uint64_t>(static_cast<uint32_t>(host_slots[i])) |
+                       (static_cast<uint64_t>(static_cast<uint32_t>(gpu_blocks[i])) << 32);
+  if (c.pool_dev) sort_table(g_noalloc_tab, n_blocks, 32, g_noalloc_tmp);
+  if (a.layers + n_blocks <= kPoolWords) {
+    memcpy(a.w + a.layers, g_noalloc_tab, n_blocks * sizeof(uint64_t));
+    a.words += static_cast<uint32_t>(n_blocks);
+  } else {
+    // The table goes into the scratch array through kernel arguments, chunk by
+    // chunk, on the caller's stream: no copy call and no staging buffer.
+    a.tab = scratch + kNoallocTabOffset / 8;
+    NoallocTabArgs t;
+    t.scratch = scratch;
+    for (uint64_t first = 0; first < n_blocks; first += kNoallocTabChunk) {
+      t.first = static_cast<uint32_t>(first);
+      t.count = static_cast<uint32_t>(std::min<uint64_t>(kNoallocTabChunk, n_blocks - first));
+      memcpy(t.e, g_noalloc_tab + first, t.count * sizeof(uint64_t));
+      const hipError_t err = launch_noalloc_table(t, hs);
+      if (err != hipSuccess) return fail(MMA_ERR_HIP, "no-alloc table launch failed: %s", hipGetErrorString(err));
+    }
   }
-  // CU path alone: the engine thread's workgroup limit for a transfer over
-  // PCIe (1.5x for the transformed layouts); a pool in HBM gets a grid sized
-  // for HBM rates.
-  const uint64_t claims = (a.units + a.per_claim - 1) / a.per_claim;
-  const uint64_t wgs = c.kv.layout == MMA_KV_LAYOUT_PIECE ? rt->cfg.cu_wgs : (3ull * rt->cfg.cu_wgs + 1) / 2;
-  const uint64_t cap = c.pool_dev ? 2048 : std::min<uint64_t>(wgs, kMaxWorkgroups);
-  const uint32_t grid =
-      static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>((claims + kWavesPerWG - 1) / kWavesPerWG, cap)));
-  const hipError_t err = launch_noalloc(a, grid, hs);
+  // CU path alone: a pool in HBM as any pool launch, one on the host with the
+  // workgroups of a launch over the link.
+  const uint32_t wgs =
+      c.pool_dev ? 0 : static_cast<uint32_t>(std::min<uint64_t>((3ull * rt->cfg.cu_wgs + 1) / 2, kMaxWorkgroups));
+  if (!c.pool_dev && link_claims(MMA_H2D, c.kv.layout, n_blocks * c.slot_bytes)) a.claim = a.ctr + kPoolCtrStride;
+  const hipError_t err = launch_noalloc(a, static_cast<uint32_t>(n_blocks), c.kv.layout, wgs, hs);
   return err == hipSuccess ? MMA_OK : fail(MMA_ERR_HIP, "no-alloc KV fetch launch failed: %s", hipGetErrorString(err));
 } catch (...) {
   return boundary_error("mma_kv_fetch_noalloc");
