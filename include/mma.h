@@ -383,7 +383,7 @@ mma_status_t mma_kv_offload(const mma_kv_layout_t* layout, void* host_pool, cons
  * `stream` carries every piece on the CU path alone (no copy engine, no engine
  * thread); the transfer is complete when that launch completes on the stream,
  * and it does not appear in mma_get_stats. Layer pointers and block table travel
- * in its arguments up to 466 of them in all; a longer table goes to `scratch`, a
+ * in its arguments up to 448 of them in all; a longer table goes to `scratch`, a
  * fixed array of the library's device code (256 B of counters + 8 B per block,
  * 512 KiB + 256 B in all per GPU, held until the process ends) whose address
  * mma_init looks up, through the arguments of ceil(n_blocks / 448) small launches

@@ -648,16 +648,14 @@ __global__ __launch_bounds__(kBlock) void mma_transfer_hnd_kernel(KernelArgs a) 
 // With the pool in this GPU's memory it is bound by HBM: every byte is read once and written once, in the order
 // of the destinations (mma_pool.h), with no ring and no host round trip.
 
-// Source and destination address of piece number q. word(i): word i of the
-// arguments; kTab: the block table is in device memory instead.
+// Source and destination address of a piece. word(i): word i of the arguments;
+// kTab: the block table is in device memory instead.
 struct PoolEnds {
   uint64_t from, to;
-  uint32_t p;
 };
 template <bool kTab, class Word>
-__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q, Word word) {
+__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, PoolPiece pp, Word word) {
   typedef __attribute__((address_space(1))) uint64_t gu64;
-  const PoolPiece pp = pool_piece(a.g, q);
   uint64_t e;
   if constexpr (kTab)
     e = ((const gu64*)(a.tab))[pp.entry];
@@ -665,11 +663,16 @@ __device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q, Wor
     e = word(a.layers + pp.entry);
   const uint64_t pooled = a.pool + (e & 0xffffffffull) * a.slot_bytes + static_cast<uint64_t>(pp.p) * a.piece;
   const uint64_t paged = word(pp.p >> 1) + (pp.p & 1u) * a.kstride + (e >> 32) * a.piece;
-  return PoolEnds{a.to_paged ? pooled : paged, a.to_paged ? paged : pooled, pp.p};
+  return PoolEnds{a.to_paged ? pooled : paged, a.to_paged ? paged : pooled};
 }
-__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, uint32_t q) {
+__device__ __forceinline__ PoolEnds pool_ends(const PoolArgs& a, PoolPiece pp) {
   const auto word = [&](uint32_t i) { return a.w[i]; };
-  return a.tab ? pool_ends<true>(a, q, word) : pool_ends<false>(a, q, word);
+  return a.tab ? pool_ends<true>(a, pp, word) : pool_ends<false>(a, pp, word);
+}
+// Piece number q of the layers' keys (kind 0) or values (1).
+__device__ __forceinline__ PoolPiece kind_piece(const PoolGeom& g, uint32_t q, uint32_t kind) {
+  const PoolPiece pp = pool_piece(g, q);
+  return PoolPiece{pp.entry, 2 * pp.p + kind};
 }
 
 // The workgroup that finishes last writes the done tag. The counters only order
@@ -710,8 +713,11 @@ struct SpanWalk {
   uint64_t at, nw;
   uint32_t got;
 };
-__device__ __forceinline__ SpanWalk span_walk(uint32_t wave) {
-  return SpanWalk{static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x,
+// Over the link few spans go to as many workgroups as there are; in HBM a
+// workgroup's are neighbours.
+__device__ __forceinline__ SpanWalk span_walk(const PoolArgs& a, uint32_t wave) {
+  return SpanWalk{a.link ? static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x
+                         : static_cast<uint64_t>(blockIdx.x) * kWavesPerWG + wave,
                   static_cast<uint64_t>(gridDim.x) * kWavesPerWG, 0};
 }
 // Before the span's own reads, so that the claim's round trip overlaps theirs.
@@ -733,7 +739,10 @@ constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link
 // order: 8 GiB fetch and offload 2.90 and 2.86 ms, 5.9 and 6.0 TB/s; with 32 KiB
 // read per wave before it writes 2.96 and 2.87, and 5.5 against 6.1 TB/s at 1 GiB.
 // Nontemporal: every byte is moved once, caching it would only evict other data.
-template <bool kHnd>
+// But reads (kNt) not where head rows end inside a 128-byte line, whose other part
+// a neighbour reads: 160-byte rows, 1 GiB fetched in 431 us, nontemporally 492;
+// 256-byte rows 393 and 375.
+template <bool kHnd, bool kNt>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -741,37 +750,132 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
        w += static_cast<uint64_t>(gridDim.x) * kWavesPerWG) {
     const PoolUnit x = pool_unit(a.g, static_cast<uint32_t>(w), lane);
     if (x.ok) {
-      const PoolEnds e = pool_ends(a, x.q);
+      const PoolEnds e = pool_ends(a, pool_piece(a.g, x.q));
       const gu4* src = (const gu4*)(e.from) + (kHnd ? hnd_other(a.hnd, x.u) : x.u);
-      __builtin_nontemporal_store(__builtin_nontemporal_load(src), (gu4*)(e.to) + x.u);
+      __builtin_nontemporal_store(kNt ? __builtin_nontemporal_load(src) : *src, (gu4*)(e.to) + x.u);
     }
   }
   pool_finish(a);
 }
 
-// The other pieces, span by span (a.g counts a span as a row): x-packed ones
-// (kXE: element bytes) whole, through the wave's LDS tile, a.group at a time; kXE = 0, pieces or
-// addresses that are no multiple of 16, in spans of kPoolSpan by wave_copy.
+// Pieces span by span (a.g counts a span as a row), in HBM or over the link:
+// x-packed ones (kXE: element bytes) whole, through the wave's LDS tile, a.group at
+// a time; kXE = 0, pieces or addresses that are no multiple of 16, by wave_copy.
 template <uint32_t kXE>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const XGeom g{a.tokens, a.heads, a.row_bytes, a.elem, a.lds_wave};
-  for (SpanWalk s = span_walk(wave); s.at * a.group < a.g.waves; span_next(a, s)) {
+  for (SpanWalk s = span_walk(a, wave); s.at * a.group < a.g.waves; span_next(a, s)) {
     span_claim(a, s, lane);
     const uint64_t end = min(a.g.waves, (s.at + 1) * a.group);
     for (uint64_t w = s.at * a.group; w < end; ++w) {
       const uint32_t q = div_by(a.g.rows, static_cast<uint32_t>(w));
-      PoolEnds e = pool_ends(a, q);
+      const PoolPiece pp = pool_piece(a.g, q);
+      PoolEnds e = pool_ends(a, pp);
       e.from = lane_u64(e.from, 0);
       e.to = lane_u64(e.to, 0);
       if constexpr (kXE != 0) {
         xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
-                           e.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
+                           pp.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
       } else {
         const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * a.span;
         wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
                   min(static_cast<uint64_t>(a.span), a.piece - off), lane);
+      }
+    }
+  }
+  pool_finish(a);
+}
+
+// x units of x elements each, transposed: unit j gets element j of every unit.
+template <uint32_t E>
+__device__ __forceinline__ void transpose_units(u32x4 (&v)[16 / E]) {
+  constexpr uint32_t X = 16 / E;
+  u32x4 o[X];
+  if constexpr (E == 1) {
+#pragma unroll
+    for (uint32_t j = 0; j < X; ++j)
+#pragma unroll
+      for (uint32_t w = 0; w < 4; ++w) {
+        const uint32_t s = (j & 3u) | ((j & 3u) + 4) << 8;  // byte j of either word
+        const uint32_t lo = __builtin_amdgcn_perm(v[4 * w + 1][j / 4], v[4 * w][j / 4], s);
+        const uint32_t hi = __builtin_amdgcn_perm(v[4 * w + 3][j / 4], v[4 * w + 2][j / 4], s);
+        o[j][w] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+      }
+  } else if constexpr (E == 2) {
+#pragma unroll
+    for (uint32_t j = 0; j < X; ++j)
+#pragma unroll
+      for (uint32_t w = 0; w < 4; ++w)
+        o[j][w] = __builtin_amdgcn_perm(v[2 * w + 1][j / 2], v[2 * w][j / 2], j & 1u ? 0x07060302u : 0x05040100u);
+  } else if constexpr (E == 4) {
+#pragma unroll
+    for (uint32_t j = 0; j < X; ++j)
+#pragma unroll
+      for (uint32_t w = 0; w < 4; ++w) o[j][w] = v[w][j];
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < X; ++j)
+#pragma unroll
+      for (uint32_t w = 0; w < 4; ++w) o[j][w] = v[w / 2][2 * j + w % 2];
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < X; ++j) v[j] = o[j];
+}
+
+// x-packed pieces, in HBM (kLink false: a row per wave) or over the link (as
+// mma_kv_link_kernel): keys first, then values, both straight through registers
+// (XpMap), so no LDS limits the waves in flight and small pieces share a wave.
+// Where it is used and what it gains: xp_registers.
+template <uint32_t E, bool kLink>
+__global__ __launch_bounds__(kBlock) void mma_kv_pool_xp_kernel(PoolArgs a) {
+  constexpr uint32_t X = 16 / E, K = kLink ? kLinkRows : 1;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint64_t keys = (a.g.waves + K - 1) / K;
+  for (SpanWalk s = span_walk(a, wave); s.at < keys + a.gv.waves; span_next(a, s)) {
+    span_claim(a, s, lane);
+    if (s.at < keys) {
+      const gu4* from[K];
+      gu4* to[K];
+#pragma unroll
+      for (uint32_t k = 0; k < K; ++k) {
+        const uint64_t row = s.at * K + k;
+        const bool in = row < a.g.waves;
+        const PoolUnit x = pool_unit(a.g, static_cast<uint32_t>(in ? row : s.at * K), lane);
+        const bool ok = x.ok && in;
+        const PoolEnds e = pool_ends(a, kind_piece(a.g, ok ? x.q : 0, 0));
+        const XpAt p = xp_key(a.xp, ok ? x.u : 0);
+        const uint32_t host = xp_host(a.xp, p.hc, p.t), blk = xp_key_block(a.xp, p.hc, p.t);
+        from[k] = (const gu4*)(e.from + (a.to_paged ? host : blk));
+        to[k] = ok ? (gu4*)(e.to + (a.to_paged ? blk : host)) : nullptr;
+      }
+      u32x4 v[K];
+#pragma unroll
+      for (uint32_t k = 0; k < K; ++k) v[k] = *from[k];
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t k = 0; k < K; ++k)
+        if (to[k]) *to[k] = v[k];
+    } else {
+      const PoolUnit x = pool_unit(a.gv, static_cast<uint32_t>(s.at - keys), lane);
+      if (x.ok) {
+        const PoolEnds e = pool_ends(a, kind_piece(a.gv, x.q, 1));
+        const XpAt p = xp_val(a.xp, x.u);
+        // Element i of the host side's units is token p.t * X + i, of the block's
+        // dimension p.hc * X + i.
+        const uint32_t host = xp_host(a.xp, p.hc, p.t * X), hstep = a.xp.HC * 16;
+        const uint32_t blk = xp_val_block(a.xp, p.hc * X, p.t), bstep = a.xp.groups.d * 16;
+        const uint64_t src = e.from + (a.to_paged ? host : blk), dst = e.to + (a.to_paged ? blk : host);
+        const uint32_t sstep = a.to_paged ? hstep : bstep, dstep = a.to_paged ? bstep : hstep;
+        u32x4 v[X];
+#pragma unroll
+        for (uint32_t i = 0; i < X; ++i) v[i] = *(const gu4*)(src + static_cast<uint64_t>(i) * sstep);
+        transpose_units<E>(v);
+#pragma unroll
+        for (uint32_t i = 0; i < X; ++i) *(gu4*)(dst + static_cast<uint64_t>(i) * dstep) = v[i];
       }
     }
   }
@@ -801,9 +905,9 @@ __device__ __forceinline__ void link_span(const PoolArgs& a, uint32_t first, uin
     const bool ok = x.ok && in;
     PoolEnds e;
     if constexpr (kShared) {
-      e = pool_ends<kTab>(a, ok ? x.q : 0, word);
+      e = pool_ends<kTab>(a, pool_piece(a.g, ok ? x.q : 0), word);
     } else {
-      e = pool_ends<kTab>(a, __builtin_amdgcn_readfirstlane(x.q), word);
+      e = pool_ends<kTab>(a, pool_piece(a.g, __builtin_amdgcn_readfirstlane(x.q)), word);
       e.from = lane_u64(e.from, 0);
       e.to = lane_u64(e.to, 0);
     }
@@ -832,7 +936,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_link_kernel(PoolArgs a) {
   for (uint32_t i = threadIdx.x; i < a.words; i += kBlock) s_w[i] = a.w[i];
   __syncthreads();
   const auto word = [&](uint32_t i) { return s_w[i]; };
-  for (SpanWalk s = span_walk(wave); s.at * kLinkRows < a.g.waves; span_next(a, s)) {
+  for (SpanWalk s = span_walk(a, wave); s.at * kLinkRows < a.g.waves; span_next(a, s)) {
     const uint64_t first = s.at * kLinkRows;
     span_claim(a, s, lane);
     if (a.g.per_row > 1)
@@ -907,49 +1011,88 @@ hipError_t launch_whole(const KernelArgs& args, uint32_t grid, hipStream_t strea
                          stream);
 }
 
+// Whether x-packed pieces go through registers (mma_kv_pool_xp_kernel) or a wave's
+// LDS tile, by what was faster (LDS / registers, us):
+//  - pieces below 4 KiB, of which registers take several at a time: 1 GiB of 2 KiB
+//    pieces in HBM, fetch 1243 / 503, offload 1228 / 585; 64 MiB over the link 1415
+//    / 1221; but 1 GiB of 6 KiB pieces, fetch 541 / 755: a lane's stores go to x
+//    dimensions, 32 bytes of each row at a time;
+//  - offloads in HBM, whose stores are whole rows of tokens: 512 blocks 557 / 446,
+//    of 6 KiB pieces 1028 / 638; and fetches there that are over before HBM is the
+//    limit: 2 MiB 14.4 / 12.6, 64 MiB 54.1 / 40.2, 128 MiB 59.9 / 67.7; one-byte
+//    elements 2 MiB 17.3 / 12.6, 37 MiB 20.9 / 24.4; with more than 16 KiB of tile a
+//    wave (one workgroup per CU) 25 MiB 40.2 / 13.0, 200 MiB 60.9 / 47.9, 1 GiB 424
+//    / 439;
+//  - over the link fetches whose tile is above 16 KiB a wave: 1 block of 32 tokens
+//    x 8 heads x 256 dimensions 306 / 267, but of 16 x 8 x 128 43.8 / 48.7; and
+//    offloads below 16 MiB in 8 x 8 squares: 48.3 / 45.6, but with 50 units a token
+//    175 / 186 at 8 MiB, and 64 MiB 1292 / 1361.
+bool xp_registers(const PoolArgs& p, uint32_t n, bool link) {
+  const uint64_t bytes = static_cast<uint64_t>(n) * 2 * p.layers * p.piece;
+  if (p.piece < 4096) return true;
+  if (!link) return !p.to_paged || bytes <= (p.lds_wave > 16 * 1024 ? 256ull << 20 : (p.elem > 1 ? 64ull : 8ull) << 20);
+  if (p.to_paged) return p.lds_wave > 16 * 1024;
+  return bytes < (16ull << 20) && p.tokens % 8 == 0 && p.heads * (p.row_bytes / 16) % 8 == 0;
+}
+
 // One launch of the kernel that the pool's place, the layout and the alignment
 // ask for. p holds everything but the geometry; wgs: the most workgroups of a
 // launch over the link, 0 for a pool in HBM.
 hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, uint32_t wgs,
                               hipStream_t stream) {
-  p.g = pool_geom(n, 2 * p.layers, p.piece, wgs ? 0 : p.to_paged);
+  const uint32_t by_piece = wgs ? 0 : p.to_paged, rows = wgs ? kLinkRows : 1;
+  uint32_t lds = 0;
+  p.link = wgs ? 1 : 0;
+  p.group = 1;
+  p.g = pool_geom(n, 2 * p.layers, p.piece >> 4, by_piece);
   const void* k = nullptr;
-  uint32_t lds = 0, rows = 1;
+  uint64_t spans = (p.g.waves + rows - 1) / rows;  // of one wave each
   if (layout == kKvLayoutHnd) {
     const bool heads_first = !wgs && p.to_paged;
     p.hnd = heads_first ? hnd_map(p.heads, p.tokens, p.row_bytes / 16) : hnd_map(p.tokens, p.heads, p.row_bytes / 16);
-    k = wgs ? (p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<true, true>)
-                     : reinterpret_cast<const void*>(&mma_kv_link_kernel<true, false>))
-            : reinterpret_cast<const void*>(&mma_kv_pool_kernel<true>);
-    rows = wgs ? kLinkRows : 1;
-  } else if (layout == kKvLayoutPiece && aligned) {
-    k = wgs ? (p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<false, true>)
-                     : reinterpret_cast<const void*>(&mma_kv_link_kernel<false, false>))
-            : reinterpret_cast<const void*>(&mma_kv_pool_kernel<false>);
-    rows = wgs ? kLinkRows : 1;
+    k = !wgs ? (p.row_bytes % 128 == 0 ? reinterpret_cast<const void*>(&mma_kv_pool_kernel<true, true>)
+                                       : reinterpret_cast<const void*>(&mma_kv_pool_kernel<true, false>))
+        : p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<true, true>)
+                : reinterpret_cast<const void*>(&mma_kv_link_kernel<true, false>);
+  } else if (layout == kKvLayoutXPacked && !xp_registers(p, n, wgs != 0)) {
+    lds = kWavesPerWG * p.lds_wave;
+    k = p.elem == 1   ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<1>)
+        : p.elem == 2 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<2>)
+        : p.elem == 4 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<4>)
+                      : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
+    p.g.rows = fast_div(1);
+    p.g.waves = p.g.total;
+    // A claim's round trip pays for 8 KiB at least.
+    if (p.claim) p.group = static_cast<uint32_t>(std::max<uint64_t>(1, kPoolSpan / p.piece));
+    spans = (p.g.waves + p.group - 1) / p.group;
+  } else if (layout == kKvLayoutXPacked) {
+    const uint32_t x = 16 / p.elem, hc = p.heads * (p.row_bytes / 16);
+    p.xp = xp_map(p.tokens, hc, x);
+    p.g = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * p.tokens, by_piece);
+    p.gv = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * (p.tokens / x), by_piece);
+    spans = (p.g.waves + rows - 1) / rows + p.gv.waves;
+    const void* const xp[4][2] = {{reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, true>)}};
+    k = xp[p.elem == 1 ? 0 : p.elem == 2 ? 1 : p.elem == 4 ? 2 : 3][wgs ? 1 : 0];
+  } else if (aligned) {
+    k = !wgs ? reinterpret_cast<const void*>(&mma_kv_pool_kernel<false, true>)
+        : p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<false, true>)
+                : reinterpret_cast<const void*>(&mma_kv_link_kernel<false, false>);
   } else {
-    uint64_t spans = 1;
-    if (layout == kKvLayoutXPacked) {
-      lds = kWavesPerWG * p.lds_wave;
-      k = p.elem == 1   ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<1>)
-          : p.elem == 2 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<2>)
-          : p.elem == 4 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<4>)
-                        : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
-    } else {
-      p.span = wgs ? 2 * kPoolSpan : kPoolSpan;
-      spans = (p.piece + p.span - 1) / p.span;
-      k = reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<0>);
-    }
-    p.g.rows = fast_div(static_cast<uint32_t>(spans));
-    p.g.waves = spans * p.g.total;
-    // A claim's round trip pays for 8 KiB at least (2 KiB pieces one by one:
-    // 44 GB/s, 48 without claims).
-    p.group = p.claim ? static_cast<uint32_t>(std::max<uint64_t>(1, kPoolSpan / p.piece)) : 1;
-    rows = p.group;
+    p.span = wgs ? 2 * kPoolSpan : kPoolSpan;
+    const uint64_t per = (p.piece + p.span - 1) / p.span;
+    p.g.rows = fast_div(static_cast<uint32_t>(per));
+    spans = p.g.waves = per * p.g.total;
+    k = reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<0>);
   }
   // A launch has fewer than 2^32 threads; beyond that the waves go round again.
-  const uint64_t per_wg = static_cast<uint64_t>(kWavesPerWG) * rows;
-  const uint64_t grid = std::min<uint64_t>((p.g.waves + per_wg - 1) / per_wg, wgs ? wgs : 1u << 23);
+  const uint64_t grid = std::min<uint64_t>((spans + kWavesPerWG - 1) / kWavesPerWG, wgs ? wgs : 1u << 23);
   void* params[] = {&p};
   return hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
 }
@@ -970,8 +1113,10 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
   p.heads = args.kv_heads;
   p.row_bytes = args.kv_row_bytes;
   p.elem = args.kv_elem;
+  // Stores to a host pool are in host memory before the done tag; in HBM the
+  // stream orders them (a release per wave writes back its XCD's L2 each time).
+  p.release = args.pool_link && args.release_each;
   p.lds_wave = args.kv_lds_wave;
-  p.release = args.release_each;
   uint64_t mis = p.piece | p.pool;
   for (uint32_t l = 0; l < p.layers; ++l) mis |= p.w[l] = args.layer_ptr[l];
   p.words = p.layers;

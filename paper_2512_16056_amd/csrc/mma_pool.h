@@ -55,18 +55,18 @@ struct PoolGeom {
   FastDiv div;
   // Rows of 64 units: a piece of 64 units or more takes rows.d of them, smaller
   // pieces share one, per_row each (rows.d = 1).
-  uint32_t units;    // 16-byte units of a piece
+  uint32_t units;    // of a piece: 16 bytes each (x-packed values: lane tiles)
   FastDiv rows, piece_units;  // piece_units.d = units, where pieces share rows
   uint32_t per_row;
   uint64_t waves;
 };
 
-MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t piece, uint32_t by_piece) {
+MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t units, uint32_t by_piece) {
   PoolGeom g;
   g.by_piece = by_piece;
   g.total = n * ppb;
   g.div = fast_div(by_piece ? n : ppb);
-  g.units = static_cast<uint32_t>(piece >> 4);
+  g.units = static_cast<uint32_t>(units);
   const uint32_t u = g.units ? g.units : 1;
   const uint32_t rows = (u + kPoolRowUnits - 1) / kPoolRowUnits;
   g.rows = fast_div(rows);
@@ -120,6 +120,46 @@ MMA_POOL_HD inline HndMap hnd_map(uint32_t X, uint32_t Y, uint32_t C) { return H
 MMA_POOL_HD inline uint32_t hnd_other(const HndMap& m, uint32_t u) {
   const uint32_t row = div_by(m.C, u), x = div_by(m.Y, row);
   return ((row - x * m.Y.d) * m.X + x) * m.C.d + (u - row * m.C.d);
+}
+
+// x-packed blocks. A piece is B tokens of HC 16-byte units (x = 16 / element bytes
+// elements each) on the host, [B][HC]. A key block holds the same units as [HC][B],
+// a value block rows of B elements per dimension, [HC * x][B]: so a key lane moves
+// one unit, and a value lane x units of x tokens by x dimensions, transposed in its
+// registers. Keys and values have a geometry each, over the layers' pieces (ppb =
+// layers).
+// Unit v of a key piece: 8 x 8 units per wave where both sides divide, for runs of
+// 128 bytes on either side; else the block's order.
+// Lane tile v of a value piece: the block's order, runs of B elements there and of
+// 64 / (B / x) units on the host.
+struct XpMap {
+  uint32_t B, HC;
+  FastDiv tokens, groups, squares;  // by B, by B / x, by B / 8
+  uint32_t square;                  // 1: 8 x 8
+};
+MMA_POOL_HD inline XpMap xp_map(uint32_t B, uint32_t HC, uint32_t x) {
+  return XpMap{B, HC, fast_div(B), fast_div(B / x), fast_div(B >= 8 ? B / 8 : 1), B % 8 == 0 && HC % 8 == 0 ? 1u : 0u};
+}
+struct XpAt {
+  uint32_t hc, t;  // key: unit and token; value: unit and token group
+};
+MMA_POOL_HD inline XpAt xp_key(const XpMap& m, uint32_t v) {
+  if (m.square) {
+    const uint32_t blk = v >> 6, in = v & 63, h = div_by(m.squares, blk), t = blk - h * m.squares.d;
+    return XpAt{h * 8 + (in >> 3), t * 8 + (in & 7)};
+  }
+  const uint32_t hc = div_by(m.tokens, v);
+  return XpAt{hc, v - hc * m.B};
+}
+MMA_POOL_HD inline XpAt xp_val(const XpMap& m, uint32_t v) {
+  const uint32_t hc = div_by(m.groups, v);
+  return XpAt{hc, v - hc * m.groups.d};
+}
+// Byte offsets in the host piece and in the block.
+MMA_POOL_HD inline uint32_t xp_host(const XpMap& m, uint32_t hc, uint32_t t) { return (t * m.HC + hc) * 16; }
+MMA_POOL_HD inline uint32_t xp_key_block(const XpMap& m, uint32_t hc, uint32_t t) { return (hc * m.B + t) * 16; }
+MMA_POOL_HD inline uint32_t xp_val_block(const XpMap& m, uint32_t dim, uint32_t group) {
+  return (dim * m.groups.d + group) * 16;
 }
 
 }  // namespace mma

@@ -47,7 +47,7 @@ constexpr uint32_t kBlock = kWave * kWavesPerWG;
 // launch's work.
 constexpr uint32_t kPoolSpan = 8 * 1024;
 constexpr uint32_t kPoolMaxWorkgroups = 8192;
-constexpr uint32_t kPoolWords = 466;      // 3.9 KiB of arguments in all
+constexpr uint32_t kPoolWords = 448;      // 3.9 KiB of arguments in all
 // Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
 // finished workgroups of group i, [0] the finished groups (one group: its
 // workgroups; [1] then is free for the claims of a launch over the link).
@@ -187,9 +187,11 @@ struct PoolArgs {
   PoolGeom g;
   uint32_t to_paged, layers, release;  // release: 1: system-scope release before the done tag
   HndMap hnd;               // head-major blocks
-  uint32_t tokens, heads, row_bytes, elem, lds_wave;  // x-packed blocks
+  uint32_t tokens, heads, row_bytes, elem, lds_wave;
+  PoolGeom gv;              // x-packed blocks: the value pieces (g: the key pieces)
+  XpMap xp;
   uint32_t span;            // bytes of a span where 16-byte units cannot move
-  uint32_t group;           // spans that go together
+  uint32_t link, group;     // 1: over the link; spans that go together
   uint32_t words;           // of w in use
   uint32_t tags;            // > 0: no counters, workgroup i writes done[i], done[i + grid], ... below tags
   uint64_t w[kPoolWords];   // layer pointers, then the block table if it fits

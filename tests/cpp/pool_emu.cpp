@@ -16,7 +16,7 @@ using namespace mma;
 extern "C" int emu_pool(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes, const uint64_t* tab,
                         uint32_t n, uint32_t ppb, uint64_t piece, uint32_t nb, int to_paged, int hnd, int link,
                         uint32_t B, uint32_t H, uint32_t R) {
-  const PoolGeom g = pool_geom(n, ppb, piece, to_paged && !link ? 1 : 0);
+  const PoolGeom g = pool_geom(n, ppb, piece >> 4, to_paged && !link ? 1 : 0);
   const HndMap m = to_paged && !link ? hnd_map(H, B, R / 16) : hnd_map(B, H, R / 16);
   std::vector<uint8_t> wrote(to_paged ? cache_bytes : pool_bytes, 0);
   const uint8_t* src = to_paged ? pool : cache;
@@ -54,4 +54,68 @@ extern "C" uint64_t emu_div(uint32_t d, uint32_t first, uint32_t count) {
   for (uint32_t i = 0; i < count; ++i)
     if (div_by(f, first + i) != (first + i) / d) return first + i + 1ull;
   return 0;
+}
+
+// x-packed blocks: key lanes move one unit, value lanes X units transposed, over
+// the same maps. E: element bytes; HC: 16-byte units per token.
+extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes,
+                           const uint64_t* tab, uint32_t n, uint32_t layers, uint64_t piece, uint32_t nb, int to_paged,
+                           int link, uint32_t B, uint32_t HC, uint32_t E) {
+  const uint32_t X = 16 / E, ppb = 2 * layers, by_piece = to_paged && !link ? 1 : 0;
+  const XpMap m = xp_map(B, HC, X);
+  const PoolGeom geom[2] = {pool_geom(n, layers, static_cast<uint64_t>(HC) * B, by_piece),
+                            pool_geom(n, layers, static_cast<uint64_t>(HC) * (B / X), by_piece)};
+  std::vector<uint8_t> wrote(to_paged ? cache_bytes : pool_bytes, 0);
+  const uint8_t* src = to_paged ? pool : cache;
+  uint8_t* dst = to_paged ? cache : pool;
+  const uint64_t src_bytes = to_paged ? pool_bytes : cache_bytes, dst_bytes = to_paged ? cache_bytes : pool_bytes;
+  for (uint32_t kind = 0; kind < 2; ++kind) {
+    const PoolGeom& g = geom[kind];
+    for (uint64_t w = 0; w < g.waves; ++w)
+      for (uint32_t lane = 0; lane < 64; ++lane) {
+        const PoolUnit x = pool_unit(g, static_cast<uint32_t>(w), lane);
+        if (!x.ok) continue;
+        if (x.q >= g.total || x.u >= g.units) return 1;
+        const PoolPiece pp = pool_piece(g, x.q);
+        if (pp.entry >= n || pp.p >= layers) return 2;
+        const uint64_t e = tab[pp.entry], p = 2 * pp.p + kind;
+        const uint64_t in_pool = (e & 0xffffffffull) * ppb * piece + p * piece;
+        const uint64_t in_cache = p * nb * piece + (e >> 32) * piece;
+        const uint64_t from = to_paged ? in_pool : in_cache, to = to_paged ? in_cache : in_pool;
+        uint8_t in[16 * 16], out[16 * 16];
+        uint64_t so[16], to_off[16];
+        const uint32_t count = kind ? X : 1;
+        for (uint32_t i = 0; i < count; ++i) {
+          uint64_t host, blk;
+          if (kind) {
+            const XpAt a = xp_val(m, x.u);
+            host = xp_host(m, a.hc, a.t * X + i);
+            blk = xp_val_block(m, a.hc * X + i, a.t);
+          } else {
+            const XpAt a = xp_key(m, x.u);
+            host = xp_host(m, a.hc, a.t);
+            blk = xp_key_block(m, a.hc, a.t);
+          }
+          if (host + 16 > piece || blk + 16 > piece) return 3;
+          so[i] = from + (to_paged ? host : blk);
+          to_off[i] = to + (to_paged ? blk : host);
+          if (so[i] + 16 > src_bytes || to_off[i] + 16 > dst_bytes) return 4;
+          std::memcpy(in + 16 * i, src + so[i], 16);
+        }
+        if (kind) {
+          for (uint32_t j = 0; j < X; ++j)
+            for (uint32_t i = 0; i < X; ++i) std::memcpy(out + 16 * j + i * E, in + 16 * i + j * E, E);
+        } else {
+          std::memcpy(out, in, 16);
+        }
+        for (uint32_t j = 0; j < count; ++j) {
+          std::memcpy(dst + to_off[j], out + 16 * j, 16);
+          for (uint32_t i = 0; i < 16; ++i)
+            if (wrote[to_off[j] + i]++) return 5;
+        }
+      }
+  }
+  uint64_t total = 0;
+  for (uint8_t v : wrote) total += v;
+  return total == static_cast<uint64_t>(n) * ppb * piece ? 0 : 6;
 }

@@ -598,6 +598,12 @@ LINK_SHAPES = {
     # more blocks than the launch's arguments hold
     "long_table": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=700,
                             host_num_slots=650, n_blocks=600),
+    # one-byte elements: 16 x 16 per lane in the x-packed transform
+    "bytes": W.KVShape(layers=2, block_tokens=32, kv_heads=4, head_dim=64, elem_bytes=1, gpu_num_blocks=20,
+                       host_num_slots=16, n_blocks=9),
+    # 33 KiB of tile per wave
+    "large_heads": W.KVShape(layers=2, block_tokens=64, kv_heads=2, head_dim=256, elem_bytes=2, gpu_num_blocks=9,
+                             host_num_slots=8, n_blocks=5),
     # above the whole-transfer limits, in small blocks
     "many_small": W.KVShape(layers=4, block_tokens=16, kv_heads=2, head_dim=128, elem_bytes=2, gpu_num_blocks=520,
                             host_num_slots=500, n_blocks=480),
@@ -647,6 +653,56 @@ def test_kv_link_launch(shape, gpu_layout, mis):
         assert st["pool_launches"] == 0 and st["engine_wall_busy_ns"] == 0
         del pool, pv
         raw.free()
+
+
+XP_POOL_SHAPES = {
+    # pieces below and at the size that goes through LDS, with 8 and 9 MiB and a bit in all
+    "small_pieces": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=1300,
+                              host_num_slots=1250, n_blocks=1200),
+    "lds_fetch": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=520,
+                           host_num_slots=510, n_blocks=500),
+    "reg_fetch": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=420,
+                           host_num_slots=410, n_blocks=400),
+    "words": W.KVShape(layers=1, block_tokens=4, kv_heads=4, head_dim=64, elem_bytes=4, gpu_num_blocks=20,
+                       host_num_slots=18, n_blocks=17),
+    "doubles": W.KVShape(layers=1, block_tokens=2, kv_heads=5, head_dim=8, elem_bytes=8, gpu_num_blocks=90,
+                         host_num_slots=80, n_blocks=77),
+    "bytes": W.KVShape(layers=2, block_tokens=32, kv_heads=5, head_dim=80, elem_bytes=1, gpu_num_blocks=40,
+                       host_num_slots=36, n_blocks=33),
+}
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("shape", list(XP_POOL_SHAPES))
+def test_kv_xpacked_device_pool_launch(shape, noalloc):
+    """x-packed blocks with the pool in HBM, by one launch: through registers and through LDS, each
+    element size; fetch (also without allocations) and offload against the oracle."""
+    s = XP_POOL_SHAPES[shape]
+    log(f"x-packed device pool launch {shape} noalloc={noalloc}")
+    geom = _geom(s)
+    lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                        s.host_num_slots, mma.MMA_KV_LAYOUT_XPACKED)
+    hs, gb = W.kv_fetch_tables(s, cfg=3)
+    with session("both"):
+        pool_np = np.random.default_rng(41).integers(0, 256, s.host_num_slots * s.slot_bytes, dtype=np.uint8)
+        pool = torch.from_numpy(pool_np.copy()).cuda()
+        layers = _layers(s, W.GPU_POISON)
+        before = _layer_views(s, layers)
+        (mma.mma_kv_fetch_noalloc if noalloc else mma.mma_kv_fetch)(lay, pool, layers, hs, gb)
+        torch.cuda.synchronize()
+        pv = pool_np.reshape(s.host_num_slots, s.slot_bytes)
+        for l in range(s.layers):
+            want = okv.kv_fetch_layer(pv, before[l], l, s.layers, hs, gb, okv.LAYOUT_XPACKED, geom)
+            assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), l
+        if not noalloc:
+            src = _layers(s, seed=800)
+            dest = np.roll(hs, 1).astype(np.int32)
+            mma.mma_kv_offload(lay, pool, src, gb, dest)
+            torch.cuda.synchronize()
+            want = okv.kv_offload(pv, _layer_views(s, src), gb, dest, okv.LAYOUT_XPACKED, geom)
+            assert np.array_equal(to_host(pool).reshape(s.host_num_slots, -1), want)
+            mma.mma_synchronize()
+            assert mma.mma_get_stats()["pool_launches"] == 2
 
 
 def _fill_pool_c3(pool: np.ndarray, s: W.KVShape, hs: np.ndarray):

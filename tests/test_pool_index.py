@@ -34,6 +34,10 @@ def emu(tmp_path_factory):
     f.restype = ctypes.c_int
     f.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
                   ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 3 + [ctypes.c_uint32] * 3)
+    f.xp = lib.emu_pool_xp
+    f.xp.restype = ctypes.c_int
+    f.xp.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
+                     ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 2 + [ctypes.c_uint32] * 3)
     f.div = lib.emu_div
     f.div.restype = ctypes.c_uint64
     f.div.argtypes = [ctypes.c_uint32] * 3
@@ -74,6 +78,38 @@ def test_pool_index_maps_match_oracle(emu, shape, layout, link):
     got = pool.copy()
     run(got, cache.copy(), 0)
     assert np.array_equal(got, okv.kv_offload(pool, list(cache), gb, hs, layout, geom))
+
+
+# tokens, heads, head_dim, element bytes, layers, blocks: squares of 8 x 8 units and shapes they do not
+# divide, pieces that share a row, each element size
+XP_SHAPES = [(16, 8, 128, 2, 2, 4), (16, 1, 64, 2, 3, 9), (16, 5, 80, 2, 1, 3), (16, 4, 96, 1, 2, 5),
+             (32, 2, 16, 1, 1, 6), (8, 3, 16, 2, 2, 5), (24, 1, 24, 2, 1, 3), (4, 8, 16, 4, 2, 3), (2, 5, 8, 8, 1, 7)]
+
+
+@pytest.mark.parametrize("link", [0, 1])
+@pytest.mark.parametrize("shape", XP_SHAPES)
+def test_pool_xpacked_maps_match_oracle(emu, shape, link):
+    B, H, D, E, L, n = shape
+    piece, nb, slots, geom = B * H * D * E, n + 3, n + 2, (B, H, D, E)
+    r = np.random.default_rng(B * 31 + H + D)
+    pool = r.integers(0, 256, (slots, 2 * L * piece), dtype=np.uint8)
+    cache = r.integers(0, 256, (L, 2, nb, piece), dtype=np.uint8)
+    hs = r.permutation(slots)[:n].astype(np.int32)
+    gb = np.sort(r.permutation(nb)[:n]).astype(np.int32)
+    tab = hs.astype(np.uint64) | (gb.astype(np.uint64) << np.uint64(32))
+
+    def run(p, c, to_paged):
+        rc = emu.xp(p.ctypes.data, p.nbytes, c.ctypes.data, c.nbytes, tab.ctypes.data, n, L, piece, nb, to_paged, link,
+                    B, H * D * E // 16, E)
+        assert rc == 0, rc
+
+    got = cache.copy()
+    run(pool.copy(), got, 1)
+    for l in range(L):
+        assert np.array_equal(got[l], okv.kv_fetch_layer(pool, cache[l], l, L, hs, gb, okv.LAYOUT_XPACKED, geom)), l
+    got = pool.copy()
+    run(got, cache.copy(), 0)
+    assert np.array_equal(got, okv.kv_offload(pool, list(cache), gb, hs, okv.LAYOUT_XPACKED, geom))
 
 
 def test_division_by_reciprocal(emu):
