@@ -675,12 +675,17 @@ __device__ __forceinline__ PoolPiece kind_piece(const PoolGeom& g, uint32_t q, u
   return PoolPiece{pp.entry, 2 * pp.p + kind};
 }
 
+// s_waitcnt vmcnt(0), the other counters left alone (gfx9 encoding).
+constexpr int kWaitVm0 = 0x0f70;
+
 // The workgroup that finishes last writes the done tag. The counters only order
 // the tag after every workgroup: the data itself becomes visible to later work
 // through the stream, when the kernel ends, as for any kernel (a device-wide
-// release per workgroup would write back the L2 of its XCD each time). A launch
-// of many workgroups counts them in up to kPoolCtrs groups first: two million
-// counts of an 8 GiB transfer do not queue up on one address.
+// release per workgroup would write back the L2 of its XCD each time). Counts on
+// one address go one after the other, some 12 ns each, so more than 32 workgroups
+// count in groups of at least 16 first: with 512 and more to a group a launch of
+// 2048 took 8 us longer. A launch of many has its tag written by a launch of its
+// own instead (kPoolTagLaunch).
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   if (!a.done && !a.claim) return;
   if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
@@ -690,7 +695,7 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
     for (uint32_t t = blockIdx.x; t < a.tags; t += gridDim.x) st_sys(&a.done[t], make_tag(a.seq, t));
     return;
   }
-  const uint32_t groups = max(1u, min(gridDim.x / 512u, 0u + kPoolCtrs));
+  const uint32_t groups = max(1u, min(gridDim.x / 16u, 0u + kPoolCtrs));
   if (groups > 1) {
     const uint32_t i = blockIdx.x % groups, members = (gridDim.x - i + groups - 1) / groups;
     uint32_t* c = a.ctr + (1 + i) * kPoolCtrStride;
@@ -698,11 +703,17 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
     __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   const uint32_t members = groups > 1 ? groups : gridDim.x;
-  if (__hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
+  if (__hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
   __hip_atomic_store(a.ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (a.claim) __hip_atomic_store(a.claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  if (a.done) st_sys(a.done, make_tag(a.seq, 0));
+  if (!a.done) return;
+  // The counters are back at 0 where other XCDs see it before the tag frees them
+  // for another launch: a wait for these stores, which go there themselves. A
+  // release, which writes back the L2, cost a launch of one block 6 us.
+  if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __builtin_amdgcn_sched_barrier(0);
+  st_sys(a.done, make_tag(a.seq, 0));
 }
 
 // The spans of one wave of a launch with fewer waves than spans: its own first,
@@ -729,8 +740,6 @@ __device__ __forceinline__ void span_next(const PoolArgs& a, SpanWalk& s) {
   s.at = a.claim ? s.nw + __builtin_amdgcn_readfirstlane(s.got) : s.at + s.nw;
 }
 
-// s_waitcnt vmcnt(0), the other counters left alone (gfx9 encoding).
-constexpr int kWaitVm0 = 0x0f70;
 constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link
 
 // Aligned pieces in the piece layout or (kHnd) head-major: one 16-byte unit per
@@ -947,6 +956,10 @@ __global__ __launch_bounds__(kBlock) void mma_kv_link_kernel(PoolArgs a) {
   pool_finish(a);
 }
 
+// The done tag of a pool launch that does not count its workgroups: this launch
+// starts when that one has ended.
+__global__ void mma_kv_pool_tag_kernel(uint64_t* done, uint64_t tag) { st_sys(done, tag); }
+
 // A pool launch's block table from the arena in host memory to its copy in
 // device memory: 512 bytes per wave and read.
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_table_kernel(PoolTabArgs a) {
@@ -1035,6 +1048,10 @@ bool xp_registers(const PoolArgs& p, uint32_t n, bool link) {
   return bytes < (16ull << 20) && p.tokens % 8 == 0 && p.heads * (p.row_bytes / 16) % 8 == 0;
 }
 
+// Above this many workgroups (64 MiB at 4 KiB each) counting them costs more than a
+// second launch: 1 GiB 371 / 354 us, 4 GiB 1498 / 1438.
+constexpr uint64_t kPoolTagLaunch = 16384;
+
 // One launch of the kernel that the pool's place, the layout and the alignment
 // ask for. p holds everything but the geometry; wgs: the most workgroups of a
 // launch over the link, 0 for a pool in HBM.
@@ -1093,8 +1110,16 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
   }
   // A launch has fewer than 2^32 threads; beyond that the waves go round again.
   const uint64_t grid = std::min<uint64_t>((spans + kWavesPerWG - 1) / kWavesPerWG, wgs ? wgs : 1u << 23);
+  uint64_t* const done = p.done;
+  if (grid > kPoolTagLaunch) p.done = nullptr;
   void* params[] = {&p};
-  return hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
+  const hipError_t e = hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
+  if (e != hipSuccess || p.done == done) return e;
+  uint64_t* d = done;
+  uint64_t tag = make_tag(p.seq, 0);
+  void* tag_params[] = {&d, &tag};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&mma_kv_pool_tag_kernel), dim3(1), dim3(1), tag_params, 0,
+                         stream);
 }
 
 hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
