@@ -206,8 +206,17 @@ def _ptr(x) -> int:
     raise TypeError(f"cannot take the address of {type(x)}")
 
 
+# The handle of torch's current stream, without building a Stream object: the two calls take
+# 0.2 us, torch.cuda.current_stream() and is_available() 3.4 us, as much as the rest of a small
+# copy's call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(s) -> int:
     if s is None:
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
     if isinstance(s, int):
         return s
@@ -215,6 +224,8 @@ def _stream(s) -> int:
 
 
 def _i32(a) -> np.ndarray:
+    if type(a) is np.ndarray and a.dtype == np.int32 and a.ndim and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
