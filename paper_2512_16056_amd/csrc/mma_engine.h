@@ -146,6 +146,7 @@ struct Transfer {
   bool pool_launch = false;
   uint64_t pool_base = 0;
   std::vector<uint64_t> pool_pairs;
+  std::vector<uint64_t> pool_tmp;  // room to sort them
   int32_t tab_seg = -1;
   uint32_t tab_nseg = 0;
   bool self_contained = false; // whole transfer in the kernel args; the kernel does not wait on the host
@@ -816,8 +817,7 @@ class Engine {
     const uint64_t nblk = x->pool_pairs.size();
     // In HBM the kernel takes the pieces in the order of their destinations (mma_pool.h).
     if (x->pool_dev) {
-      std::vector<uint64_t> tmp(nblk);
-      sort_table(x->pool_pairs.data(), nblk, x->kind == Kind::kKvFetch ? 32 : 0, tmp.data());
+      sort_table(x->pool_pairs.data(), nblk, x->kind == Kind::kKvFetch ? 32 : 0, x->pool_tmp.data());
     }
     memcpy(pool_tab_ + static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg, x->pool_pairs.data(),
            nblk * sizeof(uint64_t));
@@ -2085,6 +2085,7 @@ inline void set_pool_table(Transfer* x, uint64_t pool, const int32_t* host_slots
                            uint64_t n) {
   x->pool_base = pool;
   x->pool_pairs.resize(n);
+  if (x->pool_dev) x->pool_tmp.resize(n);
   for (uint64_t i = 0; i < n; ++i)
     x->pool_pairs[i] = static_cast<uint32_t>(host_slots[i]) | static_cast<uint64_t>(gpu_blocks[i]) << 32;
 }

@@ -1056,7 +1056,7 @@ constexpr uint64_t kPoolTagLaunch = 16384;
 // ask for. p holds everything but the geometry; wgs: the most workgroups of a
 // launch over the link, 0 for a pool in HBM.
 hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, uint32_t wgs,
-                              hipStream_t stream) {
+                              hipStream_t stream, bool* begun) {
   const uint32_t by_piece = wgs ? 0 : p.to_paged, rows = wgs ? kLinkRows : 1;
   uint32_t lds = 0;
   p.link = wgs ? 1 : 0;
@@ -1114,7 +1114,9 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
   if (grid > kPoolTagLaunch) p.done = nullptr;
   void* params[] = {&p};
   const hipError_t e = hipLaunchKernel(k, dim3(static_cast<uint32_t>(grid)), dim3(kBlock), params, lds, stream);
-  if (e != hipSuccess || p.done == done) return e;
+  if (e != hipSuccess) return e;
+  *begun = true;
+  if (p.done == done) return e;
   uint64_t* d = done;
   uint64_t tag = make_tag(p.seq, 0);
   void* tag_params[] = {&d, &tag};
@@ -1122,7 +1124,7 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
                          stream);
 }
 
-hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
+hipError_t launch_pool(const KernelArgs& args, hipStream_t stream, bool* begun) {
   static thread_local PoolArgs p;
   p.done = args.done;
   p.seq = args.seq;
@@ -1157,14 +1159,17 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream) {
         hipLaunchKernel(reinterpret_cast<const void*>(&mma_kv_pool_table_kernel),
                         dim3(static_cast<uint32_t>((t.n + kBlock - 1) / kBlock)), dim3(kBlock), params, 0, stream);
     if (e != hipSuccess) return e;
+    *begun = true;
     p.tab = args.pool_tab_copy;
   }
   return launch_pool_kernel(p, static_cast<uint32_t>(args.pool_blocks), args.kv_layout, (mis & 15u) == 0,
-                            args.pool_link ? args.pool_wgs : 0, stream);
+                            args.pool_link ? args.pool_wgs : 0, stream, begun);
 }
 
-hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream) {
-  if (args.pool_tab) return launch_pool(args, stream);
+// begun: set once a launch of the transfer is on the stream, also when a later
+// one of the same transfer fails.
+hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream, bool* begun) {
+  if (args.pool_tab) return launch_pool(args, stream, begun);
   if (args.self_contained && args.kv_layers == 0) {  // linear: the lean kernel; KV: below, by layout
     if (args.n_pre <= 4) return launch_whole<4>(args, grid, stream);
     if (args.n_pre <= 16) return launch_whole<16>(args, grid, stream);
@@ -1238,7 +1243,8 @@ hipError_t launch_noalloc_table(const NoallocTabArgs& t, hipStream_t stream) {
 hipError_t launch_noalloc(PoolArgs& p, uint32_t n, uint32_t layout, uint32_t wgs, hipStream_t stream) {
   uint64_t mis = p.piece | p.pool;
   for (uint32_t l = 0; l < p.layers; ++l) mis |= p.w[l];
-  return launch_pool_kernel(p, n, layout, (mis & 15u) == 0, wgs, stream);
+  bool begun = false;  // this call's scratch is never given back
+  return launch_pool_kernel(p, n, layout, (mis & 15u) == 0, wgs, stream, &begun);
 }
 
 }  // namespace mma

@@ -17,7 +17,7 @@
 
 namespace mma {
 
-hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream);
+hipError_t launch_transfer(const KernelArgs& args, uint32_t grid, hipStream_t stream, bool* begun);
 hipError_t launch_digest(const void* ptr, uint64_t bytes, uint64_t* out, hipStream_t stream);
 hipError_t noalloc_setup(int dev);
 uint64_t* noalloc_scratch(int dev);
@@ -402,6 +402,9 @@ mma_status_t submit(std::unique_ptr<Transfer> x, uint64_t payload_bytes, void* s
   }
   DeviceGuard dg(rt->dev);
   const hipStream_t hs = static_cast<hipStream_t>(stream);
+  // A transfer of several launches of which a later one failed: what is on the
+  // stream still uses the light slot and the table, so neither is reused.
+  bool begun = false;
   if (e->device_control()) {
     // Device control: the transfer is planned in full here and the kernel
     // tracks its completion; no engine-thread work. A transfer with more
@@ -410,12 +413,13 @@ mma_status_t submit(std::unique_ptr<Transfer> x, uint64_t payload_bytes, void* s
                                         : e->prepare_device(x.get(), ++rt->seq, payload_bytes, kv, wd,
                                                             stream_idle(hs), a);
     if (grid) {
-      const hipError_t err = launch_transfer(a, grid, hs);
+      const hipError_t err = launch_transfer(a, grid, hs, &begun);
       if (err != hipSuccess) {
-        if (x->light >= 0)
-          e->release_unused(x.get());
-        else
+        if (x->light >= 0) {
+          if (!begun) e->release_unused(x.get());
+        } else {
           e->abandon_device(x.get(), rt->cfg.watchdog_ms + 10000ull);
+        }
         return fail(MMA_ERR_HIP, "dummy-task kernel launch failed: %s", hipGetErrorString(err));
       }
       e->track(std::move(x));
@@ -433,7 +437,7 @@ mma_status_t submit(std::unique_ptr<Transfer> x, uint64_t payload_bytes, void* s
     std::shared_ptr<Waiter> w = x->waiter;
     Transfer* raw = x.get();  // the engine retires it only after the kernel (or `unlaunched`) releases it
     e->submit(std::move(x));
-    const hipError_t err = launch_transfer(a, grid, hs);
+    const hipError_t err = launch_transfer(a, grid, hs, &begun);
     if (err != hipSuccess) {
       raw->unlaunched.store(true, std::memory_order_release);
       std::unique_lock<std::mutex> lk(w->mu);
@@ -442,9 +446,9 @@ mma_status_t submit(std::unique_ptr<Transfer> x, uint64_t payload_bytes, void* s
     }
     return MMA_OK;
   }
-  const hipError_t err = launch_transfer(a, grid, hs);
+  const hipError_t err = launch_transfer(a, grid, hs, &begun);
   if (err != hipSuccess) {
-    e->release_unused(x.get());
+    if (!begun) e->release_unused(x.get());
     return fail(MMA_ERR_HIP, "dummy-task kernel launch failed: %s", hipGetErrorString(err));
   }
   // A whole transfer needs nothing from the engine thread but retirement:
