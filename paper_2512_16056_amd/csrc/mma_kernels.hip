@@ -682,9 +682,9 @@ constexpr int kWaitVm0 = 0x0f70;
 // the tag after every workgroup: the data itself becomes visible to later work
 // through the stream, when the kernel ends, as for any kernel (a device-wide
 // release per workgroup would write back the L2 of its XCD each time). Counts on
-// one address go one after the other, some 12 ns each, so more than 32 workgroups
-// count in groups of at least 16 first: with 512 and more to a group a launch of
-// 2048 took 8 us longer. A launch of many has its tag written by a launch of its
+// one address go one after the other, some 12 ns each, so 32 workgroups and more
+// count in groups of at least 16 first (pool_groups): with 512 and more to a group a
+// launch of 2048 took 8 us longer. A launch of many has its tag written by a launch of its
 // own instead (kPoolTagLaunch).
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   if (!a.done && !a.claim) return;
@@ -695,7 +695,7 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
     for (uint32_t t = blockIdx.x; t < a.tags; t += gridDim.x) st_sys(&a.done[t], make_tag(a.seq, t));
     return;
   }
-  const uint32_t groups = max(1u, min(gridDim.x / 16u, 0u + kPoolCtrs));
+  const uint32_t groups = pool_groups(gridDim.x, a.claim != nullptr, kPoolCtrs);
   if (groups > 1) {
     const uint32_t i = blockIdx.x % groups, members = (gridDim.x - i + groups - 1) / groups;
     uint32_t* c = a.ctr + (1 + i) * kPoolCtrStride;

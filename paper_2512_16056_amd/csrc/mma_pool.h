@@ -77,6 +77,15 @@ MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t units, 
   return g;
 }
 
+// Groups in which the workgroups of a launch count when they finish, at least 16
+// to a group. A launch whose waves claim spans counts in one, whatever its grid:
+// its claim counter stands where the first group's counter would, and the table of
+// a fetch without allocations follows right after. Its workgroups are few.
+MMA_POOL_HD inline uint32_t pool_groups(uint32_t grid, bool claims, uint32_t most) {
+  const uint32_t groups = grid / 16u < most ? grid / 16u : most;
+  return claims || groups == 0 ? 1 : groups;
+}
+
 // Table entry and piece of its block of piece number q.
 struct PoolPiece {
   uint32_t entry, p;

@@ -50,7 +50,8 @@ constexpr uint32_t kPoolMaxWorkgroups = 8192;
 constexpr uint32_t kPoolWords = 448;      // 3.9 KiB of arguments in all
 // Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
 // finished workgroups of group i, [0] the finished groups (one group: its
-// workgroups; [1] then is free for the claims of a launch over the link).
+// workgroups; [1] then is free for the claims of a launch over the link, which
+// always is one group: pool_groups).
 constexpr uint32_t kPoolCtrs = 64;
 constexpr uint32_t kPoolCtrStride = 32;   // 128 bytes
 constexpr uint32_t kPoolCtrWords = (1 + kPoolCtrs) * kPoolCtrStride;

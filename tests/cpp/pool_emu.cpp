@@ -56,6 +56,12 @@ extern "C" uint64_t emu_div(uint32_t d, uint32_t first, uint32_t count) {
   return 0;
 }
 
+// The highest counter (kPoolCtrStride words each) that the workgroups of a launch count on.
+extern "C" uint32_t emu_last_counter(uint32_t grid, int claims, uint32_t most) {
+  const uint32_t groups = pool_groups(grid, claims != 0, most);
+  return groups > 1 ? groups : 0;
+}
+
 // x-packed blocks: key lanes move one unit, value lanes X units transposed, over
 // the same maps. E: element bytes; HC: 16-byte units per token.
 extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes,

@@ -655,6 +655,35 @@ def test_kv_link_launch(shape, gpu_layout, mis):
         raw.free()
 
 
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("workgroups", [20, 21, 64, 256])
+def test_kv_link_launch_claims_with_many_workgroups(workgroups, noalloc):
+    """A fetch over the link large enough that its waves claim spans, with 30, 32 and many workgroups,
+    twice (counters are back at 0), with a table in memory: claims and finish counts stay apart."""
+    s = W.KVShape(layers=2, block_tokens=16, kv_heads=4, head_dim=128, elem_bytes=2, gpu_num_blocks=520,
+                  host_num_slots=500, n_blocks=480)
+    assert s.n_blocks * s.slot_bytes >= 16 << 20
+    log(f"claims workgroups={workgroups} noalloc={noalloc}")
+    lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                        s.host_num_slots, mma.MMA_KV_LAYOUT_PIECE)
+    hs, gb = W.kv_fetch_tables(s, cfg=3)
+    with session("both", cu_workgroups=workgroups, cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+        pool = mma.PinnedBuffer(s.host_num_slots * s.slot_bytes)
+        pool.array[:] = np.random.default_rng(51).integers(0, 256, pool.nbytes, dtype=np.uint8)
+        pv = pool.array.reshape(s.host_num_slots, s.slot_bytes)
+        for _ in range(2):
+            layers = _layers(s, W.GPU_POISON)
+            before = _layer_views(s, layers)
+            (mma.mma_kv_fetch_noalloc if noalloc else mma.mma_kv_fetch)(lay, pool, layers, hs, gb)
+            torch.cuda.synchronize()
+            mma.mma_synchronize()
+            for l in range(s.layers):
+                want = okv.kv_fetch_layer(pv, before[l], l, s.layers, hs, gb, okv.LAYOUT_PIECE, _geom(s))
+                assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), l
+        del pv
+        pool.free()
+
+
 XP_POOL_SHAPES = {
     # pieces below and at the size that goes through LDS, with 8 and 9 MiB and a bit in all
     "small_pieces": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=1300,

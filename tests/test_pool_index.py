@@ -41,6 +41,9 @@ def emu(tmp_path_factory):
     f.div = lib.emu_div
     f.div.restype = ctypes.c_uint64
     f.div.argtypes = [ctypes.c_uint32] * 3
+    f.last_counter = lib.emu_last_counter
+    f.last_counter.restype = ctypes.c_uint32
+    f.last_counter.argtypes = [ctypes.c_uint32, ctypes.c_int, ctypes.c_uint32]
     return f
 
 
@@ -117,3 +120,12 @@ def test_division_by_reciprocal(emu):
         for first in {0, max(d - 500, 0), 2 ** 28 // d * d - min(500, 2 ** 28 // d * d), 2 ** 32 - 1000}:
             bad = emu.div(d, first, 1000)
             assert bad == 0, (d, bad - 1)
+
+
+def test_finish_counters_keep_off_the_claims(emu):
+    """Counter 1 holds the claims of a launch that has them, and nothing after it is the launch's own
+    in a fetch without allocations (its table follows); without claims 64 groups fit the counters."""
+    for grid in [1, 15, 16, 31, 32, 33, 48, 96, 255, 256, 384]:
+        assert emu.last_counter(grid, 1, 64) == 0, grid
+    for grid, last in [(1, 0), (31, 0), (32, 2), (1024, 64), (16384, 64)]:
+        assert emu.last_counter(grid, 0, 64) == last, grid
