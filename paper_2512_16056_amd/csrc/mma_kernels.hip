@@ -740,7 +740,7 @@ __device__ __forceinline__ void span_next(const PoolArgs& a, SpanWalk& s) {
   s.at = a.claim ? s.nw + __builtin_amdgcn_readfirstlane(s.got) : s.at + s.nw;
 }
 
-constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link
+constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link, and of staged x-packed keys
 
 // Aligned pieces in the piece layout or (kHnd) head-major: one 16-byte unit per
 // lane. What hides the latency is the 32 waves a CU holds (the kernel takes few
@@ -837,9 +837,23 @@ __device__ __forceinline__ void transpose_units(u32x4 (&v)[16 / E]) {
 // mma_kv_link_kernel): keys first, then values, both straight through registers
 // (XpMap), so no LDS limits the waves in flight and small pieces share a wave.
 // Where it is used and what it gains: xp_registers.
-template <uint32_t E, bool kLink>
+// kStage (in HBM, where xp_stages): the block side of the values goes through a
+// tile of the wave in LDS, in whole rows of 1 KiB, where each lane by itself
+// accesses 2 * B bytes of each of its x dimensions at a time. The tiles (8 KiB a
+// wave for 2-byte elements, 16 for one byte) leave 20 and 8 waves a CU, so a wave
+// reads 8 rows of keys at once, as over the link. Before (the faster of whole
+// pieces through LDS and plain registers) / staged, fetch and offload, us:
+//   2 GiB of 32 KiB pieces          828 / 813    872 / 845
+//   1 GiB                           408 / 412    430 / 421
+//   128 MiB                          54 / 45      56 / 47
+//   1 GiB, one-byte elements        469 / 421    534 / 426
+//   469 MiB, 32 tokens x 5 x 80     208 / 192    266 / 229
+// 1, 2 and 4 rows of keys: 2 GiB 1110, 879, 817 and 1092, 871, 846; one-byte
+// elements -, 572, 459.
+template <uint32_t E, bool kLink, bool kStage>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_xp_kernel(PoolArgs a) {
-  constexpr uint32_t X = 16 / E, K = kLink ? kLinkRows : 1;
+  constexpr uint32_t X = 16 / E, K = kLink || kStage ? kLinkRows : 1;
+  __shared__ u32x4 s_tile[kStage ? kWavesPerWG * kWave * X : 1];
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint64_t keys = (a.g.waves + K - 1) / K;
@@ -868,6 +882,48 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_xp_kernel(PoolArgs a) {
 #pragma unroll
       for (uint32_t k = 0; k < K; ++k)
         if (to[k]) *to[k] = v[k];
+    } else if constexpr (kStage) {
+      const PoolUnit x = pool_unit(a.gv, static_cast<uint32_t>(s.at - keys), lane);
+      const uint32_t first = __builtin_amdgcn_readfirstlane(x.u), n = min(kWave, a.gv.units - first) * X;
+      const PoolEnds e = pool_ends(a, kind_piece(a.gv, __builtin_amdgcn_readfirstlane(x.q), 1));
+      const XpAt p = xp_val(a.xp, x.ok ? x.u : first);
+      const uint32_t host = xp_host(a.xp, p.hc, p.t * X), hstep = a.xp.HC * 16;
+      const uint64_t blk = static_cast<uint64_t>(first) * X * 16;
+      lu4* tile = (lu4*)(s_tile) + wave * kWave * X;
+      u32x4 v[X];
+      if (a.to_paged) {
+        if (x.ok) {
+#pragma unroll
+          for (uint32_t i = 0; i < X; ++i)
+            v[i] = *(const gu4*)(e.from + host + static_cast<uint64_t>(i) * hstep);
+          transpose_units<E>(v);
+#pragma unroll
+          for (uint32_t i = 0; i < X; ++i) tile[xp_stage_at<X>(a.xp, xp_stage_unit<X>(a.xp, lane, i))] = v[i];
+        }
+        wave_sync();
+#pragma unroll
+        for (uint32_t k = 0; k < X; ++k) {
+          const uint32_t u = k * kWave + lane;
+          if (u < n) __builtin_nontemporal_store(tile[xp_stage_at<X>(a.xp, u)], (gu4*)(e.to + blk) + u);
+        }
+      } else {
+#pragma unroll
+        for (uint32_t k = 0; k < X; ++k) {
+          const uint32_t u = k * kWave + lane;
+          v[k] = __builtin_nontemporal_load((const gu4*)(e.from + blk) + (u < n ? u : 0));
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < X; ++k) tile[xp_stage_at<X>(a.xp, k * kWave + lane)] = v[k];
+        wave_sync();
+        if (x.ok) {
+#pragma unroll
+          for (uint32_t i = 0; i < X; ++i) v[i] = tile[xp_stage_at<X>(a.xp, xp_stage_unit<X>(a.xp, lane, i))];
+          transpose_units<E>(v);
+#pragma unroll
+          for (uint32_t i = 0; i < X; ++i) *(gu4*)(e.to + host + static_cast<uint64_t>(i) * hstep) = v[i];
+        }
+      }
+      wave_sync();  // before the next row overwrites the tile
     } else {
       const PoolUnit x = pool_unit(a.gv, static_cast<uint32_t>(s.at - keys), lane);
       if (x.ok) {
@@ -1024,8 +1080,9 @@ hipError_t launch_whole(const KernelArgs& args, uint32_t grid, hipStream_t strea
                          stream);
 }
 
-// Whether x-packed pieces go through registers (mma_kv_pool_xp_kernel) or a wave's
-// LDS tile, by what was faster (LDS / registers, us):
+// Whether x-packed pieces that are not staged (xp_stages) go through registers
+// (mma_kv_pool_xp_kernel) or whole through a wave's LDS tile, by what was faster
+// (LDS / registers, us):
 //  - pieces below 4 KiB, of which registers take several at a time: 1 GiB of 2 KiB
 //    pieces in HBM, fetch 1243 / 503, offload 1228 / 585; 64 MiB over the link 1415
 //    / 1221; but 1 GiB of 6 KiB pieces, fetch 541 / 755: a lane's stores go to x
@@ -1064,6 +1121,7 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
   p.g = pool_geom(n, 2 * p.layers, p.piece >> 4, by_piece);
   const void* k = nullptr;
   uint64_t spans = (p.g.waves + rows - 1) / rows;  // of one wave each
+  const bool stage = !wgs && layout == kKvLayoutXPacked && xp_stages(p.piece, p.tokens, p.elem);
   if (layout == kKvLayoutHnd) {
     const bool heads_first = !wgs && p.to_paged;
     p.hnd = heads_first ? hnd_map(p.heads, p.tokens, p.row_bytes / 16) : hnd_map(p.tokens, p.heads, p.row_bytes / 16);
@@ -1071,7 +1129,7 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
                                        : reinterpret_cast<const void*>(&mma_kv_pool_kernel<true, false>))
         : p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<true, true>)
                 : reinterpret_cast<const void*>(&mma_kv_link_kernel<true, false>);
-  } else if (layout == kKvLayoutXPacked && !xp_registers(p, n, wgs != 0)) {
+  } else if (layout == kKvLayoutXPacked && !stage && !xp_registers(p, n, wgs != 0)) {
     lds = kWavesPerWG * p.lds_wave;
     k = p.elem == 1   ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<1>)
         : p.elem == 2 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<2>)
@@ -1087,16 +1145,21 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
     p.xp = xp_map(p.tokens, hc, x);
     p.g = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * p.tokens, by_piece);
     p.gv = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * (p.tokens / x), by_piece);
-    spans = (p.g.waves + rows - 1) / rows + p.gv.waves;
-    const void* const xp[4][2] = {{reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false>),
-                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, true>)},
-                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, false>),
-                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, true>)},
-                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, false>),
-                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, true>)},
-                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, false>),
-                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, true>)}};
-    k = xp[p.elem == 1 ? 0 : p.elem == 2 ? 1 : p.elem == 4 ? 2 : 3][wgs ? 1 : 0];
+    const uint32_t key_rows = stage ? kLinkRows : rows;
+    spans = (p.g.waves + key_rows - 1) / key_rows + p.gv.waves;
+    const void* const xp[4][3] = {{reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, true, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, false, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, true, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<2, false, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, false, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, true, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<4, false, true>)},
+                                  {reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, false, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, true, false>),
+                                   reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, false, true>)}};
+    k = xp[p.elem == 1 ? 0 : p.elem == 2 ? 1 : p.elem == 4 ? 2 : 3][wgs ? 1 : stage ? 2 : 0];
   } else if (aligned) {
     k = !wgs ? reinterpret_cast<const void*>(&mma_kv_pool_kernel<false, true>)
         : p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<false, true>)

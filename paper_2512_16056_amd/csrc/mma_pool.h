@@ -171,6 +171,25 @@ MMA_POOL_HD inline uint32_t xp_val_block(const XpMap& m, uint32_t dim, uint32_t 
   return (dim * m.groups.d + group) * 16;
 }
 
+// A row of 64 value tiles covers 64 * x units of the block in a row, 8 KiB of 2-byte
+// elements, where B / x divides 64 and pieces have rows of their own. It can then
+// go through a tile in LDS, so that every access to the block is 1 KiB in a row:
+// unit u of the row is kept at xp_stage_at(u), and xp_stage_unit is the unit that
+// lane `lane` holds in its register i (of the block's order). The exchange of units
+// within a run of x dimensions spreads the lanes' accesses over the banks.
+MMA_POOL_HD inline bool xp_stages(uint64_t piece, uint32_t B, uint32_t elem) {
+  const uint32_t x = 16 / elem, groups = B / x;
+  return piece / 16 / x >= kPoolRowUnits && groups <= kPoolRowUnits && (groups & (groups - 1)) == 0;
+}
+template <uint32_t X>
+MMA_POOL_HD inline uint32_t xp_stage_unit(const XpMap& m, uint32_t lane, uint32_t i) {
+  return (div_by(m.groups, lane) * X + i) * m.groups.d + (lane & (m.groups.d - 1));
+}
+template <uint32_t X>
+MMA_POOL_HD inline uint32_t xp_stage_at(const XpMap& m, uint32_t u) {
+  return u ^ (div_by(m.groups, u) / X % X * m.groups.d);
+}
+
 }  // namespace mma
 
 #endif  // MMA_POOL_H_

@@ -62,6 +62,34 @@ extern "C" uint32_t emu_last_counter(uint32_t grid, int claims, uint32_t most) {
   return groups > 1 ? groups : 0;
 }
 
+// The tile of a staged row: unit and place of every lane's register i. Bijective places, and the
+// same unit of the block as the lane would write by itself.
+template <uint32_t X>
+static int stage_row(const XpMap& m, const PoolGeom& g, uint64_t w) {
+  bool place[64 * X] = {}, unit[64 * X] = {};
+  const uint32_t first = pool_unit(g, static_cast<uint32_t>(w), 0).u;
+  const uint32_t n = (g.units - first < 64 ? g.units - first : 64) * X;
+  for (uint32_t u = 0; u < 64 * X; ++u) {
+    const uint32_t at = xp_stage_at<X>(m, u);
+    if (at >= 64 * X || place[at]) return 10;
+    place[at] = true;
+  }
+  for (uint32_t lane = 0; lane < 64; ++lane) {
+    const PoolUnit x = pool_unit(g, static_cast<uint32_t>(w), lane);
+    if (!x.ok) continue;
+    const XpAt a = xp_val(m, x.u);
+    for (uint32_t i = 0; i < X; ++i) {
+      const uint32_t u = xp_stage_unit<X>(m, lane, i);
+      if (u >= n || unit[u]) return 11;
+      unit[u] = true;
+      if ((first * X + u) * 16 != xp_val_block(m, a.hc * X + i, a.t)) return 12;
+    }
+  }
+  for (uint32_t u = 0; u < n; ++u)
+    if (!unit[u]) return 13;
+  return 0;
+}
+
 // x-packed blocks: key lanes move one unit, value lanes X units transposed, over
 // the same maps. E: element bytes; HC: 16-byte units per token.
 extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes,
@@ -75,6 +103,15 @@ extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, u
   const uint8_t* src = to_paged ? pool : cache;
   uint8_t* dst = to_paged ? cache : pool;
   const uint64_t src_bytes = to_paged ? pool_bytes : cache_bytes, dst_bytes = to_paged ? cache_bytes : pool_bytes;
+  if (!link && xp_stages(piece, B, E)) {
+    for (uint64_t w = 0; w < geom[1].waves; ++w) {
+      const int rc = X == 16  ? stage_row<16>(m, geom[1], w)
+                     : X == 8 ? stage_row<8>(m, geom[1], w)
+                     : X == 4 ? stage_row<4>(m, geom[1], w)
+                              : stage_row<2>(m, geom[1], w);
+      if (rc) return rc;
+    }
+  }
   for (uint32_t kind = 0; kind < 2; ++kind) {
     const PoolGeom& g = geom[kind];
     for (uint64_t w = 0; w < g.waves; ++w)

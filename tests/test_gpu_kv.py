@@ -698,6 +698,15 @@ XP_POOL_SHAPES = {
                          host_num_slots=80, n_blocks=77),
     "bytes": W.KVShape(layers=2, block_tokens=32, kv_heads=5, head_dim=80, elem_bytes=1, gpu_num_blocks=40,
                        host_num_slots=36, n_blocks=33),
+    # values staged through a tile: a short last row, one-byte and 8-byte elements, many token groups
+    "staged": W.KVShape(layers=3, block_tokens=16, kv_heads=5, head_dim=80, elem_bytes=2, gpu_num_blocks=40,
+                        host_num_slots=36, n_blocks=33),
+    "staged_bytes": W.KVShape(layers=2, block_tokens=32, kv_heads=8, head_dim=80, elem_bytes=1, gpu_num_blocks=40,
+                              host_num_slots=36, n_blocks=31),
+    "staged_doubles": W.KVShape(layers=2, block_tokens=2, kv_heads=5, head_dim=128, elem_bytes=8, gpu_num_blocks=20,
+                                host_num_slots=18, n_blocks=13),
+    "staged_groups": W.KVShape(layers=1, block_tokens=128, kv_heads=2, head_dim=64, elem_bytes=2, gpu_num_blocks=9,
+                               host_num_slots=8, n_blocks=7),
 }
 
 

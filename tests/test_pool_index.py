@@ -84,9 +84,10 @@ def test_pool_index_maps_match_oracle(emu, shape, layout, link):
 
 
 # tokens, heads, head_dim, element bytes, layers, blocks: squares of 8 x 8 units and shapes they do not
-# divide, pieces that share a row, each element size
+# divide, pieces that share a row, each element size; value rows that go through a tile, the last ones short
 XP_SHAPES = [(16, 8, 128, 2, 2, 4), (16, 1, 64, 2, 3, 9), (16, 5, 80, 2, 1, 3), (16, 4, 96, 1, 2, 5),
-             (32, 2, 16, 1, 1, 6), (8, 3, 16, 2, 2, 5), (24, 1, 24, 2, 1, 3), (4, 8, 16, 4, 2, 3), (2, 5, 8, 8, 1, 7)]
+             (32, 2, 16, 1, 1, 6), (8, 3, 16, 2, 2, 5), (24, 1, 24, 2, 1, 3), (4, 8, 16, 4, 2, 3), (2, 5, 8, 8, 1, 7),
+             (32, 8, 80, 1, 1, 3), (16, 8, 64, 4, 1, 2), (2, 5, 128, 8, 1, 2), (128, 2, 64, 2, 1, 2)]
 
 
 @pytest.mark.parametrize("link", [0, 1])
