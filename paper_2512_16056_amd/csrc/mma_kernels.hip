@@ -678,6 +678,23 @@ __device__ __forceinline__ PoolPiece kind_piece(const PoolGeom& g, uint32_t q, u
 // s_waitcnt vmcnt(0), the other counters left alone (gfx9 encoding).
 constexpr int kWaitVm0 = 0x0f70;
 
+// The counters of a pool launch (pool_last). landed() is a wait for the wave's own
+// stores, which at this scope go to memory themselves: a release, which writes back
+// the L2, cost a launch of one block 6 us.
+struct DevCounters {
+  uint32_t* c;
+  __device__ __forceinline__ uint32_t add(uint32_t i) const {
+    return __hip_atomic_fetch_add(c + i * kPoolCtrStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void zero(uint32_t i) const {
+    __hip_atomic_store(c + i * kPoolCtrStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void landed() const {
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
 // The workgroup that finishes last writes the done tag. The counters only order
 // the tag after every workgroup: the data itself becomes visible to later work
 // through the stream, when the kernel ends, as for any kernel (a device-wide
@@ -695,24 +712,8 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
     for (uint32_t t = blockIdx.x; t < a.tags; t += gridDim.x) st_sys(&a.done[t], make_tag(a.seq, t));
     return;
   }
-  const uint32_t groups = pool_groups(gridDim.x, a.claim != nullptr, kPoolCtrs);
-  if (groups > 1) {
-    const uint32_t i = blockIdx.x % groups, members = (gridDim.x - i + groups - 1) / groups;
-    uint32_t* c = a.ctr + (1 + i) * kPoolCtrStride;
-    if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
-    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  const uint32_t members = groups > 1 ? groups : gridDim.x;
-  if (__hip_atomic_fetch_add(a.ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
-  __hip_atomic_store(a.ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (a.claim) __hip_atomic_store(a.claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!a.done) return;
-  // The counters are back at 0 where other XCDs see it before the tag frees them
-  // for another launch: a wait for these stores, which go there themselves. A
-  // release, which writes back the L2, cost a launch of one block 6 us.
+  if (!pool_last(blockIdx.x, gridDim.x, a.claim != nullptr, kPoolCtrs, DevCounters{a.ctr}) || !a.done) return;
   if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  __builtin_amdgcn_sched_barrier(0);
   st_sys(a.done, make_tag(a.seq, 0));
 }
 

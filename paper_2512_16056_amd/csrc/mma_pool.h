@@ -86,6 +86,28 @@ MMA_POOL_HD inline uint32_t pool_groups(uint32_t grid, bool claims, uint32_t mos
   return claims || groups == 0 ? 1 : groups;
 }
 
+
+// What workgroup `wg` of `grid` does when it has finished: true for the one that
+// finished last, with every counter back at 0 in memory. Counter 0 counts the
+// groups (one group: its workgroups), 1 + i the workgroups of group i, or 1 the
+// claims. c.add(i) adds 1 to counter i and returns what it held, c.zero(i) stores
+// 0 in it, c.landed() waits until this wave's stores are in memory.
+template <class Counters>
+MMA_POOL_HD inline bool pool_last(uint32_t wg, uint32_t grid, bool claims, uint32_t most, Counters c) {
+  const uint32_t groups = pool_groups(grid, claims, most);
+  if (groups > 1) {
+    const uint32_t i = wg % groups, members = (grid - i + groups - 1) / groups;
+    if (c.add(1 + i) != members - 1) return false;
+    c.zero(1 + i);
+    c.landed();  // the count below lets the last workgroup, another wave, free this counter
+  }
+  if (c.add(0) != (groups > 1 ? groups : grid) - 1) return false;
+  c.zero(0);
+  if (claims) c.zero(1);
+  c.landed();
+  return true;
+}
+
 // Table entry and piece of its block of piece number q.
 struct PoolPiece {
   uint32_t entry, p;

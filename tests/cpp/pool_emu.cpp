@@ -62,6 +62,37 @@ extern "C" uint32_t emu_last_counter(uint32_t grid, int claims, uint32_t most) {
   return groups > 1 ? groups : 0;
 }
 
+// Counters whose stores of 0 stay with the workgroup that made them until it waits (or, in the
+// end, until it is over).
+struct EmuCounters {
+  std::vector<uint32_t>* mem;
+  std::vector<uint32_t>* pending;  // of this workgroup
+  uint32_t add(uint32_t i) const { return (*mem)[i]++; }
+  void zero(uint32_t i) const { pending->push_back(i); }
+  void landed() const {
+    for (uint32_t i : *pending) (*mem)[i] = 0;
+    pending->clear();
+  }
+};
+
+// The workgroups of a launch finish in the order of `order`. 0 if the last one alone is told so,
+// and at that moment no counter is short of its 0: the done tag written then frees them for
+// another launch.
+extern "C" int emu_finish(const uint32_t* order, uint32_t grid, int claims, uint32_t most) {
+  std::vector<uint32_t> mem(1 + most, 0);
+  if (claims) mem[1] = 12345;  // what the claims left
+  std::vector<std::vector<uint32_t>> pending(grid);
+  for (uint32_t k = 0; k < grid; ++k) {
+    const bool last = pool_last(order[k], grid, claims != 0, most, EmuCounters{&mem, &pending[k]});
+    if (last != (k == grid - 1)) return 1;
+  }
+  for (const auto& p : pending)
+    if (!p.empty()) return 2;
+  for (uint32_t v : mem)
+    if (v) return 3;
+  return 0;
+}
+
 // The tile of a staged row: unit and place of every lane's register i. Bijective places, and the
 // same unit of the block as the lane would write by itself.
 template <uint32_t X>

@@ -44,6 +44,9 @@ def emu(tmp_path_factory):
     f.last_counter = lib.emu_last_counter
     f.last_counter.restype = ctypes.c_uint32
     f.last_counter.argtypes = [ctypes.c_uint32, ctypes.c_int, ctypes.c_uint32]
+    f.finish = lib.emu_finish
+    f.finish.restype = ctypes.c_int
+    f.finish.argtypes = [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_int, ctypes.c_uint32]
     return f
 
 
@@ -130,3 +133,15 @@ def test_finish_counters_keep_off_the_claims(emu):
         assert emu.last_counter(grid, 1, 64) == 0, grid
     for grid, last in [(1, 0), (31, 0), (32, 2), (1024, 64), (16384, 64)]:
         assert emu.last_counter(grid, 0, 64) == last, grid
+
+
+@pytest.mark.parametrize("grid", [1, 15, 16, 31, 32, 33, 48, 96, 384, 1024, 1025, 16384])
+def test_finish_counters_are_reset_before_the_done_tag(emu, grid):
+    """The done tag frees the launch's counters for another one: with each store of 0 held back until
+    the workgroup that made it waits for it, none is outstanding when the last workgroup writes the tag."""
+    r = np.random.default_rng(grid)
+    for claims in (0, 1):
+        for _ in range(3):
+            order = r.permutation(grid).astype(np.uint32)
+            rc = emu.finish(order.ctypes.data, grid, claims, 64)
+            assert rc == 0, (grid, claims, rc)
