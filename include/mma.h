@@ -384,10 +384,11 @@ mma_status_t mma_kv_offload(const mma_kv_layout_t* layout, void* host_pool, cons
  * thread); the transfer is complete when that launch completes on the stream,
  * and it does not appear in mma_get_stats. Layer pointers and block table travel
  * in its arguments up to 448 of them in all; a longer table goes to `scratch`, a
- * fixed array of the library's device code (256 B of counters + 8 B per block,
+ * fixed array of the library's device code (256 B of claim words + 8 B per block,
  * 512 KiB + 256 B in all per GPU, held until the process ends) whose address
  * mma_init looks up, through the arguments of ceil(n_blocks / 448) small launches
- * before.
+ * before. Under capture a fetch of 16 MiB and more (x-packed: 6 MiB) has one more
+ * small launch before it.
  * n_blocks at most 65536: larger calls return MMA_ERR_INVALID_ARG and enqueue
  * nothing. Every call on one GPU shares its scratch array, which keeps the
  * last call's table: calls that may overlap on one GPU (other streams, other

@@ -704,7 +704,9 @@ struct DevCounters {
 // launch of 2048 took 8 us longer. A launch of many has its tag written by a launch of its
 // own instead (kPoolTagLaunch).
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
-  if (!a.done && !a.claim) return;
+  if (a.clear && blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!a.done) return;
   if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -712,7 +714,7 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
     for (uint32_t t = blockIdx.x; t < a.tags; t += gridDim.x) st_sys(&a.done[t], make_tag(a.seq, t));
     return;
   }
-  if (!pool_last(blockIdx.x, gridDim.x, a.claim != nullptr, kPoolCtrs, DevCounters{a.ctr}) || !a.done) return;
+  if (!pool_last(blockIdx.x, gridDim.x, a.claim != nullptr, kPoolCtrs, DevCounters{a.ctr})) return;
   if (a.release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   st_sys(a.done, make_tag(a.seq, 0));
 }
@@ -1037,6 +1039,11 @@ __global__ __launch_bounds__(kBlock) void mma_kv_noalloc_table_kernel(NoallocTab
   for (uint32_t j = threadIdx.x; j < a.count; j += kBlock) tab[a.first + j] = a.e[j];
 }
 
+// Claim words [0, n) of the scratch array to 0.
+__global__ void mma_kv_noalloc_clear_kernel(uint32_t* w, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += kWave) __hip_atomic_store(w + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // digest += sum_i (w_i + 1) * (2i + 1) mod 2^64 over nw words (+ one zero-padded
 // tail word of tail_len bytes at tail). vec4: w is 16-byte aligned.
 __global__ __launch_bounds__(256) void mma_digest_kernel(const uint32_t* __restrict__ w, uint64_t nw,
@@ -1213,6 +1220,7 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream, bool* begun) 
   p.words = p.layers;
   p.tags = args.pool_link && !args.pool_claim ? args.pool_wgs : 0;
   p.claim = args.pool_claim ? args.pool_ctr + kPoolCtrStride : nullptr;
+  p.clear = nullptr;
   if (p.layers + args.pool_blocks <= kPoolWords) {
     p.words += static_cast<uint32_t>(args.pool_blocks);
     memcpy(p.w + p.layers, args.pool_tab_host, args.pool_blocks * sizeof(uint64_t));
@@ -1272,7 +1280,7 @@ hipError_t launch_digest(const void* ptr, uint64_t bytes, uint64_t* out, hipStre
 
 
 // ------------------------------------------------------- KV fetch that allocates nothing
-// The no-alloc KV fetch's counters and block table: a fixed array of this
+// The no-alloc KV fetch's claim words and block table: a fixed array of this
 // library's device code, so that the call needs no allocation. Every GPU the
 // library runs on holds its own copy, at its own address, until the process
 // ends. In host code the array's name is only a stand-in: its device address
@@ -1281,7 +1289,6 @@ hipError_t launch_digest(const void* ptr, uint64_t bytes, uint64_t* out, hipStre
 static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
 
 namespace {
-constexpr int kNoallocDevices = 64;
 uint64_t* g_scratch_dev[kNoallocDevices] = {};
 }  // namespace
 
@@ -1302,6 +1309,12 @@ hipError_t launch_noalloc_table(const NoallocTabArgs& t, hipStream_t stream) {
   void* params[] = {const_cast<NoallocTabArgs*>(&t)};
   return hipLaunchKernel(reinterpret_cast<const void*>(&mma_kv_noalloc_table_kernel), dim3(1), dim3(kBlock), params,
                          0, stream);
+}
+
+hipError_t launch_noalloc_clear(uint32_t* w, uint32_t n, hipStream_t stream) {
+  void* params[] = {&w, &n};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&mma_kv_noalloc_clear_kernel), dim3(1), dim3(kWave), params, 0,
+                         stream);
 }
 
 hipError_t launch_noalloc(PoolArgs& p, uint32_t n, uint32_t layout, uint32_t wgs, hipStream_t stream) {

@@ -79,8 +79,8 @@ MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t units, 
 
 // Groups in which the workgroups of a launch count when they finish, at least 16
 // to a group. A launch whose waves claim spans counts in one, whatever its grid:
-// its claim counter stands where the first group's counter would, and the table of
-// a fetch without allocations follows right after. Its workgroups are few.
+// its claim counter stands where the first group's counter would. Its workgroups
+// are few.
 MMA_POOL_HD inline uint32_t pool_groups(uint32_t grid, bool claims, uint32_t most) {
   const uint32_t groups = grid / 16u < most ? grid / 16u : most;
   return claims || groups == 0 ? 1 : groups;
@@ -107,6 +107,17 @@ MMA_POOL_HD inline bool pool_last(uint32_t wg, uint32_t grid, bool claims, uint3
   c.landed();
   return true;
 }
+
+// A fetch without allocations has no slot of the engine and no counters of its own.
+// Those that claim spans take 32 words in turn, 16 in each of two 128-byte lines, and
+// the n-th of them sets the word of the (n + 16)-th, in the other line, to 0: it
+// relies on nothing else that an earlier launch left behind, and counts no
+// workgroups. So up to 16 calls that overlap, which is their callers' mistake, spoil
+// neither each other's claims nor any later call's, and more of them the next 16 at
+// most.
+constexpr uint32_t kClaimAhead = 16, kClaimWords = 64, kClaimLone = 16;
+MMA_POOL_HD inline uint32_t claim_word(uint32_t n) { return n / kClaimAhead % 2 * 32 + n % kClaimAhead; }
+MMA_POOL_HD inline uint32_t claim_clears(uint32_t n) { return claim_word(n + kClaimAhead); }
 
 // Table entry and piece of its block of piece number q.
 struct PoolPiece {

@@ -175,13 +175,15 @@ struct KernelArgs {
   uint64_t pre[kPrefill][3];  // words a, b, count|kind_p0 of the first ring entries
 };
 
-// Arguments of an HBM pool launch. The workgroup that finishes last writes
-// done[0] = make_tag(seq, 0) and leaves the counters at 0 (done null: neither).
+// Arguments of a pool launch. The workgroup that finishes last writes
+// done[0] = make_tag(seq, 0) and leaves the counters, the claims among them, at 0
+// (done null: neither, and claims are cleared by another launch).
 struct PoolArgs {
   uint64_t* done;
   uint64_t seq;
   uint32_t* ctr;
-  uint32_t* claim;          // counter of claimed spans, 0 between launches; null: fixed shares
+  uint32_t* claim;          // counter of claimed spans, 0 when the launch starts; null: fixed shares
+  uint32_t* clear;          // a word that the launch sets to 0; null: none
   const uint64_t* tab;      // block table in device memory; null: w[layers ..]
   uint64_t pool;
   uint64_t slot_bytes, piece, kstride;
@@ -221,15 +223,17 @@ struct WholeArgs {
 // KV fetch that allocates nothing (mma_kv_fetch_noalloc): one pool launch without
 // a done tag. Its block table travels in the arguments, or, if it does not fit
 // them, in one array of the library's device code, `scratch`, of
-// kNoallocScratchBytes per GPU: the launch's counters (0 between launches) in the
-// first kNoallocTabOffset bytes, then the table (host slot | GPU block << 32 per
-// block), brought there by launches of mma_kv_noalloc_table_kernel whose arguments
-// carry kNoallocTabChunk entries each.
+// kNoallocScratchBytes per GPU: the words that launches claim spans with in the
+// first kNoallocTabOffset bytes (claim_word, and kClaimLone for a launch that cannot
+// rely on another one's clearing: it has one made before it), then the table (host
+// slot | GPU block << 32 per block), brought there by launches of
+// mma_kv_noalloc_table_kernel whose arguments carry kNoallocTabChunk entries each.
+constexpr int kNoallocDevices = 64;
 constexpr uint32_t kNoallocMaxBlocks = 65536;
 constexpr uint32_t kNoallocTabOffset = 256;
 constexpr uint64_t kNoallocScratchBytes = kNoallocTabOffset + 8ull * kNoallocMaxBlocks;
 constexpr uint32_t kNoallocTabChunk = 448;
-static_assert(2 * kPoolCtrStride * sizeof(uint32_t) <= kNoallocTabOffset, "finished workgroups and claims");
+static_assert(kClaimWords * sizeof(uint32_t) <= kNoallocTabOffset, "claims");
 
 struct NoallocTabArgs {
   uint64_t* scratch;  // device address of the scratch array

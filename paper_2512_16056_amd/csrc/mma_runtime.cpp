@@ -22,6 +22,7 @@ hipError_t launch_digest(const void* ptr, uint64_t bytes, uint64_t* out, hipStre
 hipError_t noalloc_setup(int dev);
 uint64_t* noalloc_scratch(int dev);
 hipError_t launch_noalloc_table(const NoallocTabArgs& t, hipStream_t stream);
+hipError_t launch_noalloc_clear(uint32_t* w, uint32_t n, hipStream_t stream);
 hipError_t launch_noalloc(PoolArgs& p, uint32_t n, uint32_t layout, uint32_t wgs, hipStream_t stream);
 
 namespace {
@@ -1004,6 +1005,41 @@ int32_t g_noalloc_sorted[kNoallocMaxBlocks];
 std::mutex g_noalloc_tab_mu;
 uint64_t g_noalloc_tab[kNoallocMaxBlocks], g_noalloc_tmp[kNoallocMaxBlocks];
 
+// Launches that claimed spans, per device, and whether one of them failed, so that
+// the word it had to clear is not.
+struct NoallocClaims {
+  std::atomic<uint32_t> n{0};
+  std::atomic<bool> broken{false};
+};
+NoallocClaims g_noalloc_claims[kNoallocDevices];
+
+// The claim word of a launch about to be made on hs, at 0 when it starts. One that
+// is captured may run any number of times, at any time: it has a word of its own,
+// cleared by a launch before it.
+hipError_t noalloc_claims(PoolArgs& a, int dev, uint32_t* words, hipStream_t hs) {
+  NoallocClaims& c = g_noalloc_claims[dev];
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(hs, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    st = hipStreamCaptureStatusActive;  // not known: the launch that relies on no other one
+  }
+  if (st != hipStreamCaptureStatusNone) {
+    a.claim = words + kClaimLone;
+    return launch_noalloc_clear(a.claim, 1, hs);
+  }
+  if (c.broken.exchange(false)) {
+    const hipError_t err = launch_noalloc_clear(words, kClaimWords, hs);
+    if (err != hipSuccess) {
+      c.broken = true;
+      return err;
+    }
+  }
+  const uint32_t n = c.n.fetch_add(1);
+  a.claim = words + claim_word(n);
+  a.clear = words + claim_clears(n);
+  return hipSuccess;
+}
+
 bool noalloc_tables_valid(const int32_t* src, uint32_t src_count, const int32_t* dst, uint32_t dst_count,
                           uint64_t n) {
   if (n > kNoallocMaxBlocks) return false;
@@ -1062,7 +1098,6 @@ mma_status_t mma_kv_fetch_noalloc(const mma_kv_layout_t* layout, const void* hos
     return s;
   static thread_local PoolArgs a;
   memset(&a, 0, offsetof(PoolArgs, w));
-  a.ctr = reinterpret_cast<uint32_t*>(scratch);
   a.pool = c.pool_cu;
   a.slot_bytes = c.slot_bytes;
   a.piece = c.piece;
@@ -1103,8 +1138,13 @@ mma_status_t mma_kv_fetch_noalloc(const mma_kv_layout_t* layout, const void* hos
   // workgroups of a launch over the link.
   const uint32_t wgs =
       c.pool_dev ? 0 : static_cast<uint32_t>(std::min<uint64_t>((3ull * rt->cfg.cu_wgs + 1) / 2, kMaxWorkgroups));
-  if (!c.pool_dev && link_claims(MMA_H2D, c.kv.layout, n_blocks * c.slot_bytes)) a.claim = a.ctr + kPoolCtrStride;
+  const bool claims = !c.pool_dev && link_claims(MMA_H2D, c.kv.layout, n_blocks * c.slot_bytes);
+  if (claims) {
+    const hipError_t err = noalloc_claims(a, rt->dev, reinterpret_cast<uint32_t*>(scratch), hs);
+    if (err != hipSuccess) return fail(MMA_ERR_HIP, "no-alloc claims launch failed: %s", hipGetErrorString(err));
+  }
   const hipError_t err = launch_noalloc(a, static_cast<uint32_t>(n_blocks), c.kv.layout, wgs, hs);
+  if (err != hipSuccess && claims) g_noalloc_claims[rt->dev].broken = true;
   return err == hipSuccess ? MMA_OK : fail(MMA_ERR_HIP, "no-alloc KV fetch launch failed: %s", hipGetErrorString(err));
 } catch (...) {
   return boundary_error("mma_kv_fetch_noalloc");

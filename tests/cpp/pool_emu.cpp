@@ -6,6 +6,7 @@
 // oracle.
 #include <cstdint>
 #include <cstring>
+#include <random>
 #include <vector>
 
 #include "mma_pool.h"
@@ -90,6 +91,61 @@ extern "C" int emu_finish(const uint32_t* order, uint32_t grid, int claims, uint
     if (!p.empty()) return 2;
   for (uint32_t v : mem)
     if (v) return 3;
+  return 0;
+}
+
+// Launches of fetches without allocations that claim `spans` spans each, after `before` of them:
+// `overlap` at once, their steps interleaved at random, then 40 one after another. 0 if every
+// launch takes every span exactly once; else its number + 1.
+extern "C" int emu_noalloc_claims(uint32_t before, uint32_t overlap, uint32_t waves, uint32_t spans, uint32_t seed) {
+  std::vector<uint32_t> words(kClaimWords, 0);
+  std::mt19937 rng(seed);
+  struct Launch {
+    uint32_t claim, clear;
+    std::vector<uint64_t> at;       // of each wave
+    std::vector<uint8_t> taken;
+    bool cleared = false, once = true;
+  };
+  uint32_t n = 0;
+  const auto run = [&](uint32_t count) {
+    std::vector<Launch> ls(count);
+    for (Launch& l : ls) {
+      l.claim = claim_word(n);
+      l.clear = claim_clears(n++);
+      for (uint32_t w = 0; w < waves; ++w) l.at.push_back(w);
+      l.taken.assign(spans, 0);
+    }
+    std::vector<std::pair<uint32_t, uint32_t>> steps;  // launch, wave (`waves`: its clearing)
+    for (uint32_t i = 0; i < count; ++i)
+      for (uint32_t w = 0; w <= waves; ++w) steps.emplace_back(i, w);
+    while (!steps.empty()) {
+      const size_t k = rng() % steps.size();
+      Launch& l = ls[steps[k].first];
+      const uint32_t w = steps[k].second;
+      bool over = true;
+      if (w == waves) {
+        words[l.clear] = 0;
+      } else if (l.at[w] < spans) {
+        l.once &= !l.taken[l.at[w]]++;
+        l.at[w] = waves + words[l.claim]++;
+        over = false;
+      }
+      if (over) {
+        steps[k] = steps.back();
+        steps.pop_back();
+      }
+    }
+    for (uint32_t i = 0; i < count; ++i) {
+      for (uint8_t t : ls[i].taken) ls[i].once &= t == 1;
+      if (!ls[i].once) return static_cast<int>(n - count + i + 1);
+    }
+    return 0;
+  };
+  for (uint32_t i = 0; i < before; ++i)
+    if (const int rc = run(1)) return rc;
+  if (const int rc = run(overlap)) return rc;
+  for (uint32_t i = 0; i < 40; ++i)
+    if (const int rc = run(1)) return rc;
   return 0;
 }
 

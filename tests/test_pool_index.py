@@ -47,6 +47,9 @@ def emu(tmp_path_factory):
     f.finish = lib.emu_finish
     f.finish.restype = ctypes.c_int
     f.finish.argtypes = [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_int, ctypes.c_uint32]
+    f.claims = lib.emu_noalloc_claims
+    f.claims.restype = ctypes.c_int
+    f.claims.argtypes = [ctypes.c_uint32] * 5
     return f
 
 
@@ -127,8 +130,7 @@ def test_division_by_reciprocal(emu):
 
 
 def test_finish_counters_keep_off_the_claims(emu):
-    """Counter 1 holds the claims of a launch that has them, and nothing after it is the launch's own
-    in a fetch without allocations (its table follows); without claims 64 groups fit the counters."""
+    """Counter 1 holds the claims of a launch that has them; without claims 64 groups fit the counters."""
     for grid in [1, 15, 16, 31, 32, 33, 48, 96, 255, 256, 384]:
         assert emu.last_counter(grid, 1, 64) == 0, grid
     for grid, last in [(1, 0), (31, 0), (32, 2), (1024, 64), (16384, 64)]:
@@ -145,3 +147,13 @@ def test_finish_counters_are_reset_before_the_done_tag(emu, grid):
             order = r.permutation(grid).astype(np.uint32)
             rc = emu.finish(order.ctypes.data, grid, claims, 64)
             assert rc == 0, (grid, claims, rc)
+
+
+@pytest.mark.parametrize("overlap", [1, 2, 16])
+def test_noalloc_claims_after_calls_that_overlap(emu, overlap):
+    """Fetches without allocations share their claim words: calls that overlapped, against the rule,
+    leave none that makes a later call skip or repeat a span."""
+    for seed in range(30):
+        for before in (0, 5, 33):
+            bad = emu.claims(before, overlap, 6, 40, seed)
+            assert bad == 0, (seed, before, bad - 1)

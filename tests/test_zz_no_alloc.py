@@ -63,6 +63,80 @@ def test_noalloc_fetch_matches_kv_fetch(layout):
         pool.free()
 
 
+# 24 blocks of 1 MiB: large enough that the launch's waves claim their spans, its table in the arguments
+CLAIMS = W.KVShape(layers=16, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2,
+                   gpu_num_blocks=28, host_num_slots=26, n_blocks=24)
+
+
+def _claims_inputs():
+    s = CLAIMS
+    assert s.n_blocks * s.slot_bytes >= 16 << 20
+    lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                        s.host_num_slots)
+    pool = mma.PinnedBuffer(s.host_num_slots * s.slot_bytes)
+    pool.array[:] = np.frombuffer(W.rng(18, W.TAG_DATA, 0).bytes(pool.nbytes), dtype=np.uint8)
+    return lay, pool, *_tables(s, s.n_blocks, cfg=30)
+
+
+def _check_claims(pool, layers, hs, gb):
+    s = CLAIMS
+    pv = pool.array.reshape(s.host_num_slots, s.slot_bytes)
+    poison = np.full((2, s.gpu_num_blocks, s.piece_bytes), W.GPU_POISON, np.uint8)
+    for l in range(s.layers):
+        want = okv.kv_fetch_layer(pv, poison, l, s.layers, hs, gb)
+        assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), l
+
+
+def test_noalloc_calls_after_ones_that_overlapped():
+    """Calls on two streams at once share the claim words, which their callers have to prevent; every
+    call ordered after them still moves all of its bytes, more of them than there are words."""
+    with session("both", cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+        lay, pool, hs, gb = _claims_inputs()
+        a, b = torch.cuda.Stream(), torch.cuda.Stream()
+        junk = [device_bytes(CLAIMS.layer_bytes) for _ in range(CLAIMS.layers)]
+        layers = [device_bytes(CLAIMS.layer_bytes) for _ in range(CLAIMS.layers)]
+        torch.cuda.synchronize()
+        log("overlapping no-alloc fetches")
+        for _ in range(4):
+            mma.mma_kv_fetch_noalloc(lay, pool, junk, hs, gb, a)
+            mma.mma_kv_fetch_noalloc(lay, pool, junk, hs, gb, b)
+        torch.cuda.synchronize()
+        for call in range(36):
+            for t in layers:
+                t.fill_(W.GPU_POISON)
+            mma.mma_kv_fetch_noalloc(lay, pool, layers, hs, gb)
+            torch.cuda.synchronize()
+            log(f"no-alloc fetch {call} after them")
+            _check_claims(pool, layers, hs, gb)
+        pool.free()
+
+
+def test_noalloc_fetch_in_a_graph():
+    """A captured fetch whose waves claim spans, replayed with calls of its own kind between."""
+    with session("both", cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+        lay, pool, hs, gb = _claims_inputs()
+        layers = [device_bytes(CLAIMS.layer_bytes) for _ in range(CLAIMS.layers)]
+        other = [device_bytes(CLAIMS.layer_bytes) for _ in range(CLAIMS.layers)]
+        mma.mma_kv_fetch_noalloc(lay, pool, layers, hs, gb)
+        torch.cuda.synchronize()
+        log("capturing a no-alloc fetch")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, capture_error_mode="relaxed"):
+            mma.mma_kv_fetch_noalloc(lay, pool, layers, hs, gb)
+        for replay in range(4):
+            for t in layers + other:
+                t.fill_(W.GPU_POISON)
+            g.replay()
+            for _ in range(replay):
+                mma.mma_kv_fetch_noalloc(lay, pool, other, hs, gb)
+            torch.cuda.synchronize()
+            log(f"replay {replay}")
+            _check_claims(pool, layers, hs, gb)
+            if replay:
+                _check_claims(pool, other, hs, gb)
+        pool.free()
+
+
 def test_noalloc_fetch_limits():
     s = W.KVShape(layers=1, block_tokens=1, kv_heads=1, head_dim=8, elem_bytes=2,
                   gpu_num_blocks=70000, host_num_slots=70000, n_blocks=65537)
