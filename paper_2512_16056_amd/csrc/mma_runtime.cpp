@@ -14,6 +14,7 @@
 #include <new>
 
 #include "mma_engine.h"
+#include "mma_noalloc.h"
 
 namespace mma {
 
@@ -1001,9 +1002,6 @@ std::mutex g_noalloc_mu;
 constexpr uint32_t kNoallocBitmapBits = 1u << 24;
 uint64_t g_noalloc_seen[kNoallocBitmapBits / 64];
 int32_t g_noalloc_sorted[kNoallocMaxBlocks];
-// The table of the call being launched, and room to sort it.
-std::mutex g_noalloc_tab_mu;
-uint64_t g_noalloc_tab[kNoallocMaxBlocks], g_noalloc_tmp[kNoallocMaxBlocks];
 
 // Launches that claimed spans, per device, and whether one of them failed, so that
 // the word it had to clear is not.
@@ -1112,28 +1110,10 @@ mma_status_t mma_kv_fetch_noalloc(const mma_kv_layout_t* layout, const void* hos
   memcpy(a.w, c.kv.layer_ptr, sizeof(uint64_t) * c.kv.layers);
   a.words = a.layers;
   const hipStream_t hs = static_cast<hipStream_t>(stream);
-  std::lock_guard<std::mutex> g(g_noalloc_tab_mu);
-  for (uint64_t i = 0; i < n_blocks; ++i)
-    g_noalloc_tab[i] = static_cast<uint64_t>(static_cast<uint32_t>(host_slots[i])) |
-                       (static_cast<uint64_t>(static_cast<uint32_t>(gpu_blocks[i])) << 32);
-  if (c.pool_dev) sort_table(g_noalloc_tab, n_blocks, 32, g_noalloc_tmp);
-  if (a.layers + n_blocks <= kPoolWords) {
-    memcpy(a.w + a.layers, g_noalloc_tab, n_blocks * sizeof(uint64_t));
-    a.words += static_cast<uint32_t>(n_blocks);
-  } else {
-    // The table goes into the scratch array through kernel arguments, chunk by
-    // chunk, on the caller's stream: no copy call and no staging buffer.
-    a.tab = scratch + kNoallocTabOffset / 8;
-    NoallocTabArgs t;
-    t.scratch = scratch;
-    for (uint64_t first = 0; first < n_blocks; first += kNoallocTabChunk) {
-      t.first = static_cast<uint32_t>(first);
-      t.count = static_cast<uint32_t>(std::min<uint64_t>(kNoallocTabChunk, n_blocks - first));
-      memcpy(t.e, g_noalloc_tab + first, t.count * sizeof(uint64_t));
-      const hipError_t err = launch_noalloc_table(t, hs);
-      if (err != hipSuccess) return fail(MMA_ERR_HIP, "no-alloc table launch failed: %s", hipGetErrorString(err));
-    }
-  }
+  const int terr = noalloc_table(a, scratch, host_slots, gpu_blocks, static_cast<uint32_t>(n_blocks), c.pool_dev,
+                                 [&](const NoallocTabArgs& t) { return static_cast<int>(launch_noalloc_table(t, hs)); });
+  if (terr)
+    return fail(MMA_ERR_HIP, "no-alloc table launch failed: %s", hipGetErrorString(static_cast<hipError_t>(terr)));
   // CU path alone: a pool in HBM as any pool launch, one on the host with the
   // workgroups of a launch over the link.
   const uint32_t wgs =
