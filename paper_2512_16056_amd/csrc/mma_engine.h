@@ -339,6 +339,10 @@ inline void sort_table(uint64_t* v, size_t n, uint32_t shift, uint64_t* tmp) {
   if (from != v) std::copy(from, from + n, v);
 }
 
+// See link_eligible.
+constexpr uint32_t kLinkWgs = 8;
+constexpr uint64_t kLinkFewBytes = 256 * KiB;
+
 // Whether the waves of a launch over the link claim their spans. Below these sizes
 // fixed shares and done tags per workgroup save the counts' round trips. Fixed /
 // claimed: fetch, 8 MiB 158 / 159 us, 16 MiB 312 / 302, 64 MiB 1237 / 1184;
@@ -568,9 +572,22 @@ class Engine {
   //    256 KiB piece 46.3 / 57.4, 47.6 / 55.6; x-packed 34.1 / 57.4, 31.7 / 55.5
   //    512 KiB piece 53.3 / 57.4, 53.4 / 55.6; x-packed 49.7 / 57.4, 45.6 / 55.5
   //    1 MiB   piece 57.0 / 57.4, 56.6 / 55.6; x-packed 56.1 / 57.4, 54.3 / 55.5
-  // The launch has 1.5 times cu_workgroups at most, as the transformed layouts.
-  bool link_eligible(const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
+  // The launch has 1.5 times cu_workgroups at most, as the transformed layouts. With
+  // cu_workgroups below kLinkWgs that does not fill the link, while whole entries get
+  // up to 12 workgroups whatever the limit and the ring has the copy engines. So with
+  // few, the launch takes only what is small (kLinkFewBytes a workgroup), fetches in
+  // blocks so small that the ring is at 7 GB/s, and offloads that entries cannot
+  // carry. cu_workgroups 1, 2, 4, entries or ring / one launch:
+  //    fetch of 10 x-packed blocks of 2 MiB   386 / 1328, 387 / 895, 385 / - us
+  //    of 5 head-major blocks of 384 KiB      46 / 94, 47 / 66, 46 / 43 us
+  //    512 MiB in 256 KiB blocks              16.9 / 10.9, 30.4 / 16.5, 46.8 / 31.7 GB/s
+  //    512 MiB in 64 KiB blocks               4.0 / 10.9, 6.4 / 16.4, 6.7 / 31.0 GB/s
+  bool link_eligible(const Transfer* x, const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
     if (!cu_enabled() || cfg_.static_split || cfg_.whole[dir_] <= 1) return false;
+    if (cfg_.cu_wgs < kLinkWgs && payload_bytes > cfg_.cu_wgs * kLinkFewBytes) {
+      if (payload_bytes <= cfg_.whole[dir_] && whole_kv_per(x) != 0) return false;
+      if (dir_ == MMA_H2D && slot_bytes > 64 * KiB) return false;
+    }
     if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / (dir_ == MMA_H2D ? 2 : 4);
     const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
     return !few_large || payload_bytes > 12 * MiB;

@@ -987,7 +987,7 @@ static mma_status_t kv_common(const mma_kv_layout_t* lay, const void* host_pool,
                                                  c.pool_cu, c.pool_dev, sdma_ok, host_slots, gpu_blocks, n, rt->cfg);
   // A pool in HBM, or a transfer over the link that one launch carries best: a
   // pool launch, if the table finds room (acquire).
-  x->pool_launch = c.pool_dev || rt->eng[dir]->link_eligible(c.kv, n * c.slot_bytes, c.slot_bytes);
+  x->pool_launch = c.pool_dev || rt->eng[dir]->link_eligible(x.get(), c.kv, n * c.slot_bytes, c.slot_bytes);
   if (x->pool_launch && !c.pool_dev) set_pool_table(x.get(), c.pool_cu, host_slots, gpu_blocks, n);
   x->t_api = t_api;
   return submit(std::move(x), n * c.slot_bytes, stream, &c.kv);

@@ -831,6 +831,49 @@ void whole_kv_transfers() {
   std::printf("ok   small KV fetches and offloads taken whole by the CU path; larger ones use every path\n");
 }
 
+// Which KV transfers with a pool on the host are one launch over the link, where both
+// routes were measured (link_eligible).
+struct LinkCase {
+  int dir;
+  uint32_t layout;
+  uint64_t piece;
+  uint32_t layers, blocks, wgs;
+  bool link;
+};
+void link_routes(const char* name, const std::vector<LinkCase>& cases) {
+  for (const LinkCase& k : cases) {
+    Setup s;
+    s.cfg = default_config();
+    s.cfg.chunk = 2 * MiB;
+    s.cfg.whole[MMA_H2D] = 24 * MiB;
+    s.cfg.whole[MMA_D2H] = 8 * MiB;
+    s.cfg.cu_wgs = k.wgs;
+    Harness h(s);
+    KvGeom kv;
+    kv.piece = k.piece;
+    kv.layers = k.layers;
+    kv.layout = k.layout;
+    std::vector<int32_t> hs(k.blocks), gb(k.blocks);
+    for (uint32_t i = 0; i < k.blocks; ++i) hs[i] = gb[i] = static_cast<int32_t>(i);
+    const uint64_t slot = 2 * k.layers * k.piece;
+    const std::unique_ptr<Transfer> x =
+        make_kv_transfer(k.dir, k.piece, 2 * k.layers, 1 << 20, 1 << 20, false, true, hs.data(), gb.data(), k.blocks, h.cfg());
+    CHECK(h.engine(k.dir)->link_eligible(x.get(), kv, k.blocks * slot, slot) == k.link,
+          "%s: dir %d layout %u, %u blocks of %llu KiB in %llu KiB pieces, %u workgroups: expected %d", name, k.dir, k.layout,
+          k.blocks, static_cast<unsigned long long>(slot / KiB), static_cast<unsigned long long>(k.piece / KiB), k.wgs, k.link);
+  }
+  std::printf("ok   route of KV transfers over the link: %s\n", name);
+}
+const uint32_t kP = kKvLayoutPiece, kX = kKvLayoutXPacked, kH = kKvLayoutHnd;
+const std::vector<LinkCase> kFewWorkgroups = {
+    {MMA_H2D, kX, 32 * KiB, 32, 10, 1, false}, {MMA_H2D, kX, 32 * KiB, 32, 10, 16, true},
+    {MMA_H2D, kH, 8 * KiB, 24, 5, 2, false},   {MMA_H2D, kH, 8 * KiB, 24, 5, 16, true},
+    {MMA_D2H, kP, 8 * KiB, 24, 18, 2, false},  {MMA_D2H, kP, 8 * KiB, 24, 18, 16, true},
+    {MMA_H2D, kP, 2 * KiB, 12, 42, 1, false},  {MMA_H2D, kP, 2 * KiB, 12, 3, 1, true},
+    {MMA_H2D, kP, 32 * KiB, 4, 2048, 4, false}, {MMA_H2D, kP, 32 * KiB, 4, 2048, 8, true},
+    {MMA_H2D, kP, 2 * KiB, 16, 8192, 1, true}, {MMA_D2H, kH, 8 * KiB, 24, 53, 2, true},
+};
+
 // KV transfers between a pool in device memory and the paged layers (piece
 // layout) run as pool launches: one launch, table from the arena, no ring and
 // no copy engine. Pieces of 8 KiB + 48 bytes end in a short span. Launches
@@ -1605,6 +1648,7 @@ int main(int argc, char** argv) {
     unlaunched_transfer_drains();
     whole_transfers_on_cu();
     whole_kv_transfers();
+    link_routes("few workgroups", kFewWorkgroups);
     hbm_pool_launches();
     deep_queue_does_not_block();
     submit_failures_rerouted();
