@@ -573,20 +573,25 @@ class Engine {
   //    512 KiB piece 53.3 / 57.4, 53.4 / 55.6; x-packed 49.7 / 57.4, 45.6 / 55.5
   //    1 MiB   piece 57.0 / 57.4, 56.6 / 55.6; x-packed 56.1 / 57.4, 54.3 / 55.5
   // The launch has 1.5 times cu_workgroups at most, as the transformed layouts. With
-  // cu_workgroups below kLinkWgs that does not fill the link, while whole entries get
+  // cu_workgroups below kLinkWgs that may not fill the link, while whole entries get
   // up to 12 workgroups whatever the limit and the ring has the copy engines. So with
-  // few, the launch takes only what is small (kLinkFewBytes a workgroup), fetches in
-  // blocks so small that the ring is at 7 GB/s, and offloads that entries cannot
-  // carry. cu_workgroups 1, 2, 4, entries or ring / one launch:
+  // few, what the entries can carry goes by them unless it is small (kLinkFewBytes a
+  // workgroup), and a fetch in blocks above 64 KiB by the ring where that is faster.
+  // cu_workgroups 1, 2, 4, entries or ring / one launch:
   //    fetch of 10 x-packed blocks of 2 MiB   386 / 1328, 387 / 895, 385 / - us
   //    of 5 head-major blocks of 384 KiB      46 / 94, 47 / 66, 46 / 43 us
-  //    512 MiB in 256 KiB blocks              16.9 / 10.9, 30.4 / 16.5, 46.8 / 31.7 GB/s
+  //    128 MiB in 256 KiB blocks, GB/s: head-major 17.7 / 13.9, 25.0 / 20.7, 36.1 / 38.8 (1 MiB blocks 41.2 /
+  //      36.6, with 6 50.4 / 51.1), x-packed 15.8 / 15.7, 22.6 / 23.3, 33.8 / 43.4 (192 KiB blocks 9.4 / 8.5,
+  //      14.2 / 12.8, 20.5 / 24.8), as on the host 17.2 / 30.9, 30.3 / 43.9, 46.4 / 56.8 (kLinkFewSpan);
+  //      offload 24.3 / 28.0, 34.2 / 41.3, 41.0 / 54.0; 13.1 / 15.4, 19.2 / 22.9, 31.1 / 44.2; 22.9 / 55.2,
+  //      38.9 / 55.2, 49.3 / 55.1
   //    512 MiB in 64 KiB blocks               4.0 / 10.9, 6.4 / 16.4, 6.7 / 31.0 GB/s
   bool link_eligible(const Transfer* x, const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
     if (!cu_enabled() || cfg_.static_split || cfg_.whole[dir_] <= 1) return false;
     if (cfg_.cu_wgs < kLinkWgs && payload_bytes > cfg_.cu_wgs * kLinkFewBytes) {
       if (payload_bytes <= cfg_.whole[dir_] && whole_kv_per(x) != 0) return false;
-      if (dir_ == MMA_H2D && slot_bytes > 64 * KiB) return false;
+      const uint32_t least = kv.layout == kKvLayoutHnd ? 6 : kv.layout == kKvLayoutXPacked ? 3 : 1;
+      if (dir_ == MMA_H2D && slot_bytes > 64 * KiB && cfg_.cu_wgs < least) return false;
     }
     if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / (dir_ == MMA_H2D ? 2 : 4);
     const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;

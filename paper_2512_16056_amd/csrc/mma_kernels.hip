@@ -1145,8 +1145,10 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
                       : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
     p.g.rows = fast_div(1);
     p.g.waves = p.g.total;
-    // A claim's round trip pays for 8 KiB at least.
-    if (p.claim) p.group = static_cast<uint32_t>(std::max<uint64_t>(1, kPoolSpan / p.piece));
+    // A claim's round trip pays for 8 KiB at least; with few waves for more, as they
+    // lose less at the end.
+    if (p.claim)
+      p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / p.piece));
     spans = (p.g.waves + p.group - 1) / p.group;
   } else if (layout == kKvLayoutXPacked) {
     const uint32_t x = 16 / p.elem, hc = p.heads * (p.row_bytes / 16);
@@ -1168,12 +1170,12 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
                                    reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, true, false>),
                                    reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<8, false, true>)}};
     k = xp[p.elem == 1 ? 0 : p.elem == 2 ? 1 : p.elem == 4 ? 2 : 3][wgs ? 1 : stage ? 2 : 0];
-  } else if (aligned) {
+  } else if (aligned && !link_long_spans(wgs, p.piece)) {
     k = !wgs ? reinterpret_cast<const void*>(&mma_kv_pool_kernel<false, true>)
         : p.tab ? reinterpret_cast<const void*>(&mma_kv_link_kernel<false, true>)
                 : reinterpret_cast<const void*>(&mma_kv_link_kernel<false, false>);
   } else {
-    p.span = wgs ? 2 * kPoolSpan : kPoolSpan;
+    p.span = link_few(wgs) ? kLinkFewSpan : wgs ? 2 * kPoolSpan : kPoolSpan;
     const uint64_t per = (p.piece + p.span - 1) / p.span;
     p.g.rows = fast_div(static_cast<uint32_t>(per));
     spans = p.g.waves = per * p.g.total;

@@ -164,6 +164,15 @@ MMA_POOL_HD inline uint32_t hnd_other(const HndMap& m, uint32_t u) {
   return ((row - x * m.Y.d) * m.X + x) * m.C.d + (u - row * m.C.d);
 }
 
+// Over the link with few workgroups each wave needs more in flight than the rows of a
+// span, 8 KiB: pieces of 16 KiB and more, as they are on the host, go by wave_copy, up
+// to kLinkFewSpan at a time. 64 MiB in 32 KiB pieces, 3 and 6 workgroups: by rows 2634
+// and 1710 us, so 1613 and 1192; 16 KiB pieces 1785 and 1194. And x-packed claims are
+// of as much: 64 MiB in 8 KiB pieces, 2 and 3 workgroups, 4973 / 4521 and 3223 / 2866.
+constexpr uint32_t kLinkFewWgs = 12, kLinkFewSpan = 64 * 1024;
+MMA_POOL_HD inline bool link_few(uint32_t wgs) { return wgs && wgs < kLinkFewWgs; }
+MMA_POOL_HD inline bool link_long_spans(uint32_t wgs, uint64_t piece) { return link_few(wgs) && piece >= 16 * 1024; }
+
 // x-packed blocks. A piece is B tokens of HC 16-byte units (x = 16 / element bytes
 // elements each) on the host, [B][HC]. A key block holds the same units as [HC][B],
 // a value block rows of B elements per dimension, [HC * x][B]: so a key lane moves

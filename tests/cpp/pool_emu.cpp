@@ -63,6 +63,8 @@ extern "C" uint32_t emu_last_counter(uint32_t grid, int claims, uint32_t most) {
   return groups > 1 ? groups : 0;
 }
 
+extern "C" int emu_long_spans(uint32_t wgs, uint64_t piece) { return link_long_spans(wgs, piece) ? 1 : 0; }
+
 // Counters whose stores of 0 stay with the workgroup that made them until it waits (or, in the
 // end, until it is over).
 struct EmuCounters {

@@ -870,7 +870,9 @@ const std::vector<LinkCase> kFewWorkgroups = {
     {MMA_H2D, kH, 8 * KiB, 24, 5, 2, false},   {MMA_H2D, kH, 8 * KiB, 24, 5, 16, true},
     {MMA_D2H, kP, 8 * KiB, 24, 18, 2, false},  {MMA_D2H, kP, 8 * KiB, 24, 18, 16, true},
     {MMA_H2D, kP, 2 * KiB, 12, 42, 1, false},  {MMA_H2D, kP, 2 * KiB, 12, 3, 1, true},
-    {MMA_H2D, kP, 32 * KiB, 4, 2048, 4, false}, {MMA_H2D, kP, 32 * KiB, 4, 2048, 8, true},
+    {MMA_H2D, kH, 32 * KiB, 4, 2048, 3, false}, {MMA_H2D, kH, 32 * KiB, 4, 2048, 8, true},
+    {MMA_H2D, kX, 4 * KiB, 24, 700, 2, false}, {MMA_H2D, kX, 4 * KiB, 24, 700, 4, true},
+    {MMA_H2D, kP, 32 * KiB, 4, 2048, 1, true}, {MMA_H2D, kH, 2 * KiB, 16, 8192, 1, true},
     {MMA_H2D, kP, 2 * KiB, 16, 8192, 1, true}, {MMA_D2H, kH, 8 * KiB, 24, 53, 2, true},
 };
 

@@ -684,6 +684,37 @@ def test_kv_link_launch_claims_with_many_workgroups(workgroups, noalloc):
         pool.free()
 
 
+@pytest.mark.parametrize("gpu_layout", [mma.MMA_KV_LAYOUT_PIECE, mma.MMA_KV_LAYOUT_XPACKED])
+@pytest.mark.parametrize("workgroups", [1, 7])
+@pytest.mark.parametrize("kv_heads", [2, 4, 5, 18])  # pieces of 8, 16, 20 and 72 KiB
+def test_kv_link_launch_with_few_workgroups(kv_heads, workgroups, gpu_layout):
+    """Launches over the link with fewer than 12 workgroups, whose spans are up to 64 KiB: below and
+    above the sizes whose waves claim them, without allocations and above the whole-transfer limit."""
+    ol = okv.LAYOUT_PIECE if gpu_layout == mma.MMA_KV_LAYOUT_PIECE else okv.LAYOUT_XPACKED
+    for n in (3, 31):
+        s = W.KVShape(layers=18, block_tokens=16, kv_heads=kv_heads, head_dim=128, elem_bytes=2,
+                      gpu_num_blocks=n + 2, host_num_slots=n + 1, n_blocks=n)
+        lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                            s.host_num_slots, gpu_layout)
+        hs, gb = W.kv_fetch_tables(s, cfg=3)
+        log(f"few workgroups={workgroups} heads={kv_heads} layout={gpu_layout} blocks={n}")
+        with session("both", cu_workgroups=workgroups, cu_whole_bytes=2, cu_whole_bytes_d2h=2):
+            pool = mma.PinnedBuffer(s.host_num_slots * s.slot_bytes)
+            pool.array[:] = np.random.default_rng(61).integers(0, 256, pool.nbytes, dtype=np.uint8)
+            pv = pool.array.reshape(s.host_num_slots, s.slot_bytes)
+            for call in (mma.mma_kv_fetch, mma.mma_kv_fetch_noalloc):
+                layers = _layers(s, W.GPU_POISON)
+                before = _layer_views(s, layers)
+                call(lay, pool, layers, hs, gb)
+                torch.cuda.synchronize()
+                mma.mma_synchronize()
+                for l in range(s.layers):
+                    want = okv.kv_fetch_layer(pv, before[l], l, s.layers, hs, gb, ol, _geom(s))
+                    assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), (call.__name__, l)
+            del pv
+            pool.free()
+
+
 XP_POOL_SHAPES = {
     # pieces below and at the size that goes through LDS, with 8 and 9 MiB and a bit in all
     "small_pieces": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=1300,
