@@ -119,9 +119,9 @@ typedef struct mma_config {
                                setup of several paths costs more than it gains (Section 3.2
                                fallback); default 24 MiB; 1 keeps every transfer on the multipath
                                engine. KV transfers up to this size, and larger ones whose blocks
-                               are at most chunk_bytes / 2 (device->host: chunk_bytes / 4),
-                               likewise take one launch; with cu_workgroups below 8, which do
-                               not fill the link, fewer of them do */
+                               are at most 1 MiB (device->host: 512 KiB), likewise take one
+                               launch; with cu_workgroups below 8, which may not fill the link,
+                               fewer of them do */
   uint32_t cu_whole_bytes_d2h; /* the same for device->host; default 8 MiB (CU stores to host
                                memory reach the link less efficiently than CU loads, measured) */
   uint32_t control;         /* who drives a transfer once it is submitted (Section 6, Current

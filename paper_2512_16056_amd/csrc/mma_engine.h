@@ -565,13 +565,16 @@ class Engine {
   //    83.0, 121.2; but head-major 49.5 / 44.0, x-packed 51.4 / 43.2, one block of
   //    768 KiB 21.2 / 19.4, 8 blocks 318 / 313, 56 blocks of 147 KiB, which are
   //    too many entries, 578 / 155;
-  //  - beyond it, blocks of at most half (offload: a quarter) of a chunk. The
-  //    engine thread's micro-tasks never span blocks, so with small ones the CU
-  //    path's queue holds too little and the copy engines get short commands.
+  //  - beyond it, blocks of at most 1 MiB (offload: 512 KiB). The engine thread's
+  //    micro-tasks never span blocks, so with small ones the CU path's queue holds too
+  //    little and the copy engines get short commands.
   //    512 MiB, ring / one launch, fetch and offload in GB/s, by block:
   //    256 KiB piece 46.3 / 57.4, 47.6 / 55.6; x-packed 34.1 / 57.4, 31.7 / 55.5
   //    512 KiB piece 53.3 / 57.4, 53.4 / 55.6; x-packed 49.7 / 57.4, 45.6 / 55.5
   //    1 MiB   piece 57.0 / 57.4, 56.6 / 55.6; x-packed 56.1 / 57.4, 54.3 / 55.5
+  //    The block decides, not chunk_bytes: with 512 KiB to 8 MiB of it the ring moves
+  //    256 KiB blocks at 46.0 to 46.3 GB/s and 512 KiB ones at 53.1 to 53.3, and with
+  //    8 MiB 2 MiB blocks at 57.0 (launch 57.4) and, offloading, 56.8 (launch 55.3).
   // The launch has 1.5 times cu_workgroups at most, as the transformed layouts. With
   // cu_workgroups below kLinkWgs that may not fill the link, while whole entries get
   // up to 12 workgroups whatever the limit and the ring has the copy engines. So with
@@ -593,7 +596,7 @@ class Engine {
       const uint32_t least = kv.layout == kKvLayoutHnd ? 6 : kv.layout == kKvLayoutXPacked ? 3 : 1;
       if (dir_ == MMA_H2D && slot_bytes > 64 * KiB && cfg_.cu_wgs < least) return false;
     }
-    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= cfg_.chunk / (dir_ == MMA_H2D ? 2 : 4);
+    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= (dir_ == MMA_H2D ? MiB : 512 * KiB);
     const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
     return !few_large || payload_bytes > 12 * MiB;
   }

@@ -839,12 +839,13 @@ struct LinkCase {
   uint64_t piece;
   uint32_t layers, blocks, wgs;
   bool link;
+  uint64_t chunk = 2 * MiB;
 };
 void link_routes(const char* name, const std::vector<LinkCase>& cases) {
   for (const LinkCase& k : cases) {
     Setup s;
     s.cfg = default_config();
-    s.cfg.chunk = 2 * MiB;
+    s.cfg.chunk = k.chunk;
     s.cfg.whole[MMA_H2D] = 24 * MiB;
     s.cfg.whole[MMA_D2H] = 8 * MiB;
     s.cfg.cu_wgs = k.wgs;
@@ -874,6 +875,12 @@ const std::vector<LinkCase> kFewWorkgroups = {
     {MMA_H2D, kX, 4 * KiB, 24, 700, 2, false}, {MMA_H2D, kX, 4 * KiB, 24, 700, 4, true},
     {MMA_H2D, kP, 32 * KiB, 4, 2048, 1, true}, {MMA_H2D, kH, 2 * KiB, 16, 8192, 1, true},
     {MMA_H2D, kP, 2 * KiB, 16, 8192, 1, true}, {MMA_D2H, kH, 8 * KiB, 24, 53, 2, true},
+};
+const std::vector<LinkCase> kChunks = {
+    {MMA_H2D, kP, 32 * KiB, 32, 256, 16, false, 8 * MiB}, {MMA_H2D, kP, 32 * KiB, 16, 512, 16, true, 8 * MiB},
+    {MMA_D2H, kP, 32 * KiB, 16, 512, 16, false, 8 * MiB}, {MMA_D2H, kP, 32 * KiB, 8, 1024, 16, true, 8 * MiB},
+    {MMA_H2D, kP, 32 * KiB, 16, 512, 16, true, 512 * KiB}, {MMA_D2H, kX, 32 * KiB, 4, 2048, 16, true, 512 * KiB},
+    {MMA_H2D, kP, 32 * KiB, 32, 256, 16, false},          {MMA_D2H, kP, 32 * KiB, 16, 512, 16, false},
 };
 
 // KV transfers between a pool in device memory and the paged layers (piece
@@ -1651,6 +1658,7 @@ int main(int argc, char** argv) {
     whole_transfers_on_cu();
     whole_kv_transfers();
     link_routes("few workgroups", kFewWorkgroups);
+    link_routes("chunk sizes", kChunks);
     hbm_pool_launches();
     deep_queue_does_not_block();
     submit_failures_rerouted();
