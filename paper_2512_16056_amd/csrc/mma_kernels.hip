@@ -719,20 +719,8 @@ __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   st_sys(a.done, make_tag(a.seq, 0));
 }
 
-// The spans of one wave of a launch with fewer waves than spans: its own first,
-// then every nw-th, or, with a claim counter, the next one nobody has taken. Over
-// the link the waves' shares of it differ, and with fixed shares the slow ones
-// leave it idle at the end: x-packed fetches 53.5 GB/s, with claims 57.
-struct SpanWalk {
-  uint64_t at, nw;
-  uint32_t got;
-};
-// Over the link few spans go to as many workgroups as there are; in HBM a
-// workgroup's are neighbours.
 __device__ __forceinline__ SpanWalk span_walk(const PoolArgs& a, uint32_t wave) {
-  return SpanWalk{a.link ? static_cast<uint64_t>(wave) * gridDim.x + blockIdx.x
-                         : static_cast<uint64_t>(blockIdx.x) * kWavesPerWG + wave,
-                  static_cast<uint64_t>(gridDim.x) * kWavesPerWG, 0};
+  return span_walk(blockIdx.x, gridDim.x, wave, kWavesPerWG, a.link != 0);
 }
 // Before the span's own reads, so that the claim's round trip overlaps theirs.
 __device__ __forceinline__ void span_claim(const PoolArgs& a, SpanWalk& s, uint32_t lane) {
@@ -740,10 +728,8 @@ __device__ __forceinline__ void span_claim(const PoolArgs& a, SpanWalk& s, uint3
     s.got = __hip_atomic_fetch_add(a.claim, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void span_next(const PoolArgs& a, SpanWalk& s) {
-  s.at = a.claim ? s.nw + __builtin_amdgcn_readfirstlane(s.got) : s.at + s.nw;
+  span_next(s, a.claim != nullptr, a.claim ? __builtin_amdgcn_readfirstlane(s.got) : 0);
 }
-
-constexpr uint32_t kLinkRows = 8;  // rows per span of a launch over the link, and of staged x-packed keys
 
 // Aligned pieces in the piece layout or (kHnd) head-major: one 16-byte unit per
 // lane. What hides the latency is the 32 waves a CU holds (the kernel takes few
@@ -855,11 +841,11 @@ __device__ __forceinline__ void transpose_units(u32x4 (&v)[16 / E]) {
 // elements -, 572, 459.
 template <uint32_t E, bool kLink, bool kStage>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_xp_kernel(PoolArgs a) {
-  constexpr uint32_t X = 16 / E, K = kLink || kStage ? kLinkRows : 1;
+  constexpr uint32_t X = 16 / E, K = xp_key_rows(kLink, kStage);
   __shared__ u32x4 s_tile[kStage ? kWavesPerWG * kWave * X : 1];
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint64_t keys = (a.g.waves + K - 1) / K;
+  const uint64_t keys = span_count(a.g.waves, K);
   for (SpanWalk s = span_walk(a, wave); s.at < keys + a.gv.waves; span_next(a, s)) {
     span_claim(a, s, lane);
     if (s.at < keys) {
@@ -1122,13 +1108,13 @@ constexpr uint64_t kPoolTagLaunch = 16384;
 // launch over the link, 0 for a pool in HBM.
 hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool aligned, uint32_t wgs,
                               hipStream_t stream, bool* begun) {
-  const uint32_t by_piece = wgs ? 0 : p.to_paged, rows = wgs ? kLinkRows : 1;
+  const uint32_t by_piece = wgs ? 0 : p.to_paged;
   uint32_t lds = 0;
   p.link = wgs ? 1 : 0;
   p.group = 1;
   p.g = pool_geom(n, 2 * p.layers, p.piece >> 4, by_piece);
   const void* k = nullptr;
-  uint64_t spans = (p.g.waves + rows - 1) / rows;  // of one wave each
+  uint64_t spans = span_count(p.g.waves, wgs ? kLinkRows : 1);  // of one wave each
   const bool stage = !wgs && layout == kKvLayoutXPacked && xp_stages(p.piece, p.tokens, p.elem);
   if (layout == kKvLayoutHnd) {
     const bool heads_first = !wgs && p.to_paged;
@@ -1149,14 +1135,13 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
     // lose less at the end.
     if (p.claim)
       p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / p.piece));
-    spans = (p.g.waves + p.group - 1) / p.group;
+    spans = span_count(p.g.waves, p.group);
   } else if (layout == kKvLayoutXPacked) {
     const uint32_t x = 16 / p.elem, hc = p.heads * (p.row_bytes / 16);
     p.xp = xp_map(p.tokens, hc, x);
     p.g = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * p.tokens, by_piece);
     p.gv = pool_geom(n, p.layers, static_cast<uint64_t>(hc) * (p.tokens / x), by_piece);
-    const uint32_t key_rows = stage ? kLinkRows : rows;
-    spans = (p.g.waves + key_rows - 1) / key_rows + p.gv.waves;
+    spans = span_count(p.g.waves, xp_key_rows(wgs != 0, stage)) + p.gv.waves;
     const void* const xp[4][3] = {{reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false, false>),
                                    reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, true, false>),
                                    reinterpret_cast<const void*>(&mma_kv_pool_xp_kernel<1, false, true>)},
@@ -1181,8 +1166,7 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
     spans = p.g.waves = per * p.g.total;
     k = reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<0>);
   }
-  // A launch has fewer than 2^32 threads; beyond that the waves go round again.
-  const uint64_t grid = std::min<uint64_t>((spans + kWavesPerWG - 1) / kWavesPerWG, wgs ? wgs : 1u << 23);
+  const uint64_t grid = pool_grid(spans, kWavesPerWG, wgs);
   uint64_t* const done = p.done;
   if (grid > kPoolTagLaunch) p.done = nullptr;
   void* params[] = {&p};

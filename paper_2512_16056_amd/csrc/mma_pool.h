@@ -77,6 +77,36 @@ MMA_POOL_HD inline PoolGeom pool_geom(uint32_t n, uint32_t ppb, uint64_t units, 
   return g;
 }
 
+// The spans of one wave of a launch with fewer waves than spans: its own first,
+// then every nw-th, or, with a claim counter, the next one nobody has taken (got:
+// what the counter held). Over the link the waves' shares of it differ, and with
+// fixed shares the slow ones leave it idle at the end: x-packed fetches 53.5 GB/s,
+// with claims 57. There few spans go to as many workgroups as there are; in HBM a
+// workgroup's are neighbours.
+struct SpanWalk {
+  uint64_t at, nw;
+  uint32_t got;
+};
+MMA_POOL_HD inline SpanWalk span_walk(uint32_t wg, uint32_t grid, uint32_t wave, uint32_t waves_per_wg, bool link) {
+  return SpanWalk{link ? static_cast<uint64_t>(wave) * grid + wg : static_cast<uint64_t>(wg) * waves_per_wg + wave,
+                  static_cast<uint64_t>(grid) * waves_per_wg, 0};
+}
+MMA_POOL_HD inline void span_next(SpanWalk& s, bool claims, uint32_t got) { s.at = claims ? s.nw + got : s.at + s.nw; }
+
+// Rows per span of a launch over the link, and of staged x-packed keys; spans of so
+// many rows; x-packed keys' rows per span, whose spans come before the values', of one
+// row each.
+constexpr uint32_t kLinkRows = 8;
+MMA_POOL_HD inline uint64_t span_count(uint64_t rows, uint32_t per) { return (rows + per - 1) / per; }
+MMA_POOL_HD constexpr uint32_t xp_key_rows(bool link, bool stage) { return link || stage ? kLinkRows : 1; }
+
+// Workgroups of a launch; most: over the link, else 0. A launch has fewer than 2^32
+// threads; beyond that the waves go round again.
+MMA_POOL_HD inline uint64_t pool_grid(uint64_t spans, uint32_t waves_per_wg, uint32_t most) {
+  const uint64_t grid = (spans + waves_per_wg - 1) / waves_per_wg, limit = most ? most : 1u << 23;
+  return grid < limit ? grid : limit;
+}
+
 // Groups in which the workgroups of a launch count when they finish, at least 16
 // to a group. A launch whose waves claim spans counts in one, whatever its grid:
 // its claim counter stands where the first group's counter would. Its workgroups

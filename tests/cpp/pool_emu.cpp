@@ -1,5 +1,5 @@
-// CPU emulation of a pool launch, in HBM (link = 0) or over the link, over the kernel's own index maps
-// (paper_2512_16056_amd/csrc/mma_pool.h): every wave, row and lane,
+// CPU emulation of a pool launch, in HBM (link = 0) or over the link by at most `link` workgroups, over
+// the kernel's own walk and index maps (paper_2512_16056_amd/csrc/mma_pool.h): every wave, span, row and lane,
 // in the piece layout (hnd = 0) or the head-major one. Every access is checked
 // against its buffer, and every byte of the destination pieces must be written
 // exactly once. Built by tests/test_pool_index.py and compared there with the
@@ -13,17 +13,42 @@
 
 using namespace mma;
 
+// The spans that the waves of a launch take, in the order they take them: the waves run in turn, one
+// span each, with the claims (if any) on one counter.
+static std::vector<uint64_t> walk(uint64_t spans, uint32_t wgs, bool claims) {
+  const uint32_t waves = 4, grid = static_cast<uint32_t>(pool_grid(spans, waves, wgs));
+  std::vector<SpanWalk> s;
+  for (uint32_t g = 0; g < grid; ++g)
+    for (uint32_t w = 0; w < waves; ++w) s.push_back(span_walk(g, grid, w, waves, wgs != 0));
+  std::vector<uint64_t> taken;
+  uint32_t counter = 0;
+  for (bool any = true; any;) {
+    any = false;
+    for (SpanWalk& x : s)
+      if (x.at < spans) {
+        taken.push_back(x.at);
+        span_next(x, claims, claims ? counter++ : 0);
+        any = true;
+      }
+  }
+  return taken;
+}
+
 // pool: slots of ppb pieces; cache: [layers][2][nb][piece]; tab: slot | block << 32.
 extern "C" int emu_pool(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes, const uint64_t* tab,
                         uint32_t n, uint32_t ppb, uint64_t piece, uint32_t nb, int to_paged, int hnd, int link,
-                        uint32_t B, uint32_t H, uint32_t R) {
+                        int claims, uint32_t B, uint32_t H, uint32_t R) {
   const PoolGeom g = pool_geom(n, ppb, piece >> 4, to_paged && !link ? 1 : 0);
   const HndMap m = to_paged && !link ? hnd_map(H, B, R / 16) : hnd_map(B, H, R / 16);
   std::vector<uint8_t> wrote(to_paged ? cache_bytes : pool_bytes, 0);
   const uint8_t* src = to_paged ? pool : cache;
   uint8_t* dst = to_paged ? cache : pool;
   const uint64_t src_bytes = to_paged ? pool_bytes : cache_bytes, dst_bytes = to_paged ? cache_bytes : pool_bytes;
-  for (uint64_t w = 0; w < g.waves; ++w) {
+  const uint32_t per = link ? kLinkRows : 1;
+  std::vector<uint64_t> rows;  // link: workgroups at most
+  for (uint64_t s : walk(span_count(g.waves, per), static_cast<uint32_t>(link), claims != 0))
+    for (uint64_t w = s * per; w < (s + 1) * per && w < g.waves; ++w) rows.push_back(w);
+  for (uint64_t w : rows) {
     for (uint32_t lane = 0; lane < 64; ++lane) {
       const PoolUnit x = pool_unit(g, static_cast<uint32_t>(w), lane);
       if (!x.ok) continue;
@@ -183,7 +208,7 @@ static int stage_row(const XpMap& m, const PoolGeom& g, uint64_t w) {
 // the same maps. E: element bytes; HC: 16-byte units per token.
 extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, uint64_t cache_bytes,
                            const uint64_t* tab, uint32_t n, uint32_t layers, uint64_t piece, uint32_t nb, int to_paged,
-                           int link, uint32_t B, uint32_t HC, uint32_t E) {
+                           int link, int claims, uint32_t B, uint32_t HC, uint32_t E) {
   const uint32_t X = 16 / E, ppb = 2 * layers, by_piece = to_paged && !link ? 1 : 0;
   const XpMap m = xp_map(B, HC, X);
   const PoolGeom geom[2] = {pool_geom(n, layers, static_cast<uint64_t>(HC) * B, by_piece),
@@ -201,9 +226,17 @@ extern "C" int emu_pool_xp(uint8_t* pool, uint64_t pool_bytes, uint8_t* cache, u
       if (rc) return rc;
     }
   }
+  // keys in spans of rows, then a row of values each
+  const uint32_t per = xp_key_rows(link != 0, !link && xp_stages(piece, B, E));
+  const uint64_t keys = span_count(geom[0].waves, per);
+  std::vector<uint64_t> rows[2];
+  for (uint64_t s : walk(keys + geom[1].waves, static_cast<uint32_t>(link), claims != 0)) {
+    if (s >= keys) rows[1].push_back(s - keys);
+    for (uint64_t w = s * per; s < keys && w < (s + 1) * per && w < geom[0].waves; ++w) rows[0].push_back(w);
+  }
   for (uint32_t kind = 0; kind < 2; ++kind) {
     const PoolGeom& g = geom[kind];
-    for (uint64_t w = 0; w < g.waves; ++w)
+    for (uint64_t w : rows[kind])
       for (uint32_t lane = 0; lane < 64; ++lane) {
         const PoolUnit x = pool_unit(g, static_cast<uint32_t>(w), lane);
         if (!x.ok) continue;

@@ -684,6 +684,55 @@ def test_kv_link_launch_claims_with_many_workgroups(workgroups, noalloc):
         pool.free()
 
 
+CLAIM_SHAPES = {
+    # 130 MiB in blocks of 512 KiB: the offload claims, too
+    "piece": (W.KVShape(layers=8, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2, gpu_num_blocks=266,
+                        host_num_slots=264, n_blocks=260), mma.MMA_KV_LAYOUT_PIECE),
+    "hnd": (W.KVShape(layers=8, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2, gpu_num_blocks=266,
+                      host_num_slots=264, n_blocks=260), mma.MMA_KV_LAYOUT_HND),
+    # 17.8 MiB of 2 KiB pieces, through registers: keys and values in one walk
+    "xpacked": (W.KVShape(layers=24, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=200,
+                          host_num_slots=195, n_blocks=190), mma.MMA_KV_LAYOUT_XPACKED),
+}
+
+
+@pytest.mark.parametrize("shape", list(CLAIM_SHAPES))
+def test_kv_link_launch_claims_in_both_directions(shape):
+    """Fetches and offloads over the link large enough that their waves claim spans, twice each. An
+    offload's bytes are in host memory once mma_synchronize has seen its one done tag."""
+    s, layout = CLAIM_SHAPES[shape]
+    total = s.n_blocks * s.slot_bytes
+    assert total >= (16 << 20 if layout == mma.MMA_KV_LAYOUT_XPACKED else 128 << 20)
+    ol = {mma.MMA_KV_LAYOUT_PIECE: okv.LAYOUT_PIECE, mma.MMA_KV_LAYOUT_HND: okv.LAYOUT_HND,
+          mma.MMA_KV_LAYOUT_XPACKED: okv.LAYOUT_XPACKED}[layout]
+    lay = mma.kv_layout(s.layers, s.block_tokens, s.kv_heads, s.head_dim, s.elem_bytes, s.gpu_num_blocks,
+                        s.host_num_slots, layout)
+    hs, gb = W.kv_fetch_tables(s, cfg=3)
+    with session("both", cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+        pool = mma.PinnedBuffer(s.host_num_slots * s.slot_bytes)
+        pv = pool.array.reshape(s.host_num_slots, s.slot_bytes)
+        for turn in range(2):
+            log(f"claims {shape} turn {turn}")
+            pool.array[:] = np.frombuffer(W.rng(71 + turn, W.TAG_DATA, 0).bytes(pool.nbytes), np.uint8)
+            layers = _layers(s, W.GPU_POISON)
+            before = _layer_views(s, layers)
+            mma.mma_kv_fetch(lay, pool, layers, hs, gb)
+            torch.cuda.synchronize()
+            for l in range(s.layers):
+                want = okv.kv_fetch_layer(pv, before[l], l, s.layers, hs, gb, ol, _geom(s))
+                assert np.array_equal(to_host(layers[l]).reshape(want.shape), want), l
+            src = _layers(s, seed=900 + turn)
+            dest = np.roll(hs, 1).astype(np.int32)
+            want = okv.kv_offload(pv.copy(), _layer_views(s, src), gb, dest, ol, _geom(s))
+            mma.mma_kv_offload(lay, pool, src, gb, dest)
+            mma.mma_synchronize()
+            assert np.array_equal(pv, want)
+        st = mma.mma_get_stats()
+        assert sum(st["path_bytes"][:16]) == 0 and st["transfers"] == 4 and st["failed_transfers"] == 0
+        del pv
+        pool.free()
+
+
 @pytest.mark.parametrize("gpu_layout", [mma.MMA_KV_LAYOUT_PIECE, mma.MMA_KV_LAYOUT_XPACKED])
 @pytest.mark.parametrize("workgroups", [1, 7])
 @pytest.mark.parametrize("kv_heads", [2, 4, 5, 18])  # pieces of 8, 16, 20 and 72 KiB

@@ -1,8 +1,8 @@
 """How a pool launch, in HBM or over the link, splits its pieces over waves, emulated on the CPU (no GPU).
 
-tests/cpp/pool_emu.cpp runs every lane of a launch over the kernel's own index maps
-(mma_pool.h) and checks bounds and that each destination byte is written exactly once;
-the result is compared here with the oracle, in the piece and head-major layouts and both
+tests/cpp/pool_emu.cpp runs every wave and lane of a launch over the kernel's own walk and index maps
+(mma_pool.h), with fixed shares and with claims, and checks bounds and that each destination byte is written
+exactly once; the result is compared here with the oracle, in the piece and head-major layouts and both
 directions.
 """
 import ctypes
@@ -33,11 +33,11 @@ def emu(tmp_path_factory):
     f = lib.emu_pool
     f.restype = ctypes.c_int
     f.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
-                  ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 3 + [ctypes.c_uint32] * 3)
+                  ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 4 + [ctypes.c_uint32] * 3)
     f.xp = lib.emu_pool_xp
     f.xp.restype = ctypes.c_int
     f.xp.argtypes = ([ctypes.c_void_p, ctypes.c_uint64] * 2 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint32,
-                     ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 2 + [ctypes.c_uint32] * 3)
+                     ctypes.c_uint64, ctypes.c_uint32] + [ctypes.c_int] * 3 + [ctypes.c_uint32] * 3)
     f.div = lib.emu_div
     f.div.restype = ctypes.c_uint64
     f.div.argtypes = [ctypes.c_uint32] * 3
@@ -63,10 +63,11 @@ SHAPES = [(1, 1, 16, 1, 5), (3, 1, 80, 2, 7), (16, 1, 64, 3, 9), (11, 3, 16, 1, 
           (7, 3, 1040, 1, 3), (16, 2, 2048, 1, 2)]
 
 
-@pytest.mark.parametrize("link", [0, 1])
+# workgroups over the link (0: in HBM) and whether their waves claim spans
+@pytest.mark.parametrize("link,claims", [(0, 0), (1, 0), (2, 1), (24, 0), (24, 1)])
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("layout", [okv.LAYOUT_PIECE, okv.LAYOUT_HND])
-def test_pool_index_maps_match_oracle(emu, shape, layout, link):
+def test_pool_index_maps_match_oracle(emu, shape, layout, link, claims):
     B, H, R, L, n = shape
     piece, ppb, nb, slots = B * H * R, 2 * L, n + 3, n + 2
     geom = (B, H, R, 1)
@@ -79,7 +80,7 @@ def test_pool_index_maps_match_oracle(emu, shape, layout, link):
 
     def run(p, c, to_paged):
         rc = emu(p.ctypes.data, p.nbytes, c.ctypes.data, c.nbytes, tab.ctypes.data, n, ppb, piece, nb, to_paged,
-                 int(layout == okv.LAYOUT_HND), link, B, H, R)
+                 int(layout == okv.LAYOUT_HND), link, claims, B, H, R)
         assert rc == 0, rc
 
     got = cache.copy()
@@ -98,9 +99,10 @@ XP_SHAPES = [(16, 8, 128, 2, 2, 4), (16, 1, 64, 2, 3, 9), (16, 5, 80, 2, 1, 3), 
              (32, 8, 80, 1, 1, 3), (16, 8, 64, 4, 1, 2), (2, 5, 128, 8, 1, 2), (128, 2, 64, 2, 1, 2)]
 
 
-@pytest.mark.parametrize("link", [0, 1])
+# workgroups over the link (0: in HBM) and whether their waves claim spans
+@pytest.mark.parametrize("link,claims", [(0, 0), (1, 0), (2, 1), (24, 0), (24, 1)])
 @pytest.mark.parametrize("shape", XP_SHAPES)
-def test_pool_xpacked_maps_match_oracle(emu, shape, link):
+def test_pool_xpacked_maps_match_oracle(emu, shape, link, claims):
     B, H, D, E, L, n = shape
     piece, nb, slots, geom = B * H * D * E, n + 3, n + 2, (B, H, D, E)
     r = np.random.default_rng(B * 31 + H + D)
@@ -112,7 +114,7 @@ def test_pool_xpacked_maps_match_oracle(emu, shape, link):
 
     def run(p, c, to_paged):
         rc = emu.xp(p.ctypes.data, p.nbytes, c.ctypes.data, c.nbytes, tab.ctypes.data, n, L, piece, nb, to_paged, link,
-                    B, H * D * E // 16, E)
+                    claims, B, H * D * E // 16, E)
         assert rc == 0, rc
 
     got = cache.copy()
