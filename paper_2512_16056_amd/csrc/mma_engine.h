@@ -834,10 +834,8 @@ class Engine {
     return grid;
   }
 
-  // A pool launch: the table goes to the arena and the kernel is the
-  // transfer's only copy engine. Returns a grid for the spans counted here (at
-  // least one per wave, at most kPoolMaxWorkgroups workgroups); the launch sizes
-  // its own (mma_pool.h).
+  // A pool launch: the table goes to the arena and the kernel is the transfer's only
+  // copy engine. The launch sizes its own grid (mma_pool.h); returns 1.
   uint32_t prepare_pool(Transfer* x, const KvGeom* kv, KernelArgs& a) {
     const uint64_t nblk = x->pool_pairs.size();
     // In HBM the kernel takes the pieces in the order of their destinations (mma_pool.h).
@@ -853,13 +851,8 @@ class Engine {
     x->whole = x->self_contained = true;
     x->started = x->closed = x->completed = true;
     x->t_started = x->t_complete = x->t_submit;
-    const uint64_t spans = kv->layout == kKvLayoutHnd ? 1 : (kv->piece + kPoolSpan - 1) / kPoolSpan;
-    const uint64_t units = nblk * 2 * kv->layers * spans;
-    uint64_t grid = std::min<uint64_t>(kPoolMaxWorkgroups, (units + kWavesPerWG - 1) / kWavesPerWG);
-    const uint64_t per_wg = (units + grid - 1) / grid;
-    grid = (units + per_wg - 1) / per_wg;
-    x->waves = static_cast<uint32_t>(grid) * kWavesPerWG;
-    fill_args(x, kv, 0, static_cast<uint32_t>(grid), 0, a);
+    x->waves = kWavesPerWG;
+    fill_args(x, kv, 0, 1, 0, a);
     a.self_contained = 1;
     const uint64_t tab = static_cast<uint64_t>(x->tab_seg) * kPoolTabSeg;
     a.pool_tab = pool_tab_dev_ + tab;
@@ -874,11 +867,8 @@ class Engine {
     }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;
-    a.pool_units = units;
-    a.pool_per_wg = per_wg;
-    a.pool_spans = static_cast<uint32_t>(spans);
     a.pool_to_paged = x->kind == Kind::kKvFetch ? 1u : 0u;
-    return static_cast<uint32_t>(grid);
+    return 1;
   }
 
   // Kernel arguments common to both control modes.

@@ -1099,10 +1099,6 @@ bool xp_registers(const PoolArgs& p, uint32_t n, bool link) {
   return bytes < (16ull << 20) && p.tokens % 8 == 0 && p.heads * (p.row_bytes / 16) % 8 == 0;
 }
 
-// Above this many workgroups (64 MiB at 4 KiB each) counting them costs more than a
-// second launch: 1 GiB 371 / 354 us, 4 GiB 1498 / 1438.
-constexpr uint64_t kPoolTagLaunch = 16384;
-
 // One launch of the kernel that the pool's place, the layout and the alignment
 // ask for. p holds everything but the geometry; wgs: the most workgroups of a
 // launch over the link, 0 for a pool in HBM.

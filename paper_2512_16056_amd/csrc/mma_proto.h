@@ -43,10 +43,8 @@ constexpr uint32_t kBlock = kWave * kWavesPerWG;
 // per wave, about 80 ns each one after the other: 1.30 ms for 64 blocks of 2 MiB
 // that HBM moves in 45 us.
 // kPoolSpan: bytes a wave moves at a time in HBM where it cannot move 16-byte
-// units (twice that over the link), and the unit in the engine's own count of a
-// launch's work.
+// units (over the link more: launch_pool_kernel).
 constexpr uint32_t kPoolSpan = 8 * 1024;
-constexpr uint32_t kPoolMaxWorkgroups = 8192;
 constexpr uint32_t kPoolWords = 448;      // 3.9 KiB of arguments in all
 // Counters of a pool launch, kPoolCtrStride words apart: [1 + i] counts the
 // finished workgroups of group i, [0] the finished groups (one group: its
@@ -156,8 +154,10 @@ struct KernelArgs {
   uint32_t kv_layout;
   uint32_t kv_tokens, kv_heads, kv_row_bytes, kv_elem;
   uint32_t kv_lds_wave;     // kKvLayoutXPacked: dynamic LDS bytes per wave (the launch asks for 4x)
-  // HBM pool launch (pool_tab non-null): the whole transfer is one launch of
-  // mma_kv_pool_kernel, converted from these arguments (see PoolArgs).
+  // Pool launch (pool_tab non-null): one launch of a kernel of its own carries the
+  // whole transfer, with arguments made from these (PoolArgs; launch_pool_kernel picks
+  // the kernel). A launch before it brings a table that does not fit them to device
+  // memory, and one after it writes the done tag of a launch of many workgroups.
   const uint64_t* pool_tab;  // per block: pool slot | GPU block << 32 (device-visible host memory)
   const uint64_t* pool_tab_host;  // the same, host address
   uint64_t* pool_tab_copy;   // room for it in device memory
@@ -167,9 +167,6 @@ struct KernelArgs {
   uint32_t pool_claim;       // 1: its waves claim their spans (else fixed shares and a done tag per workgroup)
   uint32_t* pool_ctr;        // device counters of finished workgroups, 0 between launches
   uint64_t pool_base;        // device address of the pool
-  uint64_t pool_units;       // spans in the transfer
-  uint64_t pool_per_wg;      // spans per workgroup
-  uint32_t pool_spans;       // spans per piece
   uint32_t pool_to_paged;    // 1: pool -> layers (fetch); 0: layers -> pool (offload)
   uint64_t layer_ptr[kMaxLayers];
   uint64_t pre[kPrefill][3];  // words a, b, count|kind_p0 of the first ring entries

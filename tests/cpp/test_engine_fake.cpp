@@ -280,42 +280,80 @@ void copy_at_rate(void* dst, const void* src, uint64_t n, double wave_rate) {
   std::memcpy(dst, src, n);
 }
 
-// The HBM pool kernel: workgroup g moves spans [g * per_wg, (g + 1) * per_wg)
-// from the table entries, then counts itself done; the last one resets the
-// counter and writes the done tag.
-void pool_workgroup(const KernelArgs& a, uint32_t g, uint32_t grid) {
-  const uint64_t per_blk = 2ull * a.kv_layers * a.pool_spans;
-  const uint64_t slot_bytes = 2ull * a.kv_layers * a.kv_piece_bytes;
-  const uint64_t u0 = static_cast<uint64_t>(g) * a.pool_per_wg;
-  const uint64_t u1 = std::min(a.pool_units, u0 + a.pool_per_wg);
-  for (uint64_t u = u0; u < u1; ++u) {
-    const uint64_t i = u / per_blk, r = u % per_blk;
-    const uint64_t p = r / a.pool_spans, off = (r % a.pool_spans) * kPoolSpan;
-    const uint64_t e = aload(&a.pool_tab[i]);
-    const uint64_t n = std::min<uint64_t>(kPoolSpan, a.kv_piece_bytes - off);
-    uint8_t* pooled = reinterpret_cast<uint8_t*>(a.pool_base + (e & 0xffffffffull) * slot_bytes + p * a.kv_piece_bytes + off);
-    uint8_t* paged = reinterpret_cast<uint8_t*>(a.layer_ptr[p >> 1] + (p & 1u) * a.kv_kstride + (e >> 32) * a.kv_piece_bytes + off);
+// A pool launch of aligned pieces in the piece layout, as the runtime makes it of its
+// arguments: the table in them or in its copy in device memory, the split of mma_pool.h,
+// and a done tag per workgroup, or one by the workgroup that counts itself last or by a
+// launch after it.
+struct FakePool {
+  KernelArgs a;
+  std::vector<uint64_t> tab;  // as the arguments carry it
+  bool copied;                // it does not fit them
+  PoolGeom g;
+  uint32_t grid;
+};
+struct FakeCounters {
+  uint32_t* c;
+  uint32_t add(uint32_t i) const { return __atomic_fetch_add(c + i * kPoolCtrStride, 1u, __ATOMIC_ACQ_REL); }
+  void zero(uint32_t i) const { __atomic_store_n(c + i * kPoolCtrStride, 0u, __ATOMIC_RELEASE); }
+  void landed() const {}
+};
+void pool_row(const FakePool& p, uint32_t w) {
+  const KernelArgs& a = p.a;
+  const uint64_t piece = a.kv_piece_bytes, slot_bytes = 2ull * a.kv_layers * piece;
+  for (uint32_t lane = 0; lane < kWave; ++lane) {
+    const PoolUnit u = pool_unit(p.g, w, lane);
+    if (!u.ok) continue;
+    const PoolPiece pp = pool_piece(p.g, u.q);
+    const uint64_t e = p.copied ? a.pool_tab_copy[pp.entry] : p.tab[pp.entry];
+    uint8_t* pooled = reinterpret_cast<uint8_t*>(a.pool_base + (e & 0xffffffffull) * slot_bytes + pp.p * piece + u.u * 16ull);
+    uint8_t* paged = reinterpret_cast<uint8_t*>(a.layer_ptr[pp.p >> 1] + (pp.p & 1u) * a.kv_kstride + (e >> 32) * piece + u.u * 16ull);
     if (a.pool_to_paged)
-      std::memcpy(paged, pooled, n);
+      std::memcpy(paged, pooled, 16);
     else
-      std::memcpy(pooled, paged, n);
-  }
-  if (__atomic_fetch_add(a.pool_ctr, 1u, __ATOMIC_ACQ_REL) == grid - 1) {
-    __atomic_store_n(a.pool_ctr, 0u, __ATOMIC_RELAXED);
-    astore(a.done, make_tag(a.seq, 0));
+      std::memcpy(pooled, paged, 16);
   }
 }
+void pool_workgroup(const FakePool& p, uint32_t wg) {
+  const KernelArgs& a = p.a;
+  const bool link = a.pool_link != 0, claims = a.pool_claim != 0;
+  const uint32_t per = link ? kLinkRows : 1;
+  FakeCounters ctr{a.pool_ctr};
+  for (uint32_t wave = 0; wave < kWavesPerWG; ++wave) {
+    SpanWalk s = span_walk(wg, p.grid, wave, kWavesPerWG, link);
+    while (s.at < span_count(p.g.waves, per)) {
+      const uint32_t got = claims ? ctr.add(1) : 0;
+      for (uint64_t w = s.at * per; w < std::min<uint64_t>(p.g.waves, (s.at + 1) * per); ++w)
+        pool_row(p, static_cast<uint32_t>(w));
+      span_next(s, claims, got);
+    }
+  }
+  if (link && !claims) {
+    for (uint32_t t = wg; t < a.pool_wgs; t += p.grid) astore(&a.done[t], make_tag(a.seq, t));
+    return;
+  }
+  if (p.grid <= kPoolTagLaunch && pool_last(wg, p.grid, claims, kPoolCtrs, ctr)) astore(&a.done[0], make_tag(a.seq, 0));
+}
 
-// A pool launch on the fake stream: a few host threads share its workgroups.
-void pool_launch(FakeStream& st, const KernelArgs& a, uint32_t grid) {
-  st.launch([a, grid] {
-    const uint32_t nt = std::min<uint32_t>(grid, 4);
+// On the fake stream: a few host threads share its workgroups.
+void pool_launch(FakeStream& st, const KernelArgs& a) {
+  auto p = std::make_shared<FakePool>();
+  p->a = a;
+  const uint32_t n = static_cast<uint32_t>(a.pool_blocks);
+  p->copied = a.kv_layers + a.pool_blocks > kPoolWords;
+  if (!p->copied) p->tab.assign(a.pool_tab_host, a.pool_tab_host + n);
+  p->g = pool_geom(n, 2 * a.kv_layers, a.kv_piece_bytes >> 4, a.pool_link ? 0 : a.pool_to_paged);
+  p->grid = static_cast<uint32_t>(
+      pool_grid(span_count(p->g.waves, a.pool_link ? kLinkRows : 1), kWavesPerWG, a.pool_link ? a.pool_wgs : 0));
+  st.launch([p, n] {
+    if (p->copied) std::memcpy(p->a.pool_tab_copy, p->a.pool_tab, n * sizeof(uint64_t));
+    const uint32_t nt = std::min<uint32_t>(p->grid, 4);
     std::vector<std::thread> ts;
     for (uint32_t t = 0; t < nt; ++t)
-      ts.emplace_back([&a, grid, t, nt] {
-        for (uint32_t g = t; g < grid; g += nt) pool_workgroup(a, g, grid);
+      ts.emplace_back([&p, t, nt] {
+        for (uint32_t wg = t; wg < p->grid; wg += nt) pool_workgroup(*p, wg);
       });
     for (auto& t : ts) t.join();
+    if (p->grid > kPoolTagLaunch) astore(&p->a.done[0], make_tag(p->a.seq, 0));
   });
 }
 
@@ -503,7 +541,7 @@ class Harness {
       return;
     }
     if (a.pool_tab) {
-      pool_launch(st, a, grid);
+      pool_launch(st, a);
     } else {
       st.launch([a, waves, rate] {
         std::vector<std::thread> ts;
@@ -548,7 +586,7 @@ class Harness {
     const uint32_t waves = grid * kWavesPerWG;
     const double rate = s_.wave_rate;
     if (a.pool_tab) {
-      pool_launch(st, a, grid);
+      pool_launch(st, a);
     } else {
       st.launch([a, waves, rate] {
         std::vector<std::thread> ts;
@@ -885,17 +923,18 @@ const std::vector<LinkCase> kChunks = {
 
 // KV transfers between a pool in device memory and the paged layers (piece
 // layout) run as pool launches: one launch, table from the arena, no ring and
-// no copy engine. Pieces of 8 KiB + 48 bytes end in a short span. Launches
-// queued back to back on one stream reuse light slots and counters. With the
+// no copy engine. Pieces of 8 KiB + 48 bytes end in a short row. Launches
+// queued back to back on one stream reuse light slots and counters. So does a launch
+// over the link, with a done tag per workgroup and with claims. With the
 // stream held, a transfer whose table finds no room in the arena takes the
 // ring path instead, and all of them land once the stream runs.
 void hbm_pool_launches() {
   Setup s;
   s.cfg = default_config();
   Harness h(s);
-  {
+  for (const bool dev : {true, false}) {
     FakeStream st;
-    const uint32_t L = 2, ppb = 2 * L, slots = 300, nb = 320;
+    const uint32_t L = 2, ppb = 2 * L, slots = 620, nb = 640;
     const uint64_t piece = 8192 + 48, slot_bytes = piece * ppb;
     std::vector<uint8_t> pool = random_bytes(slots * slot_bytes, 61);
     std::vector<std::vector<uint8_t>> layers(L, std::vector<uint8_t>(2 * nb * piece, 0xA5));
@@ -906,18 +945,22 @@ void hbm_pool_launches() {
     for (uint32_t l = 0; l < L; ++l) kv.layer_ptr[l] = reinterpret_cast<uint64_t>(layers[l].data());
     const uint64_t base = reinterpret_cast<uint64_t>(pool.data());
     const uint64_t cmds = h.stats().sdma_commands.load();
-    for (int n : {1, 7, 300}) {
+    // 600 blocks do not fit the arguments, and their fetch over the link claims spans
+    CHECK(link_claims(MMA_H2D, kKvLayoutPiece, 600 * slot_bytes) && 600 + L > kPoolWords, "sizes");
+    const auto launch = [&](int dir, const std::vector<int32_t>& hs, const std::vector<int32_t>& gb) {
+      const uint64_t n = hs.size();
+      std::unique_ptr<Transfer> x = make_kv_transfer(dir, piece, ppb, base, base, dev, false, hs.data(), gb.data(), n, h.cfg());
+      x->pool_launch = true;
+      if (!dev) set_pool_table(x.get(), base, hs.data(), gb.data(), n);
+      h.submit(std::move(x), n * slot_bytes, st, &kv);
+    };
+    for (int n : {1, 7, 300, 600}) {
       std::vector<int32_t> hs(n), gb(n);
       for (int i = 0; i < n; ++i) {
         hs[i] = (7 * i + 3) % static_cast<int>(slots);
         gb[i] = (11 * i + 1) % static_cast<int>(nb);
       }
-      for (int rep = 0; rep < 3; ++rep) {  // queued back to back: light slots and counters reused
-        std::unique_ptr<Transfer> x =
-            make_kv_transfer(MMA_H2D, piece, ppb, base, base, true, false, hs.data(), gb.data(), n, h.cfg());
-        x->pool_launch = true;
-        h.submit(std::move(x), n * slot_bytes, st, &kv);
-      }
+      for (int rep = 0; rep < 3; ++rep) launch(MMA_H2D, hs, gb);  // queued back to back
       st.synchronize();
       CHECK(h.sync(), "sync");
       bool ok = true;
@@ -936,10 +979,7 @@ void hbm_pool_launches() {
           for (uint32_t k = 0; k < 2; ++k)
             std::memcpy(want.data() + dest[j] * slot_bytes + (2 * l + k) * piece,
                         layers[l].data() + (k * nb + gb[j]) * piece, piece);
-      std::unique_ptr<Transfer> x =
-          make_kv_transfer(MMA_D2H, piece, ppb, base, base, true, false, dest.data(), gb.data(), n, h.cfg());
-      x->pool_launch = true;
-      h.submit(std::move(x), n * slot_bytes, st, &kv);
+      launch(MMA_D2H, dest, gb);
       st.synchronize();
       CHECK(h.sync(), "sync");
       CHECK(pool == want, "pool offload of %d blocks: pool differs", n);
@@ -992,7 +1032,7 @@ void hbm_pool_launches() {
     CHECK(ok, "arena-bound pool fetches differ");
   }
   CHECK(h.stats().failed.load() == 0, "pool launches: failed transfers");
-  std::printf("ok   HBM pool KV transfers run as one launch each; without arena room a transfer takes the ring\n");
+  std::printf("ok   pool launches in HBM and over the link; without arena room a transfer takes the ring\n");
 }
 
 // A deep queue of whole transfers on a stream that cannot progress yet: they
