@@ -145,14 +145,21 @@ typedef struct mma_config {
                                path. MMA_DUPLEX_UNCHANGED: path_mask_h2d. Each copy engine
                                runs one in-order queue for both directions, and CU zero-copy loads
                                send their read requests up the lanes that device->host data uses.
-                               Micro-tasks only the CU path may carry still take it. */
+                               Micro-tasks only the CU path may carry still take it. A KV transfer
+                               that one launch would carry alone (cu_whole_bytes) and that is
+                               above that limit goes to the engine thread, and so by these paths,
+                               if the other direction moves on another stream when it is
+                               submitted; once launched it stays the CU path's. Smaller ones and
+                               copies carried whole do not look at the other direction. */
   uint32_t duplex_paths_d2h; /* paths device->host pulls from while a host->device transfer is
                                moving. 0 (default): with the default path_mask_d2h, SDMA engines
                                2-5 (on MI355X the xGMI-facing engines, 13-18 GB/s each toward the
                                host), neither the host-facing engines nor the CU path, whose stores
                                to host memory share the upstream lanes in small writes; with a
                                path_mask_d2h given, its SDMA engines without the CU path.
-                               MMA_DUPLEX_UNCHANGED: path_mask_d2h.
+                               MMA_DUPLEX_UNCHANGED: path_mask_d2h. With 0, KV offloads that one
+                               launch carries keep it, CU path and all, while the other direction
+                               moves: that is faster for them by more than it costs the rest.
                                Engines the device does not offer are dropped; a set left with no
                                path, or a CU path the direction does not have, falls back to its
                                path mask. */

@@ -144,6 +144,8 @@ struct Transfer {
   // the block table (pool slot | GPU block << 32 per block) from the engine's
   // table arena, segments [tab_seg, tab_seg + tab_nseg).
   bool pool_launch = false;
+  const void* stream = nullptr;  // the caller's
+  bool link_large = false;  // over the link and above the whole-transfer limit: moves for the other direction (see set_peer)
   uint64_t pool_base = 0;
   std::vector<uint64_t> pool_pairs;
   std::vector<uint64_t> pool_tmp;  // room to sort them
@@ -234,6 +236,7 @@ struct Config {
   uint32_t device_cu_percent;  // device control: the CU path's share of a linear transfer's bytes
   uint32_t overdue_gbs;        // link rate the overdue rule assumes, GB/s (0: 50)
   uint32_t duplex[2];          // per direction: the paths used while the other direction moves (see set_peer)
+  bool duplex_given[2];        // the caller chose them
   uint64_t nap_ns;             // longest sleep of the engine thread between rounds (see nap); 0: poll
   uint64_t duplex_hold_ns;     // a direction counts as moving this long after it was last seen moving
                                // (0: kDuplexHoldNs)
@@ -341,6 +344,7 @@ inline void sort_table(uint64_t* v, size_t n, uint32_t shift, uint64_t* tmp) {
 
 // See link_eligible.
 constexpr uint32_t kLinkWgs = 8;
+inline const void* const kSeveralStreams = reinterpret_cast<const void*>(~uintptr_t{0});
 constexpr uint64_t kLinkFewBytes = 256 * KiB;
 
 // Whether the waves of a launch over the link claim their spans. Below these sizes
@@ -369,10 +373,10 @@ class Engine {
     if ((rc = be_->alloc_device_state(sizeof(DevState) * kRecords, &d)) != MMA_OK) return rc;
     ds_ = static_cast<DevState*>(d);
     for (uint32_t i = 0; i < kRecords; ++i) free_recs_.push_back(i);
-    if ((rc = be_->alloc_records(sizeof(uint64_t) * kPrefill * kLightSlots, &h, &d)) != MMA_OK) return rc;
+    if ((rc = be_->alloc_records(sizeof(uint64_t) * kLightWords * kLightSlots, &h, &d)) != MMA_OK) return rc;
     light_ = static_cast<uint64_t*>(h);
     light_dev_ = static_cast<uint64_t*>(d);
-    memset(light_, 0, sizeof(uint64_t) * kPrefill * kLightSlots);
+    memset(light_, 0, sizeof(uint64_t) * kLightWords * kLightSlots);
     for (uint32_t i = 0; i < kLightSlots; ++i) free_light_.push_back(i);
     light_ring_.reset(new CuEntry[kPrefill + kRingSize]);
     if ((rc = be_->alloc_records(sizeof(uint64_t) * kPoolTabEntries, &h, &d)) != MMA_OK) return rc;
@@ -535,14 +539,39 @@ class Engine {
   // at 102-104 ms; all paths shared: 309-312 and 170-174 ms. The CU path still
   // takes micro-tasks that no other path may carry. Device control has no
   // phases: its copy-engine share stays on the direction's own path mask.
+  //
+  // A launch over the link (link_eligible) has the CU path alone, and is no transfer
+  // of the engine thread. Above the whole-transfer limit, where its kind went by the
+  // ring before, it keeps to the rule as far as that is worth it. A load of 896 MiB
+  // (16.5 ms alone) beside 1.5 GiB in 256 KiB blocks of the other direction, ms:
+  //                                    load            blocks as on the host, x-packed
+  //  - fetch: ring                     18.4            52, 65
+  //           launch, load on all its paths or on its duplex paths
+  //                                    39.4 or 30.3 (x-packed 38.4 or 42.0)   36.8 or 28.4, 35.7 or 28.1
+  //    So a fetch is none while the engine thread moves the other direction, unless
+  //    all that it moves is on the call's own stream, which this call comes after.
+  //  - offload: ring                   17.5            42, 57
+  //           launch, load on all its paths or on its duplex paths
+  //                                    18.7 or 19.0    34.2 or 32.4, 34.2 or 32.5
+  //    So an offload steps back only for duplex paths that the caller gave.
+  //  - from its start to its end a launch moves, as the other direction sees it.
   // Called once both engines are initialised.
   void set_peer(const Engine* peer) { peer_ = peer; }
   // Bytes of the other direction's commands in flight on copy engine e.
   uint64_t peer_bytes_on(int e) const { return peer_ ? peer_->eng_bytes_[e].load(std::memory_order_relaxed) : 0; }
   // The other direction has had a started transfer that is not complete
-  // within the last kDuplexHoldNs.
-  bool peer_moving(uint64_t now) const { return peer_ && peer_->moving(now); }
+  // within the last kDuplexHoldNs, or a large launch over the link runs.
+  bool peer_moving(uint64_t now) const { return peer_ && (peer_->moving(now) || peer_->link_moving()); }
   bool moving(uint64_t now) const { return now < moving_until_.load(std::memory_order_relaxed); }
+  // A large launch over the link has started and not ended (any thread).
+  bool link_moving() const {
+    if (cfg_.device || n_links_.load(std::memory_order_acquire) == 0) return false;
+    std::lock_guard<std::mutex> g(links_mu_);
+    drop_ended_links();
+    for (const LinkRun& r : links_)
+      if (ld_acq(r.words + kPrefill) == make_tag(r.seq, 0)) return true;
+    return false;
+  }
 
   // Transfers tracked by the submitting threads are in flight (see track).
   bool tracked() const { return n_tracked_.load(std::memory_order_acquire) != 0; }
@@ -583,12 +612,16 @@ class Engine {
   // cu_workgroups 1, 2, 4, entries or ring / one launch:
   //    fetch of 10 x-packed blocks of 2 MiB   386 / 1328, 387 / 895, 385 / - us
   //    of 5 head-major blocks of 384 KiB      46 / 94, 47 / 66, 46 / 43 us
-  //    128 MiB in 256 KiB blocks, GB/s: head-major 17.7 / 13.9, 25.0 / 20.7, 36.1 / 38.8 (1 MiB blocks 41.2 /
-  //      36.6, with 6 50.4 / 51.1), x-packed 15.8 / 15.7, 22.6 / 23.3, 33.8 / 43.4 (192 KiB blocks 9.4 / 8.5,
-  //      14.2 / 12.8, 20.5 / 24.8), as on the host 17.2 / 30.9, 30.3 / 43.9, 46.4 / 56.8 (kLinkFewSpan);
-  //      offload 24.3 / 28.0, 34.2 / 41.3, 41.0 / 54.0; 13.1 / 15.4, 19.2 / 22.9, 31.1 / 44.2; 22.9 / 55.2,
-  //      38.9 / 55.2, 49.3 / 55.1
-  //    512 MiB in 64 KiB blocks               4.0 / 10.9, 6.4 / 16.4, 6.7 / 31.0 GB/s
+  //    fetch, 128 MiB in 256 KiB blocks, GB/s:
+  //      head-major                           17.7 / 13.9, 25.0 / 20.7, 36.1 / 38.8
+  //      head-major, 1 MiB blocks             18.2 / 17.3, 26.1 / 23.8, 41.2 / 36.6 (with 6: 50.4 / 51.1)
+  //      x-packed                             15.8 / 15.7, 22.6 / 23.3, 33.8 / 43.4
+  //      x-packed, 192 KiB blocks              9.4 /  8.5, 14.2 / 12.8, 20.5 / 24.8
+  //      as on the host (kLinkFewSpan)        17.2 / 30.9, 30.3 / 43.9, 46.4 / 56.8
+  //    offload, head-major                    24.3 / 28.0, 34.2 / 41.3, 41.0 / 54.0
+  //      x-packed                             13.1 / 15.4, 19.2 / 22.9, 31.1 / 44.2
+  //      as on the host                       22.9 / 55.2, 38.9 / 55.2, 49.3 / 55.1
+  //    fetch, 512 MiB in 64 KiB blocks         4.0 / 10.9,  6.4 / 16.4,  6.7 / 31.0
   bool link_eligible(const Transfer* x, const KvGeom& kv, uint64_t payload_bytes, uint64_t slot_bytes) const {
     if (!cu_enabled() || cfg_.static_split || cfg_.whole[dir_] <= 1) return false;
     if (cfg_.cu_wgs < kLinkWgs && payload_bytes > cfg_.cu_wgs * kLinkFewBytes) {
@@ -596,7 +629,13 @@ class Engine {
       const uint32_t least = kv.layout == kKvLayoutHnd ? 6 : kv.layout == kKvLayoutXPacked ? 3 : 1;
       if (dir_ == MMA_H2D && slot_bytes > 64 * KiB && cfg_.cu_wgs < least) return false;
     }
-    if (payload_bytes > cfg_.whole[dir_]) return slot_bytes <= (dir_ == MMA_H2D ? MiB : 512 * KiB);
+    if (payload_bytes > cfg_.whole[dir_]) {
+      const bool steps_back = dir_ == MMA_H2D || cfg_.duplex_given[dir_];  // see set_peer
+      if (steps_back && x->sdma_ok && duplex_without_cu() && peer_ && peer_->moving(now_ns()) &&
+          peer_->moving_stream_.load(std::memory_order_relaxed) != x->stream)
+        return false;
+      return slot_bytes <= (dir_ == MMA_H2D ? MiB : 512 * KiB);
+    }
     const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
     return !few_large || payload_bytes > 12 * MiB;
   }
@@ -645,7 +684,7 @@ class Engine {
       x->light = static_cast<int32_t>(i);
       x->rec = nullptr;
       x->ring = light_ring_.get();
-      x->done_host = light_ + static_cast<uint64_t>(i) * kPrefill;
+      x->done_host = light_ + static_cast<uint64_t>(i) * kLightWords;
     } else {
       x->rec_idx = i;
       x->rec = &recs_[i];
@@ -864,6 +903,8 @@ class Engine {
       a.pool_wgs = static_cast<uint32_t>(std::min<uint64_t>(wg_cap(true), kPrefill));
       a.pool_claim = link_claims(dir_, kv->layout, x->bytes) ? 1 : 0;
       if (!a.pool_claim) x->pushed = a.pool_wgs;
+      x->link_large = x->bytes > cfg_.whole[dir_];
+      if (x->link_large) a.pool_started = a.done + kPrefill;
     }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;
@@ -898,7 +939,7 @@ class Engine {
     if (x->light >= 0) {
       a.rec = nullptr;
       a.ds = nullptr;
-      a.done = light_dev_ + static_cast<uint64_t>(x->light) * kPrefill;
+      a.done = light_dev_ + static_cast<uint64_t>(x->light) * kLightWords;
     } else {
       a.rec = rec_dev(x->rec_idx);
       a.ds = ds(x->rec_idx);
@@ -1081,6 +1122,12 @@ class Engine {
     {
       std::lock_guard<std::mutex> g(mu_);
       ++inflight_;
+    }
+    if (x->link_large) {
+      std::lock_guard<std::mutex> g(links_mu_);
+      drop_ended_links();
+      links_.push_back(LinkRun{x->done_host, x->seq, static_cast<uint32_t>(x->pushed)});
+      n_links_.store(static_cast<uint32_t>(links_.size()), std::memory_order_release);
     }
     std::lock_guard<std::mutex> g(dev_mu_);
     tracked_.push_back(std::move(x));
@@ -1613,11 +1660,23 @@ class Engine {
   }
   // The same decision for the CU path alone, from any thread (paths_ and cfg_
   // are fixed after init).
-  bool cu_paused_at(uint64_t now) const {
-    if (!cu_enabled() || !peer_moving(now) || (cfg_.duplex[dir_] & MMA_PATH_CU)) return false;
+  bool cu_paused_at(uint64_t now) const { return duplex_without_cu() && peer_moving(now); }
+  bool duplex_without_cu() const {
+    if (!cu_enabled() || (cfg_.duplex[dir_] & MMA_PATH_CU)) return false;
     for (auto& path : paths_)
       if ((cfg_.duplex[dir_] >> path.engine) & 1u) return true;
     return false;
+  }
+  // Forgets the large launches over the link whose tags are all in (links_mu_ held). A
+  // slot that a later transfer took over holds tags of a later sequence number.
+  void drop_ended_links() const {
+    const auto ended = [](const LinkRun& r) {
+      for (uint32_t t = 0; t < r.tags; ++t)
+        if (static_cast<int32_t>((ld_acq(r.words + t) >> 32) - r.seq) < 0) return false;
+      return true;
+    };
+    links_.erase(std::remove_if(links_.begin(), links_.end(), ended), links_.end());
+    n_links_.store(static_cast<uint32_t>(links_.size()), std::memory_order_release);
   }
 
   // Paths that can make progress take work (Section 2.2; Section 3.4 contention
@@ -1985,7 +2044,13 @@ class Engine {
         p = true;
       }
       bool moving = false;
-      for (auto& up : active_) moving |= up->started && !up->completed && !up->failed;
+      const void* stream = nullptr;
+      for (auto& up : active_) {
+        if (!up->started || up->completed || up->failed) continue;
+        stream = !moving || stream == up->stream ? up->stream : kSeveralStreams;
+        moving = true;
+      }
+      if (moving) moving_stream_.store(stream, std::memory_order_relaxed);
       if (moving)
         moving_until_.store(now_ns() + (cfg_.duplex_hold_ns ? cfg_.duplex_hold_ns : kDuplexHoldNs),
                             std::memory_order_relaxed);
@@ -2016,7 +2081,7 @@ class Engine {
   Stats* st_;
   Record* recs_ = nullptr;
   Record* recs_dev_ = nullptr;
-  uint64_t* light_ = nullptr;      // light slots' done tags, kPrefill per slot (host address)
+  uint64_t* light_ = nullptr;      // light slots' tags, kLightWords per slot (host address)
   uint64_t* light_dev_ = nullptr;  // the same, device address
   std::unique_ptr<CuEntry[]> light_ring_;  // scratch ring: light transfers' entries go to the kernel args
   uint64_t* pool_tab_ = nullptr;      // HBM pool launches' table arena (host address)
@@ -2047,6 +2112,18 @@ class Engine {
   // other direction's engine thread.
   std::atomic<uint64_t> eng_bytes_[MMA_MAX_SDMA] = {};
   std::atomic<uint64_t> moving_until_{0};  // see peer_moving (read by the other direction)
+  std::atomic<const void*> moving_stream_{nullptr};  // of what moves, or moved last
+  // Large launches over the link in flight: the words of their light slots (kept as
+  // long as the engine is), sequence numbers and done tags. The other direction's
+  // engine thread looks, and forgets those that have ended.
+  struct LinkRun {
+    const uint64_t* words;
+    uint64_t seq;
+    uint32_t tags;
+  };
+  mutable std::mutex links_mu_;
+  mutable std::vector<LinkRun> links_;
+  mutable std::atomic<uint32_t> n_links_{0};
   uint32_t usable_ = 0;                    // paths of this phase (see phase)
   mutable std::vector<std::pair<const Transfer*, uint64_t>> nap_scratch_;  // see nap (engine thread)
   bool cu_paused_ = false;                 // the CU path takes only CU-only micro-tasks (see set_peer)

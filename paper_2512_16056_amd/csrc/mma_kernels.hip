@@ -695,6 +695,11 @@ struct DevCounters {
   }
 };
 
+// The start tag, where the other direction's engine thread looks for it.
+__device__ __forceinline__ void pool_begin(const PoolArgs& a) {
+  if (a.started && blockIdx.x == 0 && threadIdx.x == 0) st_sys(a.started, make_tag(a.seq, 0));
+}
+
 // The workgroup that finishes last writes the done tag. The counters only order
 // the tag after every workgroup: the data itself becomes visible to later work
 // through the stream, when the kernel ends, as for any kernel (a device-wide
@@ -764,6 +769,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const XGeom g{a.tokens, a.heads, a.row_bytes, a.elem, a.lds_wave};
+  pool_begin(a);
   for (SpanWalk s = span_walk(a, wave); s.at * a.group < a.g.waves; span_next(a, s)) {
     span_claim(a, s, lane);
     const uint64_t end = min(a.g.waves, (s.at + 1) * a.group);
@@ -846,6 +852,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_xp_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint64_t keys = span_count(a.g.waves, K);
+  if constexpr (kLink) pool_begin(a);
   for (SpanWalk s = span_walk(a, wave); s.at < keys + a.gv.waves; span_next(a, s)) {
     span_claim(a, s, lane);
     if (s.at < keys) {
@@ -987,6 +994,7 @@ __global__ __launch_bounds__(kBlock) void mma_kv_link_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   __shared__ uint64_t s_w[kPoolWords];
+  pool_begin(a);
   for (uint32_t i = threadIdx.x; i < a.words; i += kBlock) s_w[i] = a.w[i];
   __syncthreads();
   const auto word = [&](uint32_t i) { return s_w[i]; };
@@ -1203,6 +1211,7 @@ hipError_t launch_pool(const KernelArgs& args, hipStream_t stream, bool* begun) 
   p.tags = args.pool_link && !args.pool_claim ? args.pool_wgs : 0;
   p.claim = args.pool_claim ? args.pool_ctr + kPoolCtrStride : nullptr;
   p.clear = nullptr;
+  p.started = args.pool_started;
   if (p.layers + args.pool_blocks <= kPoolWords) {
     p.words += static_cast<uint32_t>(args.pool_blocks);
     memcpy(p.w + p.layers, args.pool_tab_host, args.pool_blocks * sizeof(uint64_t));

@@ -29,6 +29,9 @@ constexpr uint32_t kRecords = 64;      // records per direction (transfers in fl
 constexpr uint32_t kLightSlots = 4096;
 constexpr uint32_t kMaxWorkgroups = 256;  // dummy-task kernel size limit (ring keeps one slot per wave)
 constexpr uint32_t kPrefill = 48;      // ring entries also passed in the kernel arguments (linear kinds)
+// Words of a light slot: its done tags, and in word kPrefill the start tag of a launch
+// over the link that the other direction's paths depend on (one line of its own).
+constexpr uint32_t kLightWords = kPrefill + 8;
 constexpr uint32_t kMaxLayers = 256;   // KV layer pointers per record
 constexpr uint32_t kMaxLdsPerWave = 36 * 1024;  // x-packed KV tiles: 4 waves x 36 KiB + 2 KiB of a CU's 160 KiB
 constexpr uint32_t kWave = 64;
@@ -127,7 +130,7 @@ struct alignas(128) DevState {
 struct KernelArgs {
   Record* rec;              // device-visible address of the record (null for a light slot)
   DevState* ds;
-  uint64_t* done;           // device-visible done tags: the record's, or a light slot's kPrefill
+  uint64_t* done;           // device-visible done tags: the record's, or a light slot's
   uint64_t seq;
   uint64_t watchdog_ticks;  // wall-clock ticks without progress before giving up
   uint32_t total_waves;
@@ -164,6 +167,7 @@ struct KernelArgs {
   uint64_t pool_blocks;      // its entries
   uint32_t pool_link;        // 1: the pool is host memory (mma_kv_link_kernel), pool_wgs its workgroups at most
   uint32_t pool_wgs;
+  uint64_t* pool_started;    // gets make_tag(seq, 0) when the launch starts; null: none
   uint32_t pool_claim;       // 1: its waves claim their spans (else fixed shares and a done tag per workgroup)
   uint32_t* pool_ctr;        // device counters of finished workgroups, 0 between launches
   uint64_t pool_base;        // device address of the pool
@@ -180,6 +184,7 @@ struct PoolArgs {
   uint64_t seq;
   uint32_t* ctr;
   uint32_t* claim;          // counter of claimed spans, 0 when the launch starts; null: fixed shares
+  uint64_t* started;        // gets make_tag(seq, 0) when the launch starts; null: none
   uint32_t* clear;          // a word that the launch sets to 0; null: none
   const uint64_t* tab;      // block table in device memory; null: w[layers ..]
   uint64_t pool;

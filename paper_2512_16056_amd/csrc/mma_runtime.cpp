@@ -394,6 +394,7 @@ mma_status_t submit(std::unique_ptr<Transfer> x, uint64_t payload_bytes, void* s
   Runtime* rt = g_rt;
   Engine* e = rt->eng[x->dir].get();
   std::lock_guard<std::mutex> g(rt->submit_mu);
+  x->stream = stream;
   if (!e->acquire(x.get(), payload_bytes, kv != nullptr, 60000))
     return fail(MMA_ERR_TIMEOUT, "no free transfer record for 60 s");
   static thread_local KernelArgs a;
@@ -625,6 +626,7 @@ mma_status_t mma_init(int hip_device, const mma_config_t* user_cfg) try {
   // Paths while the other direction moves (see Engine::set_peer). A static
   // split fixes each micro-task's path at plan time, so it keeps its masks.
   uint32_t duplex[2] = {c.duplex_paths_h2d, c.duplex_paths_d2h};
+  const bool duplex_given[2] = {duplex[0] != 0, duplex[1] != 0};
   for (int d = 0; d < 2; ++d) {
     if (c.static_split || duplex[d] == MMA_DUPLEX_UNCHANGED) {
       duplex[d] = mask[d];
@@ -656,8 +658,10 @@ mma_status_t mma_init(int hip_device, const mma_config_t* user_cfg) try {
   k.watchdog_ms = c.watchdog_ms;
   k.mask[0] = mask[0];
   k.mask[1] = mask[1];
-  k.duplex[0] = duplex[0];
-  k.duplex[1] = duplex[1];
+  for (int d = 0; d < 2; ++d) {
+    k.duplex[d] = duplex[d];
+    k.duplex_given[d] = duplex_given[d];
+  }
   k.device = c.control == MMA_CONTROL_DEVICE ? 1u : 0u;
   k.device_cu_percent = c.static_cu_percent ? c.static_cu_percent : kDeviceCuPercent;
   k.static_split = c.static_split;
@@ -985,6 +989,7 @@ static mma_status_t kv_common(const mma_kv_layout_t* lay, const void* host_pool,
   const bool sdma_ok = per_task <= rt->eng[dir]->stage_bytes() && !c.pool_dev;
   std::unique_ptr<Transfer> x = make_kv_transfer(dir, c.piece, c.ppb, reinterpret_cast<uint64_t>(host_pool),
                                                  c.pool_cu, c.pool_dev, sdma_ok, host_slots, gpu_blocks, n, rt->cfg);
+  x->stream = stream;
   // A pool in HBM, or a transfer over the link that one launch carries best: a
   // pool launch, if the table finds room (acquire).
   x->pool_launch = c.pool_dev || rt->eng[dir]->link_eligible(x.get(), c.kv, n * c.slot_bytes, c.slot_bytes);

@@ -334,6 +334,9 @@ void pool_workgroup(const FakePool& p, uint32_t wg) {
   if (p.grid <= kPoolTagLaunch && pool_last(wg, p.grid, claims, kPoolCtrs, ctr)) astore(&a.done[0], make_tag(a.seq, 0));
 }
 
+// Launches over the link that start wait here until it is false.
+std::atomic<bool> g_hold_links{false};
+
 // On the fake stream: a few host threads share its workgroups.
 void pool_launch(FakeStream& st, const KernelArgs& a) {
   auto p = std::make_shared<FakePool>();
@@ -345,6 +348,8 @@ void pool_launch(FakeStream& st, const KernelArgs& a) {
   p->grid = static_cast<uint32_t>(
       pool_grid(span_count(p->g.waves, a.pool_link ? kLinkRows : 1), kWavesPerWG, a.pool_link ? a.pool_wgs : 0));
   st.launch([p, n] {
+    if (p->a.pool_started) astore(p->a.pool_started, make_tag(p->a.seq, 0));
+    while (p->a.pool_link && g_hold_links) sleep_ns(100000);
     if (p->copied) std::memcpy(p->a.pool_tab_copy, p->a.pool_tab, n * sizeof(uint64_t));
     const uint32_t nt = std::min<uint32_t>(p->grid, 4);
     std::vector<std::thread> ts;
@@ -1649,6 +1654,91 @@ void duplex_paths() {
   std::printf("ok   while the other direction moves, a direction pulls from its duplex paths only\n");
 }
 
+// Both directions at once with a launch over the link above the whole-transfer limit: it
+// moves, for the other direction, from its start to its end, and a fetch is none while
+// the engine thread moves the other direction (set_peer).
+void link_launch_and_duplex_paths() {
+  const uint32_t L = 1, ppb = 2, slots = 2100;
+  const uint64_t piece = 1024, slot_bytes = piece * ppb;
+  std::vector<uint8_t> pool = random_bytes(slots * slot_bytes, 91), layer(2 * slots * piece, 0xA5);
+  KvGeom kv;
+  kv.piece = piece;
+  kv.kstride = piece * slots;
+  kv.layers = L;
+  kv.layer_ptr[0] = reinterpret_cast<uint64_t>(layer.data());
+  const uint64_t base = reinterpret_cast<uint64_t>(pool.data());
+  std::vector<int32_t> ids(slots);
+  for (uint32_t i = 0; i < slots; ++i) ids[i] = static_cast<int32_t>(i);
+  const uint64_t n = 24ull * 1024 * 1024 + 3;
+  const auto src = random_bytes(n, 92);
+  std::vector<uint8_t> dst(n);
+  Setup s;
+  s.cfg = default_config();
+  s.cfg.cu_wgs = 16;
+  s.cfg.whole[0] = s.cfg.whole[1] = 2 * MiB;
+  s.duplex[MMA_H2D] = s.duplex[MMA_D2H] = 0x3;
+  s.cfg.duplex_hold_ns = 300000000;
+  for (const int dir : {MMA_H2D, MMA_D2H}) {
+    Harness h(s);
+    FakeStream a, b;
+    const auto link = [&](int d) {
+      std::unique_ptr<Transfer> x = make_kv_transfer(d, piece, ppb, base, base, false, true, ids.data(), ids.data(), slots, h.cfg());
+      x->pool_launch = h.engine(d)->link_eligible(x.get(), kv, slots * slot_bytes, slot_bytes);
+      set_pool_table(x.get(), base, ids.data(), ids.data(), slots);
+      return x;
+    };
+    const int other = dir == MMA_H2D ? MMA_D2H : MMA_H2D;
+    const auto cu_bytes = [&] { return h.stats().path_bytes[MMA_NUM_PATHS - 1].load(); };
+    // queued behind other work the launch does not move yet
+    std::promise<void> gate;
+    std::shared_future<void> open = gate.get_future().share();
+    a.launch([open] { open.wait(); });
+    g_hold_links = true;
+    std::unique_ptr<Transfer> x = link(dir);
+    CHECK(x->pool_launch, "no launch over the link with the other direction idle");
+    h.submit(std::move(x), slots * slot_bytes, a, &kv);
+    CHECK(!h.engine(dir)->link_moving(), "a launch that has not started moves");
+    gate.set_value();
+    for (int i = 0; i < 2000 && !h.engine(dir)->link_moving(); ++i) sleep_ns(1000000);
+    CHECK(h.engine(dir)->link_moving(), "a launch that has started does not move");
+    // a copy of the other direction keeps to its duplex paths
+    uint64_t before = cu_bytes();
+    h.submit(linear(other, dst.data(), src.data(), n, h.cfg()), n, b);
+    b.synchronize();
+    CHECK(h.engine(other)->wait_idle(60000), "the copy did not retire");
+    CHECK(h.engine(dir)->link_moving() && cu_bytes() == before, "beside the launch the CU path carried %llu bytes of the copy",
+          static_cast<unsigned long long>(cu_bytes() - before));
+    g_hold_links = false;
+    a.synchronize();
+    CHECK(!h.engine(dir)->link_moving(), "a launch that has ended moves");
+    CHECK(h.sync(), "sync");
+    before = cu_bytes();
+    h.submit(linear(other, dst.data(), src.data(), n, h.cfg()), n, b);
+    b.synchronize();
+    CHECK(h.sync() && cu_bytes() > before && dst == src, "alone the copy uses the CU path, too");
+    // the other direction moved less than the hold time ago, on this stream or another one
+    CHECK(link(dir)->pool_launch, "no launch over the link behind a copy on its own stream");
+    x = make_kv_transfer(dir, piece, ppb, base, base, false, true, ids.data(), ids.data(), slots, h.cfg());
+    x->stream = &h;
+    x->pool_launch = h.engine(dir)->link_eligible(x.get(), kv, slots * slot_bytes, slot_bytes);
+    CHECK(x->pool_launch == (dir == MMA_D2H), "dir %d: launch over the link while the engine thread moves the other one: %d", dir,
+          x->pool_launch);
+    CHECK(h.stats().failed.load() == 0, "failed transfers");
+  }
+  {
+    s.cfg.duplex_given[MMA_D2H] = true;  // chosen by the caller
+    Harness h(s);
+    FakeStream b;
+    h.submit(linear(MMA_H2D, dst.data(), src.data(), n, h.cfg()), n, b);
+    b.synchronize();
+    std::unique_ptr<Transfer> x = make_kv_transfer(MMA_D2H, piece, ppb, base, base, false, true, ids.data(), ids.data(), slots, h.cfg());
+    x->stream = &h;
+    CHECK(!h.engine(MMA_D2H)->link_eligible(x.get(), kv, slots * slot_bytes, slot_bytes), "given duplex paths are not kept to");
+    CHECK(h.sync(), "sync");
+  }
+  std::printf("ok   a large launch over the link moves for the other direction, and a fetch steps back for it\n");
+}
+
 void pull_tracks_best_static_split() {
   for (double ratio : {1.0, 2.0}) {
     const double eng = 1000, cu = 1000 * ratio;  // CU path ratio x faster
@@ -1713,6 +1803,7 @@ int main(int argc, char** argv) {
     shutdown_in_flight_keeps_shared_memory();
     foreign_work_skipped();
     duplex_paths();
+    link_launch_and_duplex_paths();
   }
   if (timing) {
     duplex_peer_commands();

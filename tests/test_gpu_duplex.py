@@ -133,3 +133,84 @@ def test_duplex_paths_while_both_directions_move():
     assert kv["path_tasks"][16] == 0, kv["path_tasks"]
     assert lst["path_tasks"][16] == 1, lst["path_tasks"]  # the 4 KiB tensor
     h2d_dst = None
+
+
+# 64 KiB blocks, 40 MiB: above both whole-transfer limits
+SMALL = W.KVShape(layers=1, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2, gpu_num_blocks=700,
+                  host_num_slots=680, n_blocks=640)
+
+
+@pytest.mark.parametrize("direction", ["fetch", "offload"])
+@pytest.mark.parametrize("first", ["kv", "copy"])
+def test_link_launch_beside_the_other_direction(direction, first):
+    """A KV transfer in small blocks at the default limits beside a multipath copy of the other direction.
+    Submitted while the copy moves, a fetch goes by the engine thread, an offload by its one launch; a
+    launch that runs makes the copy keep to its duplex paths. Bytes in either order; paths where the trace
+    shows that one ran inside the other."""
+    s = SMALL
+    lay, n_copy = _layout(s), 512 << 20
+    hs, gb = W.kv_fetch_tables(s, cfg=3)
+    r = np.random.default_rng(12)
+    pool = mma.PinnedBuffer(s.host_num_slots * s.slot_bytes)
+    pool.array[:] = np.frombuffer(r.bytes(pool.nbytes), np.uint8)
+    pool_before = pool.array.copy()
+    host = mma.PinnedBuffer(n_copy)
+    data = np.frombuffer(r.bytes(1 << 20), np.uint8)
+    kv_dir, copy_dir = (mma.MMA_H2D, mma.MMA_D2H) if direction == "fetch" else (mma.MMA_D2H, mma.MMA_H2D)
+    dev = device_bytes(n_copy)
+    for attempt in range(4):
+        log(f"link {direction} beside a copy, {first} first, attempt {attempt}")
+        src = torch.from_numpy(np.tile(data, n_copy >> 20))
+        if copy_dir == mma.MMA_D2H:
+            dev.copy_(src)
+            host.array[:] = 0
+        else:
+            host.array[:] = src.numpy()
+            dev.zero_()
+        pool.array[:] = pool_before
+        layer = torch.from_numpy(np.frombuffer(r.bytes(s.layer_bytes), np.uint8).copy()).cuda()
+        view = to_host(layer).reshape(2, s.gpu_num_blocks, s.piece_bytes)
+        sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+
+        def copy():
+            d, h = (host, dev) if copy_dir == mma.MMA_D2H else (dev, host)
+            mma.mma_memcpy_async(d, h, n_copy, copy_dir, sa)
+
+        def kv():
+            if direction == "fetch":
+                mma.mma_kv_fetch(lay, pool, [layer], hs, gb, sb)
+            else:
+                mma.mma_kv_offload(lay, pool, [layer], gb, hs, sb)
+
+        with session("both", cu_whole_bytes=0, cu_whole_bytes_d2h=0):
+            mma.mma_trace_enable(True)
+            for i, step in enumerate((kv, copy) if first == "kv" else (copy, kv)):
+                if i and first == "copy":
+                    time.sleep(0.002)
+                step()
+            torch.cuda.synchronize()
+            mma.mma_synchronize()
+            trace = mma.mma_trace_read()
+            mma.mma_trace_enable(False)
+            assert mma.mma_get_stats()["failed_transfers"] == 0
+        got = host.array if copy_dir == mma.MMA_D2H else to_host(dev)
+        assert np.array_equal(got.reshape(-1, 1 << 20), np.broadcast_to(data, (n_copy >> 20, 1 << 20)))
+        pv = pool_before.reshape(s.host_num_slots, -1)
+        if direction == "fetch":
+            want = okv.kv_fetch_layer(pv, view, 0, 1, hs, gb)
+            assert np.array_equal(to_host(layer).reshape(want.shape), want)
+        else:
+            want = okv.kv_offload(pv.copy(), [view], gb, hs)
+            assert np.array_equal(pool.array.reshape(want.shape), want)
+        k = [x for x in trace if x["dir"] == kv_dir][0]
+        c = [x for x in trace if x["dir"] == copy_dir][0]
+        log(f"kv paths {k['path_tasks']}, copy paths {c['path_tasks']}")
+        if first == "kv":
+            assert sum(k["path_tasks"][:16]) == 0, k["path_tasks"]  # nothing moved yet: one launch
+        elif c["t_started_ns"] + 1000000 < k["t_submit_ns"] and k["t_submit_ns"] < c["t_last_task_ns"]:
+            if direction == "fetch":
+                assert sum(k["path_tasks"][:16]) > 0, k["path_tasks"]  # by the engine thread
+            else:
+                assert sum(k["path_tasks"][:16]) == 0, k["path_tasks"]
+            break
