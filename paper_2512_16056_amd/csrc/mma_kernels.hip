@@ -349,14 +349,15 @@ __device__ __forceinline__ u32x4 gather16(const lds_u8* p, uint32_t stride) {
   return r;
 }
 
-// host (token-major) piece `src` -> x-packed block `dst`; k = 0 key, 1 value.
+// Heads [first, end) of host (token-major) piece `src` -> x-packed block `dst`; k = 0
+// key, 1 value.
 template <uint32_t E>
 __device__ void xpacked_to_block(const uint8_t* src, uint8_t* dst, uint32_t k, const XGeom& g, lds_u8* lds,
-                                 uint32_t lane) {
+                                 uint32_t lane, uint32_t first, uint32_t end) {
   const uint32_t G = xp_to_heads(g);
   auto to_lds = [&](uint32_t o, u32x4 v) { *reinterpret_cast<lu4*>(lds + o) = v; };
-  for (uint32_t h0 = 0; h0 < g.H; h0 += G) {
-    const uint32_t gh = xp_min(G, g.H - h0), rs = xp_to_row_stride(g, gh);
+  for (uint32_t h0 = first; h0 < end; h0 += G) {
+    const uint32_t gh = xp_min(G, end - h0), rs = xp_to_row_stride(g, gh);
     wave_units(xp_to_load_count(g, gh), lane,
                [&](uint32_t u) {
                  UnitOffs o;
@@ -377,15 +378,16 @@ __device__ void xpacked_to_block(const uint8_t* src, uint8_t* dst, uint32_t k, c
   }
 }
 
-// x-packed block `src` -> host (token-major) piece `dst`; k = 0 key, 1 value.
+// Heads [first, end) of x-packed block `src` -> host (token-major) piece `dst`; k = 0
+// key, 1 value.
 template <uint32_t E>
 __device__ void xpacked_from_block(const uint8_t* src, uint8_t* dst, uint32_t k, const XGeom& g, lds_u8* lds,
-                                   uint32_t lane) {
+                                   uint32_t lane, uint32_t first, uint32_t end) {
   const uint32_t G = xp_from_heads(g, k), rs = xp_from_row_stride(g, k);
   auto to_lds = [&](uint32_t o, u32x4 v) { *reinterpret_cast<lu4*>(lds + o) = v; };
   auto to_dst = [&](uint32_t o, u32x4 v) { *(gu4*)(dst + o) = v; };
-  for (uint32_t h0 = 0; h0 < g.H; h0 += G) {
-    const uint32_t gh = xp_min(G, g.H - h0);
+  for (uint32_t h0 = first; h0 < end; h0 += G) {
+    const uint32_t gh = xp_min(G, end - h0);
     const uint8_t* in = src + h0 * g.B * g.R;  // the group is one contiguous range of the block
     wave_units(xp_from_load_count(g, k, gh), lane,
                [&](uint32_t v) { return UnitOffs{v * 16, xp_from_load_lds(g, k, v)}; },
@@ -405,11 +407,12 @@ __device__ void xpacked_from_block(const uint8_t* src, uint8_t* dst, uint32_t k,
 
 template <uint32_t E>
 __device__ __forceinline__ void xpacked_piece(const uint8_t* src, uint8_t* dst, bool to_block, uint32_t k,
-                                              const XGeom& g, lds_u8* lds, uint32_t lane) {
+                                              const XGeom& g, lds_u8* lds, uint32_t lane, uint32_t first,
+                                              uint32_t end) {
   if (to_block)
-    xpacked_to_block<E>(src, dst, k, g, lds, lane);
+    xpacked_to_block<E>(src, dst, k, g, lds, lane, first, end);
   else
-    xpacked_from_block<E>(src, dst, k, g, lds, lane);
+    xpacked_from_block<E>(src, dst, k, g, lds, lane, first, end);
 }
 
 // ---------------------------------------------------------------- head-major KV layout
@@ -482,7 +485,7 @@ __device__ __forceinline__ void transfer_body(const KernelArgs& a) {
           hnd_piece(src, dst, kind == kEntryToPaged, xg, lane);
           continue;
         } else if constexpr (kXE != 0) {
-          xpacked_piece<kXE>(src, dst, kind == kEntryToPaged, p & 1u, xg, wave_lds, lane);
+          xpacked_piece<kXE>(src, dst, kind == kEntryToPaged, p & 1u, xg, wave_lds, lane, 0, xg.H);
           continue;
         }
       }
@@ -762,8 +765,8 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_kernel(PoolArgs a) {
 }
 
 // Pieces span by span (a.g counts a span as a row), in HBM or over the link:
-// x-packed ones (kXE: element bytes) whole, through the wave's LDS tile, a.group at
-// a time; kXE = 0, pieces or addresses that are no multiple of 16, by wave_copy.
+// x-packed ones (kXE: element bytes) through the wave's LDS tile, whole or by heads,
+// a.group at a time; kXE = 0, pieces or addresses that are no multiple of 16, by wave_copy.
 template <uint32_t kXE>
 __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -779,11 +782,14 @@ __global__ __launch_bounds__(kBlock) void mma_kv_pool_span_kernel(PoolArgs a) {
       PoolEnds e = pool_ends(a, pp);
       e.from = lane_u64(e.from, 0);
       e.to = lane_u64(e.to, 0);
+      const uint32_t part = static_cast<uint32_t>(w - static_cast<uint64_t>(q) * a.g.rows.d);
       if constexpr (kXE != 0) {
+        const uint32_t h0 = part * a.span;
         xpacked_piece<kXE>(reinterpret_cast<const uint8_t*>(e.from), reinterpret_cast<uint8_t*>(e.to), a.to_paged,
-                           pp.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane);
+                           pp.p & 1u, g, (lds_u8*)(mma_dyn_lds) + wave * a.lds_wave, lane, h0,
+                           min(g.H, h0 + a.span));
       } else {
-        const uint64_t off = (w - static_cast<uint64_t>(q) * a.g.rows.d) * a.span;
+        const uint64_t off = static_cast<uint64_t>(part) * a.span;
         wave_copy(reinterpret_cast<const uint8_t*>(e.from + off), reinterpret_cast<uint8_t*>(e.to + off),
                   min(static_cast<uint64_t>(a.span), a.piece - off), lane);
       }
@@ -1133,12 +1139,17 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
         : p.elem == 2 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<2>)
         : p.elem == 4 ? reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<4>)
                       : reinterpret_cast<const void*>(&mma_kv_pool_span_kernel<8>);
-    p.g.rows = fast_div(1);
-    p.g.waves = p.g.total;
+    // Claimed fetches go by the heads that fill the tile: with whole pieces the last
+    // ones of few kept single waves busy. 192 pieces of 32 and 64 KiB 126 / 121 and
+    // 250 / 236 us, 6 blocks of 4 MiB 488 / 457 (the entries of whole transfers: 121,
+    // 239, 461). With fixed shares whole pieces are better: 3 MiB 66.8 / 71.3.
+    p.span = p.claim && p.to_paged ? xp_to_heads(XGeom{p.tokens, p.heads, p.row_bytes, p.elem, p.lds_wave}) : p.heads;
+    p.g.rows = fast_div((p.heads + p.span - 1) / p.span);
+    p.g.waves = static_cast<uint64_t>(p.g.total) * p.g.rows.d;
     // A claim's round trip pays for 8 KiB at least; with few waves for more, as they
     // lose less at the end.
     if (p.claim)
-      p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / p.piece));
+      p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / (p.piece / p.heads * p.span)));
     spans = span_count(p.g.waves, p.group);
   } else if (layout == kKvLayoutXPacked) {
     const uint32_t x = 16 / p.elem, hc = p.heads * (p.row_bytes / 16);

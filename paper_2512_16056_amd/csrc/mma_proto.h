@@ -195,7 +195,7 @@ struct PoolArgs {
   uint32_t tokens, heads, row_bytes, elem, lds_wave;
   PoolGeom gv;              // x-packed blocks: the value pieces (g: the key pieces)
   XpMap xp;
-  uint32_t span;            // bytes of a span where 16-byte units cannot move
+  uint32_t span;            // of a span: bytes where 16-byte units cannot move, heads through the LDS tile
   uint32_t link, group;     // 1: over the link; spans that go together
   uint32_t words;           // of w in use
   uint32_t tags;            // > 0: no counters, workgroup i writes done[i], done[i + grid], ... below tags

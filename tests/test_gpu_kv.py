@@ -690,6 +690,9 @@ CLAIM_SHAPES = {
                         host_num_slots=264, n_blocks=260), mma.MMA_KV_LAYOUT_PIECE),
     "hnd": (W.KVShape(layers=8, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2, gpu_num_blocks=266,
                       host_num_slots=264, n_blocks=260), mma.MMA_KV_LAYOUT_HND),
+    # 23 MiB of 28 KiB pieces, fetched by groups of heads that do not divide them
+    "xpacked_heads": (W.KVShape(layers=8, block_tokens=16, kv_heads=7, head_dim=128, elem_bytes=2, gpu_num_blocks=60,
+                                host_num_slots=56, n_blocks=53), mma.MMA_KV_LAYOUT_XPACKED),
     # 17.8 MiB of 2 KiB pieces, through registers: keys and values in one walk
     "xpacked": (W.KVShape(layers=24, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=200,
                           host_num_slots=195, n_blocks=190), mma.MMA_KV_LAYOUT_XPACKED),

@@ -38,7 +38,7 @@ def emu(tmp_path_factory):
     lib = ctypes.CDLL(out)
     f = lib.emu_xpacked
     f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int] + [ctypes.c_uint32] * 5
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int] + [ctypes.c_uint32] * 6
     h = lib.emu_hnd
     h.restype = ctypes.c_int
     h.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int] + [ctypes.c_uint32] * 3
@@ -62,14 +62,14 @@ def test_xpacked_index_maps_match_oracle(emu, shape):
     r = np.random.default_rng(sum(shape))
     piece = np.ascontiguousarray(r.integers(0, 256, B * H * D * E, dtype=np.uint8))
     for cap in _caps(B, H, D, E):
-        for k in (0, 1):
+        for k, per in [(0, H), (1, H), (0, 1), (1, 1), (0, 3), (1, 3)]:  # heads per span: whole pieces or parts
             want = okv.piece_to_block(piece, k, XP, (B, H, D, E))
             got = np.zeros_like(piece)
-            rc = emu(piece.ctypes.data, got.ctypes.data, 1, k, B, H, D * E, E, cap)
+            rc = emu(piece.ctypes.data, got.ctypes.data, 1, k, B, H, D * E, E, cap, per)
             assert rc == 0, (shape, cap, k, "to_block", rc)
             assert np.array_equal(got, want), (shape, cap, k, "to_block")
             back = np.zeros_like(piece)
-            rc = emu(want.ctypes.data, back.ctypes.data, 0, k, B, H, D * E, E, cap)
+            rc = emu(want.ctypes.data, back.ctypes.data, 0, k, B, H, D * E, E, cap, per)
             assert rc == 0, (shape, cap, k, "from_block", rc)
             assert np.array_equal(back, piece), (shape, cap, k, "from_block")
 
@@ -79,7 +79,7 @@ def test_emulator_catches_a_wrong_map(emu):
     B, H, D, E = 16, 2, 128, 2
     piece = np.zeros(B * H * D * E, np.uint8)
     got = np.zeros_like(piece)
-    assert emu(piece.ctypes.data, got.ctypes.data, 1, 1, B, H, D * E, E, 1024) != 0
+    assert emu(piece.ctypes.data, got.ctypes.data, 1, 1, B, H, D * E, E, 1024, H) != 0
 
 
 HND_SHAPES = [(16, 8, 128, 2), (16, 8, 64, 2), (16, 1, 128, 2), (1, 8, 128, 2), (32, 8, 128, 1), (8, 3, 16, 2),
