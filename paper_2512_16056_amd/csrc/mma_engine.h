@@ -373,10 +373,14 @@ class Engine {
     if ((rc = be_->alloc_device_state(sizeof(DevState) * kRecords, &d)) != MMA_OK) return rc;
     ds_ = static_cast<DevState*>(d);
     for (uint32_t i = 0; i < kRecords; ++i) free_recs_.push_back(i);
-    if ((rc = be_->alloc_records(sizeof(uint64_t) * kLightWords * kLightSlots, &h, &d)) != MMA_OK) return rc;
+    if ((rc = be_->alloc_records(sizeof(uint64_t) * kPrefill * kLightSlots, &h, &d)) != MMA_OK) return rc;
     light_ = static_cast<uint64_t*>(h);
     light_dev_ = static_cast<uint64_t*>(d);
-    memset(light_, 0, sizeof(uint64_t) * kLightWords * kLightSlots);
+    memset(light_, 0, sizeof(uint64_t) * kPrefill * kLightSlots);
+    if ((rc = be_->alloc_records(sizeof(uint64_t) * kLightSlots, &h, &d)) != MMA_OK) return rc;
+    link_started_ = static_cast<uint64_t*>(h);
+    link_started_dev_ = static_cast<uint64_t*>(d);
+    memset(link_started_, 0, sizeof(uint64_t) * kLightSlots);
     for (uint32_t i = 0; i < kLightSlots; ++i) free_light_.push_back(i);
     light_ring_.reset(new CuEntry[kPrefill + kRingSize]);
     if ((rc = be_->alloc_records(sizeof(uint64_t) * kPoolTabEntries, &h, &d)) != MMA_OK) return rc;
@@ -474,13 +478,18 @@ class Engine {
     }
     cv_.notify_all();
     thread_.join();
+    {  // the other direction's thread may still ask
+      std::lock_guard<std::mutex> g(links_mu_);
+      links_.clear();
+      n_links_ = 0;
+    }
     if (!release) {
       slots_.clear();
       dev_sig_.clear();
       dev_sig_val_.clear();
       ds_ = nullptr;
       recs_ = nullptr;
-      light_ = nullptr;
+      light_ = link_started_ = nullptr;
       pool_tab_ = nullptr;
       pool_tab_copy_ = nullptr;
       pool_ctr_ = nullptr;
@@ -494,12 +503,13 @@ class Engine {
     if (ds_) be_->free_device_state(ds_);
     if (recs_) be_->free_records(recs_);
     if (light_) be_->free_records(light_);
+    if (link_started_) be_->free_records(link_started_);
     if (pool_tab_) be_->free_records(pool_tab_);
     if (pool_tab_copy_) be_->free_device_state(pool_tab_copy_);
     if (pool_ctr_) be_->free_device_state(pool_ctr_);
     ds_ = nullptr;
     recs_ = nullptr;
-    light_ = nullptr;
+    light_ = link_started_ = nullptr;
     pool_tab_ = nullptr;
     pool_tab_copy_ = nullptr;
     pool_ctr_ = nullptr;
@@ -569,7 +579,7 @@ class Engine {
     std::lock_guard<std::mutex> g(links_mu_);
     drop_ended_links();
     for (const LinkRun& r : links_)
-      if (ld_acq(r.words + kPrefill) == make_tag(r.seq, 0)) return true;
+      if (ld_acq(r.started) == make_tag(r.seq, 0)) return true;
     return false;
   }
 
@@ -684,7 +694,7 @@ class Engine {
       x->light = static_cast<int32_t>(i);
       x->rec = nullptr;
       x->ring = light_ring_.get();
-      x->done_host = light_ + static_cast<uint64_t>(i) * kLightWords;
+      x->done_host = light_ + static_cast<uint64_t>(i) * kPrefill;
     } else {
       x->rec_idx = i;
       x->rec = &recs_[i];
@@ -904,7 +914,7 @@ class Engine {
       a.pool_claim = link_claims(dir_, kv->layout, x->bytes) ? 1 : 0;
       if (!a.pool_claim) x->pushed = a.pool_wgs;
       x->link_large = x->bytes > cfg_.whole[dir_];
-      if (x->link_large) a.pool_started = a.done + kPrefill;
+      if (x->link_large) a.pool_started = link_started_dev_ + x->light;
     }
     a.pool_ctr = pool_ctr_ + static_cast<uint64_t>(x->light) * kPoolCtrWords;
     a.pool_base = x->pool_base;
@@ -939,7 +949,7 @@ class Engine {
     if (x->light >= 0) {
       a.rec = nullptr;
       a.ds = nullptr;
-      a.done = light_dev_ + static_cast<uint64_t>(x->light) * kLightWords;
+      a.done = light_dev_ + static_cast<uint64_t>(x->light) * kPrefill;
     } else {
       a.rec = rec_dev(x->rec_idx);
       a.ds = ds(x->rec_idx);
@@ -1126,7 +1136,7 @@ class Engine {
     if (x->link_large) {
       std::lock_guard<std::mutex> g(links_mu_);
       drop_ended_links();
-      links_.push_back(LinkRun{x->done_host, x->seq, static_cast<uint32_t>(x->pushed)});
+      links_.push_back(LinkRun{link_started_ + x->light, x->done_host, x->seq, static_cast<uint32_t>(x->pushed)});
       n_links_.store(static_cast<uint32_t>(links_.size()), std::memory_order_release);
     }
     std::lock_guard<std::mutex> g(dev_mu_);
@@ -1672,7 +1682,7 @@ class Engine {
   void drop_ended_links() const {
     const auto ended = [](const LinkRun& r) {
       for (uint32_t t = 0; t < r.tags; ++t)
-        if (static_cast<int32_t>((ld_acq(r.words + t) >> 32) - r.seq) < 0) return false;
+        if (static_cast<int32_t>((ld_acq(r.done + t) >> 32) - r.seq) < 0) return false;
       return true;
     };
     links_.erase(std::remove_if(links_.begin(), links_.end(), ended), links_.end());
@@ -2081,7 +2091,7 @@ class Engine {
   Stats* st_;
   Record* recs_ = nullptr;
   Record* recs_dev_ = nullptr;
-  uint64_t* light_ = nullptr;      // light slots' tags, kLightWords per slot (host address)
+  uint64_t* light_ = nullptr;      // light slots' done tags, kPrefill per slot (host address)
   uint64_t* light_dev_ = nullptr;  // the same, device address
   std::unique_ptr<CuEntry[]> light_ring_;  // scratch ring: light transfers' entries go to the kernel args
   uint64_t* pool_tab_ = nullptr;      // HBM pool launches' table arena (host address)
@@ -2113,11 +2123,13 @@ class Engine {
   std::atomic<uint64_t> eng_bytes_[MMA_MAX_SDMA] = {};
   std::atomic<uint64_t> moving_until_{0};  // see peer_moving (read by the other direction)
   std::atomic<const void*> moving_stream_{nullptr};  // of what moves, or moved last
-  // Large launches over the link in flight: the words of their light slots (kept as
-  // long as the engine is), sequence numbers and done tags. The other direction's
-  // engine thread looks, and forgets those that have ended.
+  // Large launches over the link in flight: their start and done tags (kept as long as
+  // the engine is), sequence and tag numbers. The other direction's engine thread
+  // looks, and forgets those that have ended.
+  uint64_t* link_started_ = nullptr;      // a start tag per light slot (host address)
+  uint64_t* link_started_dev_ = nullptr;  // the same, device address
   struct LinkRun {
-    const uint64_t* words;
+    const uint64_t *started, *done;
     uint64_t seq;
     uint32_t tags;
   };

@@ -29,9 +29,6 @@ constexpr uint32_t kRecords = 64;      // records per direction (transfers in fl
 constexpr uint32_t kLightSlots = 4096;
 constexpr uint32_t kMaxWorkgroups = 256;  // dummy-task kernel size limit (ring keeps one slot per wave)
 constexpr uint32_t kPrefill = 48;      // ring entries also passed in the kernel arguments (linear kinds)
-// Words of a light slot: its done tags, and in word kPrefill the start tag of a launch
-// over the link that the other direction's paths depend on (one line of its own).
-constexpr uint32_t kLightWords = kPrefill + 8;
 constexpr uint32_t kMaxLayers = 256;   // KV layer pointers per record
 constexpr uint32_t kMaxLdsPerWave = 36 * 1024;  // x-packed KV tiles: 4 waves x 36 KiB + 2 KiB of a CU's 160 KiB
 constexpr uint32_t kWave = 64;
@@ -130,7 +127,7 @@ struct alignas(128) DevState {
 struct KernelArgs {
   Record* rec;              // device-visible address of the record (null for a light slot)
   DevState* ds;
-  uint64_t* done;           // device-visible done tags: the record's, or a light slot's
+  uint64_t* done;           // device-visible done tags: the record's, or a light slot's kPrefill
   uint64_t seq;
   uint64_t watchdog_ticks;  // wall-clock ticks without progress before giving up
   uint32_t total_waves;
