@@ -1089,25 +1089,28 @@ hipError_t launch_whole(const KernelArgs& args, uint32_t grid, hipStream_t strea
 }
 
 // Whether x-packed pieces that are not staged (xp_stages) go through registers
-// (mma_kv_pool_xp_kernel) or whole through a wave's LDS tile, by what was faster
-// (LDS / registers, us):
-//  - pieces below 4 KiB, of which registers take several at a time: 1 GiB of 2 KiB
-//    pieces in HBM, fetch 1243 / 503, offload 1228 / 585; 64 MiB over the link 1415
-//    / 1221; but 1 GiB of 6 KiB pieces, fetch 541 / 755: a lane's stores go to x
-//    dimensions, 32 bytes of each row at a time;
-//  - offloads in HBM, whose stores are whole rows of tokens: 512 blocks 557 / 446,
-//    of 6 KiB pieces 1028 / 638; and fetches there that are over before HBM is the
-//    limit: 2 MiB 14.4 / 12.6, 64 MiB 54.1 / 40.2, 128 MiB 59.9 / 67.7; one-byte
-//    elements 2 MiB 17.3 / 12.6, 37 MiB 20.9 / 24.4; with more than 16 KiB of tile a
-//    wave (one workgroup per CU) 25 MiB 40.2 / 13.0, 200 MiB 60.9 / 47.9, 1 GiB 424
-//    / 439;
+// (mma_kv_pool_xp_kernel) or through a wave's LDS tile, by what was faster (LDS /
+// registers, us):
+//  - pieces below 4 KiB, of which registers take several at a time: 64 MiB of 2 KiB
+//    pieces over the link 1415 / 1221;
+//  - in HBM small pieces of elements of two bytes and more: 1 GiB fetched of 4, 5 and 6
+//    KiB pieces 658 / 490, 566 / 488, 503 / 486, 64 MiB 44 / 28, 38 / 28, 34 / 28;
+//  - offloads in HBM, whose stores are whole rows of tokens: 1 GiB of 6 KiB pieces
+//    531 / 504, of one-byte elements 985 / 652; only 24 tokens x 5 x 80 (557 / 620) and
+//    48 x 8 x 128 (474 / 504) are the other way round, above 256 MiB;
+//  - other fetches in HBM that are small. One-byte elements, 8 KiB pieces: 8 MiB 10.2 /
+//    11.0, 64 MiB 30 / 40, 1 GiB 459 / 664. Token groups that are no power of two: 24
+//    tokens x 8 x 128, 64 MiB 33 / 28, 126 MiB 63 / 59, 1 GiB 440 / 460; 48 x 8 x 128,
+//    64 MiB 46 / 27, 252 MiB 139 / 119, 1 GiB 451 / 450; with more than 16 KiB of tile a
+//    wave (one workgroup per CU), 48 x 8 x 256, 63 MiB 68 / 27, 252 MiB 159 / 116, 1 GiB
+//    450 / 442;
 //  - over the link fetches whose tile is above 16 KiB a wave: 1 block of 32 tokens
 //    x 8 heads x 256 dimensions 306 / 267, but of 16 x 8 x 128 43.8 / 48.7; and
 //    offloads below 16 MiB in 8 x 8 squares: 48.3 / 45.6, but with 50 units a token
 //    175 / 186 at 8 MiB, and 64 MiB 1292 / 1361.
 bool xp_registers(const PoolArgs& p, uint32_t n, bool link) {
   const uint64_t bytes = static_cast<uint64_t>(n) * 2 * p.layers * p.piece;
-  if (p.piece < 4096) return true;
+  if (p.piece < 4096 || (!link && p.elem > 1 && p.piece < 8192)) return true;
   if (!link) return !p.to_paged || bytes <= (p.lds_wave > 16 * 1024 ? 256ull << 20 : (p.elem > 1 ? 64ull : 8ull) << 20);
   if (p.to_paged) return p.lds_wave > 16 * 1024;
   return bytes < (16ull << 20) && p.tokens % 8 == 0 && p.heads * (p.row_bytes / 16) % 8 == 0;

@@ -768,13 +768,18 @@ def test_kv_link_launch_with_few_workgroups(kv_heads, workgroups, gpu_layout):
 
 
 XP_POOL_SHAPES = {
-    # pieces below and at the size that goes through LDS, with 8 and 9 MiB and a bit in all
+    # pieces below and above 4 KiB through registers, with 8 and 9 MiB and a bit in all
     "small_pieces": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=64, elem_bytes=2, gpu_num_blocks=1300,
                               host_num_slots=1250, n_blocks=1200),
-    "lds_fetch": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=520,
+    "ragged_rows": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=520,
                            host_num_slots=510, n_blocks=500),
-    "reg_fetch": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=420,
+    "ragged_rows_fewer": W.KVShape(layers=2, block_tokens=16, kv_heads=2, head_dim=80, elem_bytes=2, gpu_num_blocks=420,
                            host_num_slots=410, n_blocks=400),
+    # fetches through LDS: one-byte elements above 8 MiB, three token groups above 64 MiB
+    "lds_bytes": W.KVShape(layers=4, block_tokens=16, kv_heads=7, head_dim=64, elem_bytes=1, gpu_num_blocks=190,
+                           host_num_slots=185, n_blocks=180),
+    "lds_groups": W.KVShape(layers=8, block_tokens=24, kv_heads=8, head_dim=128, elem_bytes=2, gpu_num_blocks=92,
+                            host_num_slots=90, n_blocks=88),
     "words": W.KVShape(layers=1, block_tokens=4, kv_heads=4, head_dim=64, elem_bytes=4, gpu_num_blocks=20,
                        host_num_slots=18, n_blocks=17),
     "doubles": W.KVShape(layers=1, block_tokens=2, kv_heads=5, head_dim=8, elem_bytes=8, gpu_num_blocks=90,
