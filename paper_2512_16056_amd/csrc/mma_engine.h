@@ -599,11 +599,17 @@ class Engine {
   // A KV transfer with its pool in host memory that one launch over the link
   // carries alone, unless that route is off (cu_whole_bytes[_d2h] = 1):
   //  - within the whole-transfer limit, any but a few large pieces as they are on
-  //    the host, whose entries of whole pieces (whole_kv_per) are a little faster:
-  //    1, 2, 3 blocks of 2 MiB fetched in 43.3, 82.1, 120.1 us, by one launch 43.8,
-  //    83.0, 121.2; but head-major 49.5 / 44.0, x-packed 51.4 / 43.2, one block of
-  //    768 KiB 21.2 / 19.4, 8 blocks 318 / 313, 56 blocks of 147 KiB, which are
-  //    too many entries, 578 / 155;
+  //    the host, whose entries of whole pieces (whole_kv_per) are a little faster.
+  //    Entries / one launch, us, fetch: 1, 2, 3 blocks of 2 MiB 43.3 / 43.8, 82.1 /
+  //    83.0, 120.1 / 121.2; 48 pieces a block, of 28 KiB, 2 blocks 54.3 / 57.7, 6
+  //    151.2 / 157.6; of 16 KiB, 4 blocks 61.1 / 62.7, 7 102.1 / 106.2; of 12.5 KiB, 4
+  //    blocks 48.7 / 52.5, 20 223 / 233; of 10 KiB, 10 blocks 92.4 / 97.3; but of 8
+  //    KiB (80 pieces), 3, 7, 12 blocks 46.4 / 42.8, 91.7 / 90.5, 151.2 / 149.7.
+  //    Offload: of 16 KiB, 4, 8 blocks 63.3 / 65.8, 122.1 / 128.3; but of 14 KiB, 5
+  //    blocks 74.8 / 71.1, of 12 KiB, 7 blocks 89.0 / 85.6. Other layouts: head-major
+  //    49.5 / 44.0, x-packed 51.4 / 43.2; below 1 MiB, one block of 768 KiB 21.2 /
+  //    19.4; above 12 MiB, 8 blocks of 2 MiB 318 / 313; 56 blocks of 147 KiB, which are
+  //    too many entries, by the ring 578, by one launch 155;
   //  - beyond it, blocks of at most 1 MiB (offload: 512 KiB). The engine thread's
   //    micro-tasks never span blocks, so with small ones the CU path's queue holds too
   //    little and the copy engines get short commands.
@@ -646,8 +652,9 @@ class Engine {
         return false;
       return slot_bytes <= (dir_ == MMA_H2D ? MiB : 512 * KiB);
     }
-    const bool few_large = kv.layout == kKvLayoutPiece && kv.piece >= 32 * KiB && payload_bytes >= MiB;
-    return !few_large || payload_bytes > 12 * MiB;
+    const bool few_large = kv.layout == kKvLayoutPiece && kv.piece > (dir_ == MMA_H2D ? 8 : 15) * KiB &&
+                           payload_bytes >= MiB && payload_bytes <= 12 * MiB;
+    return !few_large || whole_kv_per(x) == 0;
   }
 
   // Pieces per CU entry of a whole KV transfer: the engine thread's entry size,

@@ -919,6 +919,13 @@ const std::vector<LinkCase> kFewWorkgroups = {
     {MMA_H2D, kP, 32 * KiB, 4, 2048, 1, true}, {MMA_H2D, kH, 2 * KiB, 16, 8192, 1, true},
     {MMA_H2D, kP, 2 * KiB, 16, 8192, 1, true}, {MMA_D2H, kH, 8 * KiB, 24, 53, 2, true},
 };
+const std::vector<LinkCase> kFewLarge = {
+    {MMA_H2D, kP, 16 * KiB, 24, 7, 16, false}, {MMA_H2D, kP, 12800, 24, 4, 16, false}, {MMA_H2D, kP, 28 * KiB, 24, 2, 16, false},
+    {MMA_H2D, kP, 8 * KiB, 24, 18, 16, true},  {MMA_H2D, kP, 16 * KiB, 24, 30, 16, true}, {MMA_H2D, kP, 10 * KiB, 24, 2, 16, true},
+    {MMA_D2H, kP, 16 * KiB, 24, 7, 16, false}, {MMA_D2H, kP, 12 * KiB, 24, 7, 16, true},
+    {MMA_H2D, kH, 16 * KiB, 24, 7, 16, true},  {MMA_H2D, kX, 32 * KiB, 32, 3, 16, true},
+    {MMA_H2D, kP, 32 * KiB, 1, 40, 16, false}, {MMA_H2D, kP, 32 * KiB, 1, 100, 16, true},  // 100 blocks are too many entries
+};
 const std::vector<LinkCase> kChunks = {
     {MMA_H2D, kP, 32 * KiB, 32, 256, 16, false, 8 * MiB}, {MMA_H2D, kP, 32 * KiB, 16, 512, 16, true, 8 * MiB},
     {MMA_D2H, kP, 32 * KiB, 16, 512, 16, false, 8 * MiB}, {MMA_D2H, kP, 32 * KiB, 8, 1024, 16, true, 8 * MiB},
@@ -1788,6 +1795,7 @@ int main(int argc, char** argv) {
     whole_transfers_on_cu();
     whole_kv_transfers();
     link_routes("few workgroups", kFewWorkgroups);
+    link_routes("a few large pieces", kFewLarge);
     link_routes("chunk sizes", kChunks);
     hbm_pool_launches();
     deep_queue_does_not_block();
