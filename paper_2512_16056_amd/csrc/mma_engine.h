@@ -145,7 +145,7 @@ struct Transfer {
   // table arena, segments [tab_seg, tab_seg + tab_nseg).
   bool pool_launch = false;
   const void* stream = nullptr;  // the caller's
-  bool link_large = false;  // over the link and above the whole-transfer limit: moves for the other direction (see set_peer)
+  bool link_large = false;  // over the link, above the whole-transfer limit: moves for the other direction (set_peer)
   uint64_t pool_base = 0;
   std::vector<uint64_t> pool_pairs;
   std::vector<uint64_t> pool_tmp;  // room to sort them
@@ -652,8 +652,8 @@ class Engine {
         return false;
       return slot_bytes <= (dir_ == MMA_H2D ? MiB : 512 * KiB);
     }
-    const bool few_large = kv.layout == kKvLayoutPiece && kv.piece > (dir_ == MMA_H2D ? 8 : 15) * KiB &&
-                           payload_bytes >= MiB && payload_bytes <= 12 * MiB;
+    const bool large = dir_ == MMA_H2D ? kv.piece > 8 * KiB : kv.piece >= 16 * KiB;
+    const bool few_large = kv.layout == kKvLayoutPiece && large && payload_bytes >= MiB && payload_bytes <= 12 * MiB;
     return !few_large || whole_kv_per(x) == 0;
   }
 

@@ -708,9 +708,9 @@ __device__ __forceinline__ void pool_begin(const PoolArgs& a) {
 // through the stream, when the kernel ends, as for any kernel (a device-wide
 // release per workgroup would write back the L2 of its XCD each time). Counts on
 // one address go one after the other, some 12 ns each, so 32 workgroups and more
-// count in groups of at least 16 first (pool_groups): with 512 and more to a group a
-// launch of 2048 took 8 us longer. A launch of many has its tag written by a launch of its
-// own instead (kPoolTagLaunch).
+// count in groups of at least 16 first (pool_last): with 512 and more to a group a
+// launch of 2048 took 8 us longer. A launch of many has its tag written by a launch of
+// its own instead (kPoolTagLaunch).
 __device__ __forceinline__ void pool_finish(const PoolArgs& a) {
   if (a.clear && blockIdx.x == 0 && threadIdx.x == 0)
     __hip_atomic_store(a.clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -849,6 +849,7 @@ __device__ __forceinline__ void transpose_units(u32x4 (&v)[16 / E]) {
 //   128 MiB                          54 / 45      56 / 47
 //   1 GiB, one-byte elements        469 / 421    534 / 426
 //   469 MiB, 32 tokens x 5 x 80     208 / 192    266 / 229
+// (by call, on one box; 2 GiB fetched took 820 to 826 on others, the kernel alone 800).
 // 1, 2 and 4 rows of keys: 2 GiB 1110, 879, 817 and 1092, 871, 846; one-byte
 // elements -, 572, 459.
 template <uint32_t E, bool kLink, bool kStage>
@@ -1041,7 +1042,8 @@ __global__ __launch_bounds__(kBlock) void mma_kv_noalloc_table_kernel(NoallocTab
 
 // Claim words [0, n) of the scratch array to 0.
 __global__ void mma_kv_noalloc_clear_kernel(uint32_t* w, uint32_t n) {
-  for (uint32_t i = threadIdx.x; i < n; i += kWave) __hip_atomic_store(w + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (uint32_t i = threadIdx.x; i < n; i += kWave)
+    __hip_atomic_store(w + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // digest += sum_i (w_i + 1) * (2i + 1) mod 2^64 over nw words (+ one zero-padded
@@ -1151,8 +1153,9 @@ hipError_t launch_pool_kernel(PoolArgs& p, uint32_t n, uint32_t layout, bool ali
     p.g.waves = static_cast<uint64_t>(p.g.total) * p.g.rows.d;
     // A claim's round trip pays for 8 KiB at least; with few waves for more, as they
     // lose less at the end.
+    const uint64_t bytes = p.piece / p.heads * p.span;
     if (p.claim)
-      p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / (p.piece / p.heads * p.span)));
+      p.group = static_cast<uint32_t>(std::max<uint64_t>(1, (link_few(wgs) ? kLinkFewSpan : kPoolSpan) / bytes));
     spans = span_count(p.g.waves, p.group);
   } else if (layout == kKvLayoutXPacked) {
     const uint32_t x = 16 / p.elem, hc = p.heads * (p.row_bytes / 16);
