@@ -182,11 +182,11 @@ def test_kv_all_permutations(paths):
 
 POOL_SHAPES = {
     **SHAPES,
-    # pieces of 8 KiB + 48 bytes: one full span of the pool kernel and a short one
+    # pieces of 8 KiB + 48 bytes: eight full rows of a wave and a short one
     "span_tail": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=515, elem_bytes=1,
                            gpu_num_blocks=90, host_num_slots=80, n_blocks=70),
-    # 32 KiB pieces, 3000 blocks: the launch's full 8192 workgroups, 12 spans each, so waves
-    # move several spans and cross from one block into the next
+    # 32 KiB pieces, 3000 blocks: 192,000 workgroups, too many to be counted, so a second launch
+    # writes the done tag; the table is copied to device memory before
     "wide": W.KVShape(layers=4, block_tokens=16, kv_heads=8, head_dim=128, elem_bytes=2,
                       gpu_num_blocks=3300, host_num_slots=3072, n_blocks=3000),
 }
@@ -474,8 +474,7 @@ def test_kv_hnd_offload(paths, shape, chunk):
 
 HND_POOL_SHAPES = {
     **HND_SHAPES,
-    # 9000 blocks of 512-byte pieces: a pool launch of 7200 workgroups with 5 pieces each, so
-    # waves move several pieces and cross from one block into the next
+    # 9000 blocks of 512-byte pieces, two to a wave's row: 4500 workgroups, counted in 64 groups
     "many_small": W.KVShape(layers=2, block_tokens=16, kv_heads=1, head_dim=16, elem_bytes=2,
                             gpu_num_blocks=9500, host_num_slots=9216, n_blocks=9000),
 }
